@@ -103,9 +103,9 @@ const char *hsma_version(void);
  *
  * Path: m <= 64 uses the register-resident small-solve kernel, one wavefront
  * per 64-column panel of B (Sec. 4.2); m > 64 uses the blocked path (Sec. 4.3):
- * diagonal blocks of edge I_B inverted in parallel, then recursive FP64
- * matrix-core updates and in-place diagonal-block solves, with I_B taken from
- * the compiled-in tuning table (Sec. 4.3.2).
+ * the rows are solved in panels, one launch each (16 x 16 diagonal blocks
+ * inverted in registers, the rest products), with recursive matrix-core
+ * updates between the panels.
  */
 hsma_status hsma_trsm(hsma_diag diag, int64_t m, int64_t n, const void *alpha,
                       const void *A, int64_t lda, void *B, int64_t ldb,
@@ -115,24 +115,20 @@ hsma_status hsma_trsm(hsma_diag diag, int64_t m, int64_t n, const void *alpha,
 /*
  * hsma_trsm_noalloc -- hsma_trsm for callers that cannot allocate device
  * memory: code under HIP graph capture, tight serving loops, harnesses that
- * forbid hipMalloc.  Same operation, arguments, path choice, I_B and kernels
- * as hsma_trsm, so the result is bit-for-bit the same; it calls no hipMalloc,
- * hipFree or other allocating routine.  The blocked path's workspace comes
- * from a fixed per-device scratch array of hsma_noalloc_scratch_bytes()
- * bytes (64 MiB) inside the library, which each GPU the library runs on
- * holds until the process ends.  A problem whose workspace does not fit
- * (hsma_trsm's blocked workspace: ceil(m/I_B) I_B^2 + (ceil(m/2) + I_B) I_B
- * elements; DTRSM up to m of about 16384 fits) returns
- * HSMA_WORKSPACE_TOO_SMALL before anything is enqueued.  Every call on one
- * GPU uses the same array: calls that overlap in time on one GPU (two
- * streams, two threads) race and give wrong results; serialise them.
+ * forbid hipMalloc.  Same operation, arguments, path choice and kernels as
+ * hsma_trsm, so the result is bit-for-bit the same; it calls no hipMalloc,
+ * hipFree or other allocating routine, and needs no device memory beyond its
+ * arguments.  The sizes it takes are bounded all the same: with I_B the tuning
+ * table's entry, ceil(m/I_B) I_B^2 + (ceil(m/2) + I_B) I_B elements have to
+ * fit hsma_noalloc_scratch_bytes() bytes (64 MiB; DTRSM up to m of about
+ * 16384), or it returns HSMA_WORKSPACE_TOO_SMALL before anything is enqueued.
  * Asynchronous on `stream`.
  */
 hsma_status hsma_trsm_noalloc(hsma_diag diag, int64_t m, int64_t n, const void *alpha,
                               const void *A, int64_t lda, void *B, int64_t ldb,
                               hsma_dtype dtype, hsma_stream_t stream);
 
-/* Bytes of the per-device scratch array of hsma_trsm_noalloc. */
+/* The size bound of hsma_trsm_noalloc in bytes. */
 uint64_t hsma_noalloc_scratch_bytes(void);
 
 /* ------------------------------------------------------------------------ */
@@ -215,8 +211,9 @@ typedef enum {
 
 /* Options of hsma_trsm_ex.  Zero-initialise and set what you need. */
 typedef struct {
-    int32_t block_size;   /* blocked-path diagonal-block edge I_B: 0 = tuning
-                             table (Sec. 4.3.2), else 16, 32, 64, 128 or 256 */
+    int32_t block_size;   /* rows of a panel of the blocked path: 16, 32, 64,
+                             128 or 256; 0 = as many as one launch takes (512
+                             real or 256 complex) */
     int32_t path;         /* 0 = automatic (m <= 64 small kernel, else blocked);
                              1 = force the small kernel (requires m <= 64);
                              2 = force the blocked path */
@@ -231,15 +228,13 @@ typedef struct {
                              formed by one triangular product whose order of
                              summation is independent of the solve's */
     int32_t use_graph;    /* 1: run the blocked schedule as a HIP graph, one
-                             per shape (dtype, diag, m, n, lda, ldb, I_B,
-                             precision): captured and instantiated on the
+                             per shape (dtype, diag, m, n, lda, ldb, panel
+                             height, precision): captured and instantiated on the
                              shape's first call, replayed with one
                              hipGraphLaunch after that, new A, B and alpha
                              moved into it with hipGraphExecUpdate.  Replays
-                             of one shape run one after another on the device
-                             (they share the graph-owned workspace that
-                             hsma_graph_cache_clear frees).  Ignored with
-                             refinement or the small path. */
+                             of one shape run one after another on the device.
+                             Ignored with refinement or the small path. */
     int32_t reserved[2];  /* must be zero */
     double refine_tol;    /* target for refine_steps = -1 (0 means 1e-13) */
 } hsma_trsm_options;
@@ -247,7 +242,9 @@ typedef struct {
 /* What hsma_trsm_ex did (filled before it returns). */
 typedef struct {
     int32_t path;         /* 1 small kernel, 2 blocked path, 0 nothing enqueued */
-    int32_t block_size;   /* I_B used by the blocked path, else 0 */
+    int32_t block_size;   /* the options' block_size, or the tuning table's I_B
+                             for the problem's scale (Sec. 4.3.2); 0 if the
+                             blocked path did not run */
     int32_t refine_steps; /* refinement steps taken */
     int32_t reserved[5];
     double backward_error;/* ||L X - alpha B0||_inf / (||L|| ||X|| + |alpha| ||B0||)
@@ -288,7 +285,7 @@ hsma_status hsma_trsm_ex(hsma_diag diag, int64_t m, int64_t n, const void *alpha
  */
 hsma_status hsma_mfma_peak(int32_t fp32, int64_t iters, double *tflops, double *shader_ghz);
 
-/* Destroy every cached graph and its workspace (waits for their work). */
+/* Destroy every cached graph (waits for their work). */
 hsma_status hsma_graph_cache_clear(void);
 
 /* Graph-cache counters since the library was loaded: graphs instantiated,
@@ -337,8 +334,8 @@ typedef struct {
  * *first_bad (if non-NULL), its status is returned and nothing is enqueued.
  * Problems with m <= 64 run in grouped launches (one per data type and
  * diagonal kind, one workgroup per 64-column panel, longest first); the rest take the
- * blocked path grouped: every problem keeps the schedule (I_B, inversions,
- * recursion) it gets alone, so its result is bit-for-bit the same, but the
+ * blocked path grouped: every problem keeps the schedule (panels, recursion)
+ * it gets alone, so its result is bit-for-bit the same, but the
  * k-th operation of all of them shares one launch.  Both parts are forked
  * onto library-owned streams and joined back into `stream`.  Asynchronous on
  * `stream`.  The problems' B matrices must not overlap each other or any A.
@@ -428,8 +425,9 @@ hsma_status hsma_generate_inputs(hsma_dtype dtype, int64_t m, int64_t n, uint64_
  *     its own completion event: the small class on the queue's small stream,
  *     the four blocked classes round-robin over the queue's other streams.  Synthetic
  *     inputs of a class are drawn in one launch on the class's stream first.
- * A request's footprint is its blocked-path workspace (a 4 KiB descriptor
- * share for small requests) plus, for synthetic requests, its L and B.
+ * A request's footprint is a share for its descriptors and scheduling (4 KiB
+ * for small requests, ceil(m/I_B) I_B^2 + (ceil(m/2) + I_B) I_B elements for
+ * larger ones) plus, for synthetic requests, its L and B.
  */
 typedef enum { HSMA_BACKEND_HIP = 0, HSMA_BACKEND_SIMULATED = 1 } hsma_backend;
 typedef enum { HSMA_INPUT_DEVICE = 0, HSMA_INPUT_SYNTHETIC = 1 } hsma_input_kind;

@@ -12,15 +12,13 @@
 
 namespace hsma {
 
-size_t blocked_workspace_bytes(bool cx, int64_t m, int ib);
-size_t blocked_workspace_bytes32(bool cx, int64_t m, int ib);
+int panel_span(bool cx, int block_size);
 hsma_status blocked_trsm32(bool cx, bool unit, int64_t m, int64_t n, cplx alpha, const float *A,
-                           int64_t lda, float *B, int64_t ldb, int ib, void *ws, hipStream_t s);
+                           int64_t lda, float *B, int64_t ldb, int span, hipStream_t s);
 hsma_status blocked_trsm(bool cx, bool unit, int64_t m, int64_t n, cplx alpha, const double *A,
-                         int64_t lda, double *B, int64_t ldb, int ib, void *ws, hipStream_t s,
-                         bool mixed);
+                         int64_t lda, double *B, int64_t ldb, int span, hipStream_t s, bool mixed);
 hsma_status blocked_trsm_graph(bool cx, bool unit, int64_t m, int64_t n, cplx alpha,
-                               const double *A, int64_t lda, double *B, int64_t ldb, int ib,
+                               const double *A, int64_t lda, double *B, int64_t ldb, int span,
                                bool mixed, hipStream_t s);
 hsma_status triangular_residual(bool cx, bool unit, int64_t m, int64_t n, const double *A,
                                 int64_t lda, const double *X, int64_t ldx, double *R, int64_t ldr,
@@ -99,6 +97,16 @@ int lookup_block_size(bool cx, int64_t m, int64_t n) {
     return best;
 }
 
+// The diagonal-block workspace of a blocked solve that inverts whole I_B
+// blocks (ceil(m / I_B) I_B^2 elements and a merge scratch of (ceil(m / 2) +
+// I_B) I_B).  The panel solve needs none of it; the formula still says which
+// sizes hsma_trsm_noalloc takes and what the queue reserves for a request.
+size_t blocked_workspace_bytes(bool cx, int64_t m, int ib) {
+    const int64_t nblk = (m + ib - 1) / ib;
+    const size_t es = cx ? 2 : 1;
+    return ((size_t)nblk * ib * ib * es + (size_t)((m + 1) / 2 + ib) * (size_t)ib * es) * sizeof(double);
+}
+
 bool valid_block_size(bool cx, int ib) {
     (void)cx;
     return ib == 16 || ib == 32 || ib == 64 || ib == 128 || ib == 256;
@@ -159,12 +167,9 @@ static hsma_status solve_once(bool cx, bool unit, int64_t m, int64_t n, cplx al,
     if (!valid_block_size(cx, ib)) return HSMA_INVALID_VALUE;
     if (path_used) *path_used = 2;
     if (ib_used) *ib_used = ib;
-    if (use_graph) return blocked_trsm_graph(cx, unit, m, n, al, Ad, lda, Bd, ldb, ib, mixed, s);
-    void *ws = nullptr;
-    HSMA_TRY(ws_alloc(&ws, blocked_workspace_bytes(cx, m, ib), s));
-    hsma_status st = blocked_trsm(cx, unit, m, n, al, Ad, lda, Bd, ldb, ib, ws, s, mixed);
-    hsma_status st2 = ws_free(ws, s);
-    return st != HSMA_SUCCESS ? st : st2;
+    const int span = panel_span(cx, ib_override);
+    if (use_graph) return blocked_trsm_graph(cx, unit, m, n, al, Ad, lda, Bd, ldb, span, mixed, s);
+    return blocked_trsm(cx, unit, m, n, al, Ad, lda, Bd, ldb, span, s, mixed);
 }
 
 // One FP32 solve in place (STRSM, CTRSM): small kernel or blocked path.
@@ -184,11 +189,7 @@ static hsma_status solve_once32(bool cx, bool unit, int64_t m, int64_t n, cplx a
     if (!valid_block_size(cx, ib)) return HSMA_INVALID_VALUE;
     if (path_used) *path_used = 2;
     if (ib_used) *ib_used = ib;
-    void *ws = nullptr;
-    HSMA_TRY(ws_alloc(&ws, blocked_workspace_bytes32(cx, m, ib), s));
-    hsma_status st = blocked_trsm32(cx, unit, m, n, al, Ad, lda, Bd, ldb, ib, ws, s);
-    hsma_status st2 = ws_free(ws, s);
-    return st != HSMA_SUCCESS ? st : st2;
+    return blocked_trsm32(cx, unit, m, n, al, Ad, lda, Bd, ldb, panel_span(cx, ib_override), s);
 }
 
 // Normwise backward error from the residual R (on the device): max row sums

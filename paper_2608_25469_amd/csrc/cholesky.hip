@@ -176,9 +176,8 @@ hsma_status potrf_rec(bool cx, int64_t n, double *A, int64_t lda, double *work, 
     HSMA_TRY(trsm_right_lower_keep(cx, n2, n1, A11, lda, A21, lda, work, s));
     // A22 <- A22 - L21 L21^H on the lower triangle: one product with the
     // lower-triangular store.
-    GemmBatch one_b;
     HSMA_TRY(launch_gemm(cx, GemmRole::Herk, (int)(es * n2), (int)n2, (int)(es * n1), cplx{-1.0, 0.0},
-                         A21, lda, work, es * n1, cplx{1.0, 0.0}, A22, es * lda, 0, one_b, s, 0, 1));
+                         A21, lda, work, es * n1, cplx{1.0, 0.0}, A22, es * lda, 0, s, 0, 1));
     return potrf_rec(cx, n2, A22, lda, work, s);
 }
 

@@ -1,22 +1,20 @@
 // HIP-graph replay of the blocked schedule, one graph per problem shape.
 //
-// A blocked solve is a fixed sequence of 2 log2(m/I_B) + ~10 dependent kernel
-// launches whose shape -- the kernels, grids and dependencies -- depends only
-// on (dtype, diag, m, n, lda, ldb, I_B, precision); the matrices and alpha
-// only change kernel arguments.  So a graph is captured once per shape (on a
-// library stream, with its own workspace, so nothing is allocated inside the
-// capture and no memset node is recorded: workspace initialisation is a
-// kernel) and instantiated once.  A later call with other pointers or
-// another alpha records the same launch sequence again (recording only, no
-// device submission) and moves the new arguments into the instantiated
-// graph with hipGraphExecUpdate, then replays it with one hipGraphLaunch.
+// A blocked solve is a fixed sequence of dependent kernel launches whose shape
+// -- the kernels, grids and dependencies -- depends only on (dtype, diag, m,
+// n, lda, ldb, panel height, precision); the matrices and alpha only change
+// kernel arguments.  So a graph is captured once per shape (on a library
+// stream; the schedule allocates nothing and records no memset node) and
+// instantiated once.  A later call with other pointers or another alpha
+// records the same launch sequence again (recording only, no device
+// submission) and moves the new arguments into the instantiated graph with
+// hipGraphExecUpdate, then replays it with one hipGraphLaunch.
 //
-// Each shape keeps two instantiated graphs used in turn, sharing the shape's
-// workspace: a graph is updated only after its previous replay (two calls
-// back) has finished, and every replay waits on the device for the other
-// graph's last replay, because both use the same workspace.  Replays of one
-// shape therefore run one after another, on any stream.  A small LRU bounds
-// the cache.
+// Each shape keeps two instantiated graphs used in turn: a graph is updated
+// only after its previous replay (two calls back) has finished, and every
+// replay waits on the device for the other graph's last replay.  Replays of
+// one shape therefore run one after another, on any stream.  A small LRU
+// bounds the cache.
 
 #include <cstring>
 #include <list>
@@ -26,16 +24,14 @@
 
 namespace hsma {
 
-size_t blocked_workspace_bytes(bool cx, int64_t m, int ib);
 hsma_status blocked_trsm(bool cx, bool unit, int64_t m, int64_t n, cplx alpha, const double *A,
-                         int64_t lda, double *B, int64_t ldb, int ib, void *ws, hipStream_t s,
-                         bool mixed);
+                         int64_t lda, double *B, int64_t ldb, int span, hipStream_t s, bool mixed);
 
 namespace {
 
 struct Key {
     int device;
-    int cx, unit, mixed, ib;
+    int cx, unit, mixed, span;
     int64_t m, n, lda, ldb;
     bool operator==(const Key &o) const { return std::memcmp(this, &o, sizeof(Key)) == 0; }
 };
@@ -52,7 +48,6 @@ struct Args {
 
 struct Entry {
     Key key;
-    void *ws = nullptr;
     hipGraphExec_t exec[2] = {nullptr, nullptr};
     Args args[2];
     hipEvent_t done[2] = {nullptr, nullptr};
@@ -78,19 +73,17 @@ void destroy(Entry &e) {
         e.exec[i] = nullptr;
         e.done[i] = nullptr;
     }
-    if (e.ws) (void)hipFree(e.ws);  // hipFree waits for outstanding work on the buffer
-    e.ws = nullptr;
 }
 
 // Record the launch sequence for `a` on the capture stream into a new graph.
-hsma_status record(const Key &k, const Args &a, void *ws, hipStream_t cs, hipGraph_t *out) {
+hsma_status record(const Key &k, const Args &a, hipStream_t cs, hipGraph_t *out) {
     *out = nullptr;
     hipError_t he = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     if (he != hipSuccess) return hip_fail(he);
     g_capturing = true;
     hsma_status st = blocked_trsm(k.cx, k.unit, k.m, k.n, cplx{a.ar, a.ai},
                                   static_cast<const double *>(a.A), k.lda, static_cast<double *>(a.B),
-                                  k.ldb, k.ib, ws, cs, k.mixed);
+                                  k.ldb, k.span, cs, k.mixed);
     g_capturing = false;
     hipGraph_t graph = nullptr;
     he = hipStreamEndCapture(cs, &graph);
@@ -109,7 +102,7 @@ hsma_status prepare(Entry &e, int i, const Args &a, hipStream_t cs) {
     if (e.exec[i] && e.args[i] == a) return HSMA_SUCCESS;
     if (e.launched[i]) HSMA_HIP(hipEventSynchronize(e.done[i]));  // its replay two calls back
     hipGraph_t g = nullptr;
-    HSMA_TRY(record(e.key, a, e.ws, cs, &g));
+    HSMA_TRY(record(e.key, a, cs, &g));
     hsma_status st = HSMA_SUCCESS;
     if (e.exec[i]) {
         hipGraphNode_t bad = nullptr;
@@ -142,7 +135,7 @@ hsma_status prepare(Entry &e, int i, const Args &a, hipStream_t cs) {
 bool graph_capture_active() { return g_capturing; }
 
 hsma_status blocked_trsm_graph(bool cx, bool unit, int64_t m, int64_t n, cplx alpha,
-                               const double *A, int64_t lda, double *B, int64_t ldb, int ib,
+                               const double *A, int64_t lda, double *B, int64_t ldb, int span,
                                bool mixed, hipStream_t s) {
     Key k;
     std::memset(&k, 0, sizeof(k));  // padding bytes take part in the comparison
@@ -151,7 +144,7 @@ hsma_status blocked_trsm_graph(bool cx, bool unit, int64_t m, int64_t n, cplx al
     k.cx = cx;
     k.unit = unit;
     k.mixed = mixed;
-    k.ib = ib;
+    k.span = span;
     k.m = m;
     k.n = n;
     k.lda = lda;
@@ -172,12 +165,7 @@ hsma_status blocked_trsm_graph(bool cx, bool unit, int64_t m, int64_t n, cplx al
     } else {
         Entry e;
         e.key = k;
-        hipError_t he = hipMalloc(&e.ws, blocked_workspace_bytes(cx, m, ib));
-        if (he == hipErrorOutOfMemory) {
-            (void)hipGetLastError();
-            return HSMA_ALLOC_FAILED;
-        }
-        HSMA_HIP(he);
+        hipError_t he = hipSuccess;
         for (int i = 0; i < 2 && he == hipSuccess; ++i) he = hipEventCreateWithFlags(&e.done[i], hipEventDisableTiming);
         if (he != hipSuccess) {
             destroy(e);
@@ -193,7 +181,7 @@ hsma_status blocked_trsm_graph(bool cx, bool unit, int64_t m, int64_t n, cplx al
     const int i = e.turn;
     HSMA_TRY(prepare(e, i, a, cs));
     e.turn ^= 1;
-    // The other graph's last replay uses the same workspace.
+    // Replays of one shape run one after another.
     if (e.launched[i ^ 1]) HSMA_HIP(hipStreamWaitEvent(s, e.done[i ^ 1], 0));
     HSMA_HIP(hipGraphLaunch(e.exec[i], s));
     HSMA_HIP(hipEventRecord(e.done[i], s));

@@ -123,26 +123,24 @@ hsma_status launch_zero(int64_t m, int64_t n, int es, double *B, int64_t ldb, hi
 // C is M x N (ldc), B is K x N (ldb).  Real: A is M x K (lda).  Complex: A is
 // (M/2) x (K/2) complex (lda in complex elements) and is expanded on the fly
 // to its M x K real representation; B and C are complex matrices viewed as
-// real with twice the rows (ldb, ldc in doubles).  Batch b addresses
-// (b / inner) * s_outer + (b % inner) * s_inner (in doubles) for each operand.
+// real with twice the rows (ldb, ldc in doubles).
 // tri_a: A is the m x m diagonal block of a lower-triangular matrix, read only
 // on and below its diagonal (0: plain, 1: lower non-unit, 2: lower unit).
-enum class GemmRole { Update = 0, Leaf = 1, Inverse = 2, Residual = 3, UpdateMixed = 4, Herk = 5 };
+enum class GemmRole { Update, Residual, UpdateMixed, Herk };
 
 // Parameters of one product (also the descriptor of a grouped launch, read
-// by the kernel from device memory).
-struct GemmParams {
+// by the kernel from device memory); T is the data type in memory.
+template <typename T>
+struct GemmParamsT {
     int M, N, K;          // real-view sizes
-    const double *A;
-    int64_t lda;          // real: doubles; complex: complex elements
-    const double *B;
-    int64_t ldb;          // doubles
-    double *C;
-    int64_t ldc;          // doubles
-    double alpha_re, alpha_im, beta_re, beta_im;
+    const T *A;
+    int64_t lda;          // real: components of T; complex: complex elements
+    const T *B;
+    int64_t ldb;          // components of T
+    T *C;
+    int64_t ldc;          // components of T
+    T alpha_re, alpha_im, beta_re, beta_im;
     int tri_a;            // 0 plain, 1 lower non-unit, 2 lower unit (diagonal block of L)
-    int inner;            // batch decomposition
-    int64_t a_outer, a_inner, b_outer, b_inner, c_outer, c_inner;
     int tiles_m, tiles_n;
     int tile0;            // grouped launch: first tile of this product in the grid
     int k_lower;          // 1: A is lower triangular as a whole (with tri_a), so a
@@ -150,63 +148,48 @@ struct GemmParams {
     int c_lower;          // 1: only the lower triangle of C (column <= row, in
                           // elements) is computed and stored
 };
+typedef GemmParamsT<double> GemmParams;
 
-// Tile shape a grouped launch of `role` uses when its largest product has
-// max_m real-view rows and max_n columns (leaves need one tile to span all
-// rows); 0 if unsupported.
-int gemm_grouped_tile(GemmRole role, int max_m, int max_n, int *bm, int *bn);
+// Tile shape a grouped launch of updates uses when its largest product has
+// max_m real-view rows and max_n columns; 0 if unsupported.
+int gemm_grouped_tile(int max_m, int max_n, int *bm, int *bn);
 // Launch over nd descriptors already in device memory (tile0 / tiles_m /
 // tiles_n filled for the shape gemm_grouped_tile returned); total_tiles is
 // the grid size.  flops is for the phase profiler.
-hsma_status launch_gemm_grouped(bool cplx_, GemmRole role, int bm, int bn, const GemmParams *descs,
+hsma_status launch_gemm_grouped(bool cplx_, int bm, int bn, const GemmParams *descs,
                                 int nd, int64_t total_tiles, double flops, hipStream_t s);
 
-// Single-precision product (FP32 data, FP32 accumulation on the FP32 matrix
-// cores): the same roles, sizes and conventions as GemmParams.
-struct Gemm32Params {
-    int M, N, K;
-    const float *A;
-    int64_t lda;
-    const float *B;
-    int64_t ldb;
-    float *C;
-    int64_t ldc;
-    float alpha_re, alpha_im, beta_re, beta_im;
-    int tri_a;
-    int k_lower;
-    int inner;
-    int64_t a_outer, a_inner, b_outer, b_inner, c_outer, c_inner;
-    int tiles_m, tiles_n;
-};
-
-struct GemmBatch {
-    int count = 1, inner = 1;
-    int64_t a_outer = 0, a_inner = 0, b_outer = 0, b_inner = 0, c_outer = 0, c_inner = 0;
-};
 // k_lower = 1: A (with tri_a != 0) is a whole lower-triangular matrix, so
 // each row tile reads only the columns left of its last row.
 // c_lower = 1: only C's lower triangle (element column <= element row) is
 // written; tiles wholly above the diagonal do nothing.
 hsma_status launch_gemm(bool cplx_, GemmRole role, int M, int N, int K,
                         cplx alpha, const double *A, int64_t lda, const double *B,
-                        int64_t ldb, cplx beta, double *C, int64_t ldc, int tri_a,
-                        const GemmBatch &batch, hipStream_t s, int k_lower = 0,
-                        int c_lower = 0);
-// The same product on FP32 data (FP32 matrix cores, FP32 accumulation).
-hsma_status launch_gemm(bool cplx_, GemmRole role, int M, int N, int K, cplx alpha,
-                        const float *A, int64_t lda, const float *B, int64_t ldb, cplx beta,
-                        float *C, int64_t ldc, int tri_a, const GemmBatch &batch, hipStream_t s,
-                        int k_lower = 0);
+                        int64_t ldb, cplx beta, double *C, int64_t ldc, int tri_a, hipStream_t s,
+                        int k_lower = 0, int c_lower = 0);
+// An update on FP32 data (FP32 matrix cores, FP32 accumulation).
+hsma_status launch_gemm(bool cplx_, GemmRole role, int M, int N, int K, cplx alpha, const float *A,
+                        int64_t lda, const float *B, int64_t ldb, cplx beta, float *C, int64_t ldc,
+                        int tri_a, hipStream_t s);
 
-// Inverse of every diagonal sub-block of edge `base` (<= 64) along the
-// diagonal of L (m rows, partitioned into consecutive chunks of `base`, last
-// chunk ragged), written into W: chunk c starting at global row o goes to
-// W + blk * ib*ib + oo + oo*ib (oo = o mod ib, blk = o / ib), in elements.
-// Every element of W's ib x ib blocks not written by this call is zeroed.
-hsma_status launch_diag_inv_base(bool cplx_, bool unit, int m, int base, int ib,
-                                 const double *A, int64_t lda, double *W, hipStream_t s);
-hsma_status launch_diag_inv_base(bool cplx_, bool unit, int m, int base, int ib,
-                                 const float *A, int64_t lda, float *W, hipStream_t s);
+// One panel solve (panel.hip): X = alpha inv(L) B in place for `rows` rows, L
+// at A, unit or not; at most kPanelRows real-view rows.
+constexpr int kPanelRows = 512;
+template <typename T>
+struct PanelParams {
+    const T *A;
+    int64_t lda;         // elements
+    T *B;
+    int64_t ldb, n;      // elements, columns
+    T alpha_re, alpha_im;
+    int rows, unit;
+    int tile0;           // grouped launch: first workgroup of this panel
+};
+template <typename T>
+hsma_status launch_panel(bool cx, const PanelParams<T> &p, hipStream_t s);
+// nd descriptors in device memory, ascending tile0; `tiles` workgroups in all.
+hsma_status launch_panel_grouped(bool cx, const PanelParams<double> *descs, int nd, int max_rows, int64_t tiles,
+                                 double flops, hipStream_t s);
 
 // dst (R x C, ldd) = src^H for src C x R (ldsrc); the transpose for real data.
 // X L^H = B for a lower, non-unit L (m x n X and B, n x n L; FP64 real or

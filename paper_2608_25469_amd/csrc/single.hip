@@ -1,5 +1,4 @@
-// Single-precision small solves (STRSM/CTRSM with m <= 64) and the inversion
-// of diagonal chunks (<= 64 rows) for the FP32 blocked path.
+// Single-precision small solves (STRSM/CTRSM with m <= 64).
 //
 // Paper Sec. 4.2.1 and Alg. 1: the lower triangle of L is staged once in
 // shared memory (LDS here) and each thread owns one column of B, walking the
@@ -9,10 +8,6 @@
 // the same l_ik at once, which LDS serves as a broadcast.  Rows beyond m are
 // zero in LDS and in registers, so the unrolled chain over MAXM (the next of
 // 16, 32, 64 at or above m) needs no per-row guards.
-//
-// The chunk inversion is the same chain against identity right-hand sides
-// (lane j solves for column j of the inverse), the paper's E_j tiles
-// (Sec. 4.3.1), written into the blocked path's workspace W.
 
 #include "internal.h"
 
@@ -117,31 +112,6 @@ __global__ __launch_bounds__(64) void hsma_small32(const float *__restrict__ A, 
         if (i < m) O::st(col, i, x[i]);
 }
 
-// Chunk c: rows [c*base, c*base + sz) of L; lane j < sz solves for column j
-// of the chunk's inverse, written to W (blocks of ib x ib, ld ib).
-template <bool CX, int MAXM, bool UNIT>
-__global__ __launch_bounds__(64) void hsma_inv32(const float *__restrict__ A, int64_t lda, int m,
-                                                 int base, int ib, float *__restrict__ W) {
-    typedef F32<CX> O;
-    typedef typename O::V V;
-    __shared__ V Ls[MAXM * MAXM];
-    const int64_t o = (int64_t)blockIdx.x * base;
-    const int sz = (int)((m - o) < base ? (m - o) : base);
-    const float *Ac = A + (CX ? 2 : 1) * (o + o * lda);
-    stage_lower<CX, MAXM, UNIT>(Ac, lda, sz, Ls);
-    const int j = threadIdx.x;
-    if (j >= sz) return;
-    V x[MAXM];
-#pragma unroll
-    for (int i = 0; i < MAXM; ++i) x[i] = i == j ? O::one() : O::zero();
-    substitute<CX, MAXM, UNIT>(Ls, sz, x);
-    const int64_t blk = o / ib, oo = o % ib;
-    float *Wc = W + (CX ? 2 : 1) * (blk * (int64_t)ib * ib + oo + (oo + j) * ib);
-#pragma unroll
-    for (int i = 0; i < MAXM; ++i)
-        if (i < sz) O::st(Wc, i, x[i]);
-}
-
 // B <- 0 on rows 0..rows-1 (floats) of each column.
 __global__ __launch_bounds__(256) void hsma_zero_fill32(float *__restrict__ B, int64_t rows,
                                                         int64_t n, int64_t ld) {
@@ -167,17 +137,6 @@ hsma_status small32_t(int m, int64_t n, cplx alpha, const float *A, int64_t lda,
     return HSMA_SUCCESS;
 }
 
-template <bool CX, bool UNIT>
-hsma_status inv32_t(int m, int base, int ib, const float *A, int64_t lda, float *W, hipStream_t s) {
-    const int chunks = (m + base - 1) / base;
-    const dim3 g((unsigned)chunks), b(64);
-    if (base <= 16) hipLaunchKernelGGL((hsma_inv32<CX, 16, UNIT>), g, b, 0, s, A, lda, m, base, ib, W);
-    else if (base <= 32) hipLaunchKernelGGL((hsma_inv32<CX, 32, UNIT>), g, b, 0, s, A, lda, m, base, ib, W);
-    else hipLaunchKernelGGL((hsma_inv32<CX, 64, UNIT>), g, b, 0, s, A, lda, m, base, ib, W);
-    HSMA_HIP(hipGetLastError());
-    return HSMA_SUCCESS;
-}
-
 }  // namespace
 
 hsma_status launch_zero32(int64_t m, int64_t n, int es, float *B, int64_t ldb, hipStream_t s) {
@@ -199,21 +158,6 @@ hsma_status launch_small_solve(bool cplx_, bool unit, int m, int64_t n, cplx alp
                            : small32_t<true, false>(m, n, alpha, A, lda, B, ldb, s);
     return unit ? small32_t<false, true>(m, n, alpha, A, lda, B, ldb, s)
                 : small32_t<false, false>(m, n, alpha, A, lda, B, ldb, s);
-}
-
-hsma_status launch_diag_inv_base(bool cplx_, bool unit, int m, int base, int ib, const float *A,
-                                 int64_t lda, float *W, hipStream_t s) {
-    if (base < 8 || base > 64 || (base & 7) || ib % base) return HSMA_INVALID_SIZE;
-    const int nblk = (m + ib - 1) / ib;
-    const int es = cplx_ ? 2 : 1;
-    // zero every block (ib * ib * es floats = half as many doubles; ib is even)
-    HSMA_TRY(launch_zero((int64_t)ib * ib * es / 2, nblk, 1, reinterpret_cast<double *>(W),
-                         (int64_t)ib * ib * es / 2, s));
-    ProfScope prof(HSMA_PHASE_DIAG_INV, 0.0, s);
-    if (cplx_) return unit ? inv32_t<true, true>(m, base, ib, A, lda, W, s)
-                           : inv32_t<true, false>(m, base, ib, A, lda, W, s);
-    return unit ? inv32_t<false, true>(m, base, ib, A, lda, W, s)
-                : inv32_t<false, false>(m, base, ib, A, lda, W, s);
 }
 
 }  // namespace hsma

@@ -1,6 +1,5 @@
-// Dispatch for the small-solve and diagonal-inversion kernels, and the
-// zero fill used for alpha == 0 and for workspace initialisation (a kernel,
-// not a memset, so the blocked schedule stays safe to capture in a graph).
+// Dispatch for the small-solve kernels, and the zero fill used for alpha == 0
+// (a kernel, not a memset, so that it is safe to capture in a graph).
 
 #include "internal.h"
 
@@ -8,9 +7,6 @@ namespace hsma {
 
 hsma_status launch_strip_one(bool cx, bool unit, int m, int64_t n, cplx alpha, const double *A,
                              int64_t lda, double *B, int64_t ldb, hipStream_t s);
-hsma_status launch_inv_base(bool cx, bool unit, int m, int base, int ib, const double *A, int64_t lda,
-                            double *W, hipStream_t s);
-
 
 namespace {
 
@@ -51,16 +47,6 @@ hsma_status launch_zero(int64_t m, int64_t n, int es, double *B, int64_t ldb, hi
     hipLaunchKernelGGL(hsma_zero_fill, dim3((unsigned)blocks), dim3(256), 0, s, B, rows, n, ld);
     HSMA_HIP(hipGetLastError());
     return HSMA_SUCCESS;
-}
-
-hsma_status launch_diag_inv_base(bool cplx_, bool unit, int m, int base, int ib, const double *A,
-                                 int64_t lda, double *W, hipStream_t s) {
-    if (base < 8 || base > 64 || (base & 7) || ib % base) return HSMA_INVALID_SIZE;
-    const int nblk = (m + ib - 1) / ib;
-    const int es = cplx_ ? 2 : 1;
-    HSMA_TRY(launch_zero((int64_t)ib * ib, nblk, es, W, (int64_t)ib * ib, s));
-    ProfScope prof(HSMA_PHASE_DIAG_INV, 0.0, s);
-    return launch_inv_base(cplx_, unit, m, base, ib, A, lda, W, s);
 }
 
 }  // namespace hsma

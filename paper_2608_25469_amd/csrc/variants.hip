@@ -25,8 +25,6 @@
 
 namespace hsma {
 
-int lookup_block_size(bool cx, int64_t m, int64_t n);
-size_t blocked_workspace_bytes(bool cx, int64_t m, int ib);
 hsma_status trsm_impl(hsma_diag diag, int64_t m, int64_t n, const void *alpha, const void *A,
                       int64_t lda, void *B, int64_t ldb, hsma_dtype dtype, int ib_override,
                       int path, hipStream_t s, int *path_used, int *ib_used,

@@ -1,0 +1,91 @@
+"""The blocked path's panels and products at the sizes where they can go
+wrong: panels of one to a few 16-row blocks and ragged last panels, a matrix
+that ends where its allocation ends, and products with every tile shape,
+ragged in rows, columns and depth.
+
+L = [[I, 0], [C, I]] with small integers gives X = B - N B (N the part below
+the diagonal blocks) exactly, in every data type, so those results are compared
+bit for bit with torch's product of the same integers."""
+import numpy as np
+import pytest
+
+import workloads as W
+from parity import assert_parity
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+hs = pytest.importorskip("paper_2608_25469_amd")
+
+DT = {"d": torch.float64, "z": torch.complex128, "s": torch.float32, "c": torch.complex64}
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    hs.lib()
+
+
+@pytest.mark.parametrize("cx", [False, True], ids=["real", "complex"])
+@pytest.mark.parametrize("ib", [16, 32, 256, 0])
+def test_ragged_panels(cx, ib):
+    """Last panels of 1, 2, 7, 8, 9, 15, 16, 17 rows after whole ones, and
+    lone panels around the steps of the kernel's sizes (128, 256, 512 rows);
+    1, 15, 16, 17 and 33 columns."""
+    span = ib or (256 if cx else 512)
+    sizes = [span * k + r for k, r in ((1, 1), (2, 2), (1, 7), (1, 8), (1, 9), (1, 15), (1, 16), (1, 17))]
+    if ib == 0:
+        sizes += [65, 127, 128, 129, 255, 256, 257] + ([] if cx else [511, 512])
+    for j, m in enumerate(s for s in sizes if s > 64 or ib):
+        n = (1, 15, 16, 17, 33)[j % 5]
+        unit = j % 3 == 0
+        L, B = W.problem(900 + j, m, n, cx)
+        alpha = complex(-0.5, 1.0) if cx else -0.75
+        Ld, Bd = hs.to_colmajor(L), hs.to_colmajor(B, ld=m + j % 3)
+        hs.trsm(Ld, Bd, alpha, unit=unit, block_size=ib, path=2)
+        torch.cuda.synchronize()
+        assert_parity(L, B, hs.from_colmajor(Bd), alpha, unit=unit, tag=("panel", m, n, cx, ib))
+
+
+def _ints(shape, dt, lo, hi, g):
+    t = torch.randint(lo, hi + 1, shape, generator=g, device="cuda").to(DT[dt])
+    if dt in "zc":
+        t = torch.complex(t.real, torch.randint(lo, hi + 1, shape, generator=g, device="cuda").to(t.real.dtype))
+    return t
+
+
+@pytest.mark.parametrize("dt", list("dzsc"))
+@pytest.mark.parametrize("m,m1,n", [(577, 512, 30), (1030, 700, 33), (1531, 530, 127), (1100, 1024, 700),
+                                    (2050, 1000, 1025), (3001, 1501, 2333), (4250, 2200, 4099)])
+def test_products_exact(dt, m, m1, n):
+    g = torch.Generator(device="cuda").manual_seed(m + n)
+    Ls = torch.full((m, m), float("nan"), dtype=DT[dt], device="cuda")   # row j: column j of L
+    Ls = torch.triu(torch.zeros_like(Ls)) + torch.tril(Ls, -1)
+    Ls.diagonal().fill_(1)
+    C = _ints((m - m1, m1), dt, -2, 2, g)
+    Ls[:m1, m1:] = C.t()
+    B = hs.colmajor(m, n, DT[dt])
+    B.copy_(_ints((m, n), dt, -3, 3, g))
+    want = B.clone()
+    want[m1:] -= C @ want[:m1].contiguous()
+    hs.trsm(Ls.t(), B, 1.0)
+    torch.cuda.synchronize()
+    assert torch.equal(B, want), (dt, m, m1, n)
+
+
+def test_mixed_products_exact():
+    """The same through the mixed mode, whose products round their operands
+    to FP32 (small integers are exact)."""
+    for m, m1, n in ((1100, 700, 37), (2300, 1100, 1300), (4200, 2100, 4097)):
+        g = torch.Generator(device="cuda").manual_seed(m)
+        Ls = torch.eye(m, dtype=torch.float64, device="cuda")
+        C = _ints((m - m1, m1), "d", -2, 2, g)
+        Ls[:m1, m1:] = C.t()
+        B = hs.colmajor(m, n, torch.float64)
+        B.copy_(_ints((m, n), "d", -3, 3, g))
+        want = B.clone()
+        want[m1:] -= C @ want[:m1].contiguous()
+        hs.trsm(Ls.t(), B, 1.0, mixed=True)
+        torch.cuda.synchronize()
+        assert torch.equal(B, want), (m, m1, n)
