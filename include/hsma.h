@@ -103,9 +103,9 @@ const char *hsma_version(void);
  *
  * Path: m <= 64 uses the register-resident small-solve kernel, one wavefront
  * per 64-column panel of B (Sec. 4.2); m > 64 uses the blocked path (Sec. 4.3):
- * the rows are solved in panels, one launch each (16 x 16 diagonal blocks
- * inverted in registers, the rest products), with recursive matrix-core
- * updates between the panels.
+ * the rows are solved in panels (16 x 16 diagonal blocks inverted in registers,
+ * the rest products), with recursive matrix-core updates between them or, for
+ * up to a few hundred columns, all in one launch whose workgroups hand X on.
  */
 hsma_status hsma_trsm(hsma_diag diag, int64_t m, int64_t n, const void *alpha,
                       const void *A, int64_t lda, void *B, int64_t ldb,
@@ -117,18 +117,22 @@ hsma_status hsma_trsm(hsma_diag diag, int64_t m, int64_t n, const void *alpha,
  * memory: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc.  Same operation, arguments, path choice and kernels as
  * hsma_trsm, so the result is bit-for-bit the same; it calls no hipMalloc,
- * hipFree or other allocating routine, and needs no device memory beyond its
- * arguments.  The sizes it takes are bounded all the same: with I_B the tuning
+ * hipFree or other allocating routine.  The workspace of solves that run as one
+ * chained launch comes from a fixed per-device scratch array of
+ * hsma_noalloc_scratch_bytes() bytes (64 MiB) inside the library, which each
+ * GPU the library runs on holds until the process ends.  With I_B the tuning
  * table's entry, ceil(m/I_B) I_B^2 + (ceil(m/2) + I_B) I_B elements have to
- * fit hsma_noalloc_scratch_bytes() bytes (64 MiB; DTRSM up to m of about
- * 16384), or it returns HSMA_WORKSPACE_TOO_SMALL before anything is enqueued.
- * Asynchronous on `stream`.
+ * fit those bytes (DTRSM up to m of about 16384), or it returns
+ * HSMA_WORKSPACE_TOO_SMALL before anything is enqueued.  Every call on one GPU
+ * uses the same array: calls that overlap in time on one GPU (two streams, two
+ * threads) race and give wrong results; serialise them.  Asynchronous on
+ * `stream`.
  */
 hsma_status hsma_trsm_noalloc(hsma_diag diag, int64_t m, int64_t n, const void *alpha,
                               const void *A, int64_t lda, void *B, int64_t ldb,
                               hsma_dtype dtype, hsma_stream_t stream);
 
-/* The size bound of hsma_trsm_noalloc in bytes. */
+/* Bytes of the per-device scratch array of hsma_trsm_noalloc. */
 uint64_t hsma_noalloc_scratch_bytes(void);
 
 /* ------------------------------------------------------------------------ */

@@ -12,11 +12,11 @@
 
 namespace hsma {
 
-int panel_span(bool cx, int block_size);
 hsma_status blocked_trsm32(bool cx, bool unit, int64_t m, int64_t n, cplx alpha, const float *A,
-                           int64_t lda, float *B, int64_t ldb, int span, hipStream_t s);
+                           int64_t lda, float *B, int64_t ldb, int span, void *ws, hipStream_t s);
 hsma_status blocked_trsm(bool cx, bool unit, int64_t m, int64_t n, cplx alpha, const double *A,
-                         int64_t lda, double *B, int64_t ldb, int span, hipStream_t s, bool mixed);
+                         int64_t lda, double *B, int64_t ldb, int span, void *ws, hipStream_t s,
+                         bool mixed);
 hsma_status blocked_trsm_graph(bool cx, bool unit, int64_t m, int64_t n, cplx alpha,
                                const double *A, int64_t lda, double *B, int64_t ldb, int span,
                                bool mixed, hipStream_t s);
@@ -167,9 +167,13 @@ static hsma_status solve_once(bool cx, bool unit, int64_t m, int64_t n, cplx al,
     if (!valid_block_size(cx, ib)) return HSMA_INVALID_VALUE;
     if (path_used) *path_used = 2;
     if (ib_used) *ib_used = ib;
-    const int span = panel_span(cx, ib_override);
-    if (use_graph) return blocked_trsm_graph(cx, unit, m, n, al, Ad, lda, Bd, ldb, span, mixed, s);
-    return blocked_trsm(cx, unit, m, n, al, Ad, lda, Bd, ldb, span, s, mixed);
+    if (use_graph) return blocked_trsm_graph(cx, unit, m, n, al, Ad, lda, Bd, ldb, ib_override, mixed, s);
+    void *ws = nullptr;
+    const size_t bytes = blocked_bytes<double>(cx, m, n, ib_override, mixed);
+    if (bytes) HSMA_TRY(ws_alloc(&ws, bytes, s));
+    hsma_status st = blocked_trsm(cx, unit, m, n, al, Ad, lda, Bd, ldb, ib_override, ws, s, mixed);
+    hsma_status st2 = ws ? ws_free(ws, s) : HSMA_SUCCESS;
+    return st != HSMA_SUCCESS ? st : st2;
 }
 
 // One FP32 solve in place (STRSM, CTRSM): small kernel or blocked path.
@@ -189,7 +193,12 @@ static hsma_status solve_once32(bool cx, bool unit, int64_t m, int64_t n, cplx a
     if (!valid_block_size(cx, ib)) return HSMA_INVALID_VALUE;
     if (path_used) *path_used = 2;
     if (ib_used) *ib_used = ib;
-    return blocked_trsm32(cx, unit, m, n, al, Ad, lda, Bd, ldb, panel_span(cx, ib_override), s);
+    void *ws = nullptr;
+    const size_t bytes = blocked_bytes<float>(cx, m, n, ib_override, false);
+    if (bytes) HSMA_TRY(ws_alloc(&ws, bytes, s));
+    hsma_status st = blocked_trsm32(cx, unit, m, n, al, Ad, lda, Bd, ldb, ib_override, ws, s);
+    hsma_status st2 = ws ? ws_free(ws, s) : HSMA_SUCCESS;
+    return st != HSMA_SUCCESS ? st : st2;
 }
 
 // Normwise backward error from the residual R (on the device): max row sums

@@ -26,6 +26,20 @@
 
 namespace hsma {
 
+// Whether a solve runs as one chain launch (panel.hip) instead of the recursion:
+// where few columns leave the recursion's launches mostly empty.  Measured, us,
+// chain / recursion in panels of 256 rows: DTRSM 1024 x 256 74 / 91, 1024 x
+// 1024 81 / 101, 1024 x 4096 180 / 159, 4096 x 256 283 / 452, 4096 x 1024 629 /
+// 648, 8192 x 256 844 / 1141, 8192 x 1024 1992 / 1967; ZTRSM 1024 x 256 124 /
+// 195, 2048 x 1024 516 / 611, 4096 x 1024 1800 / 1778, 8192 x 256 2146 / 2870;
+// STRSM 4096 x 256 175 / 392, 2048 x 4096 376 / 287.  Up to 512 real-view rows
+// one panel is as fast (38 us against 41) and needs no mail.
+bool chain_rule(bool cx, int elem, int64_t m, int64_t n) {
+    const int64_t mr = m * (cx ? 2 : 1), mail = mr * ((n + 15) / 16 * 16) * elem;
+    if (mr <= kPanelRows || n > 1024 || mail > (int64_t)HSMA_NOALLOC_SCRATCH_BYTES / 2) return false;
+    return n <= 256 || (double)mr * (double)mr * (double)n <= (double)((int64_t)1 << 35);
+}
+
 namespace {
 
 // T is double (DTRSM, ZTRSM) or float (STRSM, CTRSM); complex data is
@@ -85,9 +99,27 @@ hsma_status recurse(const Ctx<T> &c, int64_t b0, int64_t nb, bool touched) {
     return recurse(c, b0 + h, nb - h, true);
 }
 
+// One chain launch, or recursion (span 0 stands for both: the rule decides).
+template <typename T>
+bool use_chain(bool cx, int64_t m, int64_t n, int span, bool mixed) {
+    return span == 0 && !mixed && chain_rule(cx, sizeof(T), m, n);
+}
+
 template <typename T>
 hsma_status blocked_t(bool cx, bool unit, int64_t m, int64_t n, cplx alpha, const T *A,
-                      int64_t lda, T *B, int64_t ldb, int span, hipStream_t s, bool mixed) {
+                      int64_t lda, T *B, int64_t ldb, int span, void *ws, hipStream_t s, bool mixed) {
+    if (use_chain<T>(cx, m, n, span, mixed)) {
+        PanelParams<T> p{};
+        p.A = A;
+        p.lda = lda;
+        p.B = B;
+        p.ldb = ldb;
+        p.n = n;
+        p.alpha_re = (T)alpha.re;
+        p.alpha_im = (T)alpha.im;
+        p.unit = unit;
+        return launch_chain<T>(cx, p, m, ws, s);
+    }
     Ctx<T> c;
     c.mixed = mixed;
     c.cx = cx;
@@ -99,25 +131,32 @@ hsma_status blocked_t(bool cx, bool unit, int64_t m, int64_t n, cplx alpha, cons
     c.lda = lda;
     c.B = B;
     c.ldb = ldb;
-    c.span = span;
+    c.span = span > 0 ? span : kPanelRows / (cx ? 2 : 1);
     c.s = s;
-    return recurse(c, 0, (m + span - 1) / span, false);
+    return recurse(c, 0, (m + c.span - 1) / c.span, false);
 }
 
 }  // namespace
 
-int panel_span(bool cx, int block_size) { return block_size > 0 ? block_size : kPanelRows / (cx ? 2 : 1); }
+template <typename T>
+size_t blocked_bytes(bool cx, int64_t m, int64_t n, int span, bool mixed) {
+    return use_chain<T>(cx, m, n, span, mixed) ? chain_bytes<T>(cx, m, n) : 0;
+}
+template size_t blocked_bytes<double>(bool, int64_t, int64_t, int, bool);
+template size_t blocked_bytes<float>(bool, int64_t, int64_t, int, bool);
 
-// Enqueue the blocked solve in panels of `span` rows.
+// Enqueue the blocked solve: in panels of `span` rows, or as the rules say (0).
+// `ws` holds blocked_bytes.
 hsma_status blocked_trsm(bool cx, bool unit, int64_t m, int64_t n, cplx alpha, const double *A,
-                         int64_t lda, double *B, int64_t ldb, int span, hipStream_t s, bool mixed) {
-    return blocked_t<double>(cx, unit, m, n, alpha, A, lda, B, ldb, span, s, mixed);
+                         int64_t lda, double *B, int64_t ldb, int span, void *ws, hipStream_t s,
+                         bool mixed) {
+    return blocked_t<double>(cx, unit, m, n, alpha, A, lda, B, ldb, span, ws, s, mixed);
 }
 
 // The FP32 solve (STRSM, CTRSM).
 hsma_status blocked_trsm32(bool cx, bool unit, int64_t m, int64_t n, cplx alpha, const float *A,
-                           int64_t lda, float *B, int64_t ldb, int span, hipStream_t s) {
-    return blocked_t<float>(cx, unit, m, n, alpha, A, lda, B, ldb, span, s, false);
+                           int64_t lda, float *B, int64_t ldb, int span, void *ws, hipStream_t s) {
+    return blocked_t<float>(cx, unit, m, n, alpha, A, lda, B, ldb, span, ws, s, false);
 }
 
 // R <- R - tril(L) X, the residual of refinement and of the backward-error

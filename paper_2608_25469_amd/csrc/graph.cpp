@@ -4,8 +4,8 @@
 // -- the kernels, grids and dependencies -- depends only on (dtype, diag, m,
 // n, lda, ldb, panel height, precision); the matrices and alpha only change
 // kernel arguments.  So a graph is captured once per shape (on a library
-// stream; the schedule allocates nothing and records no memset node) and
-// instantiated once.  A later call with other pointers or another alpha
+// stream, with its own workspace, so nothing is allocated inside the capture
+// and no memset node is recorded) and instantiated once.  A later call with other pointers or another alpha
 // records the same launch sequence again (recording only, no device
 // submission) and moves the new arguments into the instantiated graph with
 // hipGraphExecUpdate, then replays it with one hipGraphLaunch.
@@ -25,7 +25,8 @@
 namespace hsma {
 
 hsma_status blocked_trsm(bool cx, bool unit, int64_t m, int64_t n, cplx alpha, const double *A,
-                         int64_t lda, double *B, int64_t ldb, int span, hipStream_t s, bool mixed);
+                         int64_t lda, double *B, int64_t ldb, int span, void *ws, hipStream_t s,
+                         bool mixed);
 
 namespace {
 
@@ -48,6 +49,7 @@ struct Args {
 
 struct Entry {
     Key key;
+    void *ws = nullptr;
     hipGraphExec_t exec[2] = {nullptr, nullptr};
     Args args[2];
     hipEvent_t done[2] = {nullptr, nullptr};
@@ -73,17 +75,19 @@ void destroy(Entry &e) {
         e.exec[i] = nullptr;
         e.done[i] = nullptr;
     }
+    if (e.ws) (void)hipFree(e.ws);  // hipFree waits for outstanding work on the buffer
+    e.ws = nullptr;
 }
 
 // Record the launch sequence for `a` on the capture stream into a new graph.
-hsma_status record(const Key &k, const Args &a, hipStream_t cs, hipGraph_t *out) {
+hsma_status record(const Key &k, const Args &a, void *ws, hipStream_t cs, hipGraph_t *out) {
     *out = nullptr;
     hipError_t he = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
     if (he != hipSuccess) return hip_fail(he);
     g_capturing = true;
     hsma_status st = blocked_trsm(k.cx, k.unit, k.m, k.n, cplx{a.ar, a.ai},
                                   static_cast<const double *>(a.A), k.lda, static_cast<double *>(a.B),
-                                  k.ldb, k.span, cs, k.mixed);
+                                  k.ldb, k.span, ws, cs, k.mixed);
     g_capturing = false;
     hipGraph_t graph = nullptr;
     he = hipStreamEndCapture(cs, &graph);
@@ -102,7 +106,7 @@ hsma_status prepare(Entry &e, int i, const Args &a, hipStream_t cs) {
     if (e.exec[i] && e.args[i] == a) return HSMA_SUCCESS;
     if (e.launched[i]) HSMA_HIP(hipEventSynchronize(e.done[i]));  // its replay two calls back
     hipGraph_t g = nullptr;
-    HSMA_TRY(record(e.key, a, cs, &g));
+    HSMA_TRY(record(e.key, a, e.ws, cs, &g));
     hsma_status st = HSMA_SUCCESS;
     if (e.exec[i]) {
         hipGraphNode_t bad = nullptr;
@@ -166,6 +170,13 @@ hsma_status blocked_trsm_graph(bool cx, bool unit, int64_t m, int64_t n, cplx al
         Entry e;
         e.key = k;
         hipError_t he = hipSuccess;
+        const size_t bytes = blocked_bytes<double>(cx, m, n, span, mixed);
+        if (bytes) he = hipMalloc(&e.ws, bytes);
+        if (he == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
+            return HSMA_ALLOC_FAILED;
+        }
+        HSMA_HIP(he);
         for (int i = 0; i < 2 && he == hipSuccess; ++i) he = hipEventCreateWithFlags(&e.done[i], hipEventDisableTiming);
         if (he != hipSuccess) {
             destroy(e);
@@ -181,7 +192,7 @@ hsma_status blocked_trsm_graph(bool cx, bool unit, int64_t m, int64_t n, cplx al
     const int i = e.turn;
     HSMA_TRY(prepare(e, i, a, cs));
     e.turn ^= 1;
-    // Replays of one shape run one after another.
+    // The other graph's last replay uses the same workspace.
     if (e.launched[i ^ 1]) HSMA_HIP(hipStreamWaitEvent(s, e.done[i ^ 1], 0));
     HSMA_HIP(hipGraphLaunch(e.exec[i], s));
     HSMA_HIP(hipEventRecord(e.done[i], s));

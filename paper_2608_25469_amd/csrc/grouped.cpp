@@ -1,9 +1,10 @@
 // Grouped blocked path: many problems with m > 64 advanced together.
 //
 // Each problem follows exactly the schedule the single-problem blocked path
-// gives it (the same panels, the same recursive sequence of panel solves and
-// trailing updates), so every result is bit-for-bit the one the problem gets
-// alone.  What changes is how the work is launched: the k-th operation of
+// gives it (a chain, or the same panels and the same recursive sequence of
+// panel solves and trailing updates), so every result is bit-for-bit the one
+// the problem gets alone.  What changes is how the work is launched: all chains
+// of a data type are one launch, and of the recursions the k-th operation of
 // every problem goes into one grouped launch, so a batch of hundreds of
 // mid-sized solves costs a few launches instead of a few per problem.  The
 // in-order walk of the recursion alternates panel, update, panel, ..., so step
@@ -19,7 +20,6 @@
 
 namespace hsma {
 
-int panel_span(bool cx, int block_size);
 hsma_status upload_async(const void *host, size_t bytes, void *dev, hipStream_t s);
 
 namespace {
@@ -76,7 +76,7 @@ GemmParams make(int M, int N, int K, cplx alpha, const double *A, int64_t lda, c
 }
 
 struct Launch {
-    bool panel = false;
+    bool panel = false, chain = false;
     bool cx = false;
     size_t img_off = 0;
     int64_t tiles = 0;
@@ -103,6 +103,50 @@ PanelParams<double> op_panel(const Prob &p, const Op &o) {
     return q;
 }
 
+// Every panel of every chain, as one launch.  Panels are listed by their place
+// in their chain (all first panels, all second ones, ...), the longest chains
+// first: a panel waits only for the one before it, so each round of the list
+// is work that can start once the round before it is under way, and no solve
+// holds the chip with panels that wait while another has not begun.  A
+// descriptor's mail is an offset until the mail has a place.
+void chain_launch(std::vector<Prob> &ps, Launch *l, size_t *words) {
+    std::stable_sort(ps.begin(), ps.end(), [](const Prob &a, const Prob &b) { return a.m > b.m; });
+    l->chain = l->panel = true;
+    std::vector<size_t> mail;
+    size_t at = 0;
+    for (const Prob &p : ps) {
+        mail.push_back(at);
+        at += chain_bytes<double>(p.cx, p.m, p.n) / sizeof(double);
+        l->flops += (p.cx ? 4.0 : 1.0) * p.m * (double)p.m * (double)p.n;
+    }
+    *words = at;
+    for (int64_t r = 0, more = 1; more; ++r) {
+        more = 0;
+        for (size_t i = 0; i < ps.size(); ++i) {
+            const Prob &p = ps[i];
+            const int64_t h = kChainRows / p.es(), r0 = r * h;
+            if (r0 >= p.m) continue;
+            more = 1;
+            PanelParams<double> q{};
+            q.A = p.A + p.es() * (r0 + r0 * p.lda);
+            q.lda = p.lda;
+            q.B = p.B + p.es() * r0;
+            q.ldb = p.ldb;
+            q.n = p.n;
+            q.alpha_re = p.alpha.re;
+            q.alpha_im = p.alpha.im;
+            q.rows = (int)std::min(h, p.m - r0);
+            q.unit = p.unit;
+            q.left = (int)(r * (kChainRows / 16));
+            q.nblk = (int)((p.m * p.es() + 15) / 16);
+            q.mail = reinterpret_cast<double *>(mail[i] * sizeof(double));
+            q.tile0 = (int)std::min<int64_t>(l->tiles, 0x7fffffff);
+            l->tiles += (p.n + 15) / 16;
+            l->panels.push_back(q);
+        }
+    }
+}
+
 GemmParams op_update(const Prob &p, const Op &o) {
     const int es = p.es();
     return make((int)(es * (o.r2 - o.r1)), (int)p.n, (int)(es * (o.r1 - o.k0)), cplx{-1.0, 0.0},
@@ -115,9 +159,9 @@ GemmParams op_update(const Prob &p, const Op &o) {
 // Enqueue every problem (validated; m > 64; alpha != 0) on stream s.
 hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_t s) {
     if (count <= 0) return HSMA_SUCCESS;
-    std::vector<Prob> ps;
+    std::vector<Prob> ps, chains[2];
     ps.reserve(count);
-    std::vector<std::vector<Op>> ops(count);
+    std::vector<std::vector<Op>> ops;
     size_t steps = 0;
     for (int64_t i = 0; i < count; ++i) {
         const hsma_problem &q = probs[i];
@@ -131,10 +175,15 @@ hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_
         p.lda = q.lda;
         p.B = static_cast<double *>(q.B);
         p.ldb = q.ldb;
-        p.span = panel_span(p.cx, 0);
+        p.span = kPanelRows / (p.cx ? 2 : 1);
         p.nb = (p.m + p.span - 1) / p.span;
-        walk(p, 0, p.nb, false, ops[i]);
-        steps = std::max(steps, ops[i].size());
+        if (chain_rule(p.cx, sizeof(double), p.m, p.n)) {
+            chains[p.cx].push_back(p);
+            continue;
+        }
+        ops.emplace_back();
+        walk(p, 0, p.nb, false, ops.back());
+        steps = std::max(steps, ops.back().size());
         ps.push_back(p);
     }
 
@@ -144,7 +193,17 @@ hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_
     // served mix (n log-uniform in [1, 512]) cost more than the columns the
     // wide tiles leave idle.
     std::vector<Launch> launches;
-    size_t img_bytes = 0;
+    size_t img_bytes = 0, mail_words[2] = {0, 0};
+    for (int cxi = 0; cxi < 2; ++cxi) {
+        Launch l;
+        chain_launch(chains[cxi], &l, &mail_words[cxi]);
+        if (l.panels.empty()) continue;
+        if (l.tiles > 0x7fffffff) return HSMA_INVALID_SIZE;
+        l.cx = cxi;
+        l.img_off = img_bytes;
+        img_bytes += (l.panels.size() * sizeof(PanelParams<double>) + 255) / 256 * 256;
+        launches.push_back(std::move(l));
+    }
     for (size_t k = 0; k < steps; ++k) {
         for (int cxi = 0; cxi < 2; ++cxi) {
             Launch l;
@@ -194,13 +253,30 @@ hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_
         else std::memcpy(img.data() + l.img_off, l.gemms.data(), l.gemms.size() * sizeof(GemmParams));
     }
     void *dev = nullptr;
-    HSMA_TRY(ws_alloc(&dev, img_bytes, s));
-    const unsigned char *base = static_cast<const unsigned char *>(dev);
+    img_bytes = (img_bytes + 255) / 256 * 256;
+    HSMA_TRY(ws_alloc(&dev, img_bytes + (mail_words[0] + mail_words[1]) * sizeof(double) + 512, s));
+    unsigned char *base = static_cast<unsigned char *>(dev);
+    // Mail of the real chains, then of the complex ones, 256 bytes after each.
+    double *mail[2];
+    mail[0] = reinterpret_cast<double *>(base + img_bytes);
+    mail[1] = mail[0] + mail_words[0] + 32;
+    for (const Launch &l : launches) {
+        if (!l.chain) continue;
+        unsigned char *img_l = img.data() + l.img_off;
+        for (size_t i = 0; i < l.panels.size(); ++i) {
+            PanelParams<double> q = l.panels[i];
+            q.mail = mail[l.cx] + reinterpret_cast<uintptr_t>(q.mail) / sizeof(double);
+            std::memcpy(img_l + i * sizeof(q), &q, sizeof(q));
+        }
+    }
     hsma_status st = upload_async(img.data(), img.size(), dev, s);
     for (const Launch &l : launches) {
         if (st != HSMA_SUCCESS) break;
         const void *d = base + l.img_off;
-        if (l.panel)
+        if (l.chain)
+            st = launch_chain_grouped(l.cx, static_cast<const PanelParams<double> *>(d), (int)l.panels.size(), l.tiles,
+                                      mail[l.cx], (int64_t)mail_words[l.cx], l.flops, s);
+        else if (l.panel)
             st = launch_panel_grouped(l.cx, static_cast<const PanelParams<double> *>(d), (int)l.panels.size(),
                                       l.max_rows, l.tiles, l.flops, s);
         else

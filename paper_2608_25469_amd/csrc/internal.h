@@ -184,10 +184,32 @@ struct PanelParams {
     T alpha_re, alpha_im;
     int rows, unit;
     int tile0;           // grouped launch: first workgroup of this panel
+    // A panel of a chain (launch_chain): `left` 16-row blocks lie before it, and
+    // X moves through `mail`, 256 values per block, `nblk` blocks per strip of 16
+    // columns.
+    int left, nblk;
+    T *mail;
 };
 template <typename T>
 hsma_status launch_panel(bool cx, const PanelParams<T> &p, hipStream_t s);
+// A whole solve as one launch: panels of kChainRows real-view rows in order, a
+// workgroup per panel and strip of 16 columns, X handed on through `ws`
+// (chain_bytes).  Rows any number.
+constexpr int kChainRows = 256;
+template <typename T>
+size_t chain_bytes(bool cx, int64_t m, int64_t n);
+// Device memory a blocked solve in panels of `span` rows needs (0: none).
+template <typename T>
+size_t blocked_bytes(bool cx, int64_t m, int64_t n, int span, bool mixed);
+// Whether such a solve runs as a chain (blocked.cpp); elem: bytes of a component.
+bool chain_rule(bool cx, int elem, int64_t m, int64_t n);
+template <typename T>
+hsma_status launch_chain(bool cx, const PanelParams<T> &p, int64_t m, void *ws, hipStream_t s);
 // nd descriptors in device memory, ascending tile0; `tiles` workgroups in all.
+// Chains: every descriptor one panel of a solve, a solve's panels in order; the
+// mail they point into is `words` values at `mail`, with 256 bytes more.
+hsma_status launch_chain_grouped(bool cx, const PanelParams<double> *descs, int nd, int64_t tiles, double *mail,
+                                 int64_t words, double flops, hipStream_t s);
 hsma_status launch_panel_grouped(bool cx, const PanelParams<double> *descs, int nd, int max_rows, int64_t tiles,
                                  double flops, hipStream_t s);
 

@@ -11,11 +11,13 @@
 // One workgroup of eight wavefronts solves 16 columns.  The rows are cut into
 // 16-row blocks, dealt to the wavefronts in turn (wavefront w holds blocks w,
 // w + 8, ...), each block of the right-hand side one 16 x 16 accumulator.
-// Step i: the owner of block i multiplies it by the block's inverse (X_i),
-// publishes -X_i in LDS and stores X_i; after one barrier every wavefront
-// adds L_ji (-X_i) to its blocks j > i, the owner of block i + 1 to that block
-// first, so that X_{i+1} is under way while the others still update (the
-// barrier of step i + 1 then finds it done).
+// Step i: X_i is in LDS; every wavefront adds L_ji (-X_i) to its blocks j > i +
+// 1 (the owner of block i + 2 then multiplies that block by its inverse: y),
+// while the owner of block i + 1 forms X_{i+1} = y - P X_i with P =
+// inv(L_{i+1,i+1}) L_{i+1,i}, prepared at the start, and publishes it in LDS.
+// There is no barrier: X_i has a place of its own, a count in LDS says how many
+// are there, and a wavefront waits for nothing but the X it needs, so only four
+// products lie on the chain from one X to the next.
 //
 // No operand changes layout.  With the rows of an A fragment in the order that
 // makes a lane's results four consecutive rows 4g + v of column l%16 (g =
@@ -28,6 +30,7 @@
 // block, four for its update, LDS and the barrier: about 700 cycles per 16
 // rows), otherwise the matrix cores.
 
+#include <algorithm>
 #include <type_traits>
 
 #include "dpp_fma.h"
@@ -60,14 +63,66 @@ __device__ __forceinline__ float bcast(float v) {
     return __uint_as_float((unsigned)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), 0x150 + N, 0xf, 0xf, false));
 }
 
+// A value that is the same in every lane, as a scalar.
+__device__ __forceinline__ const void *uniform(const void *p) {
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return (const void *)(((uint64_t)hi << 32) | lo);
+}
+
 template <typename T>
 __device__ __forceinline__ T div_rn(T a, T b) {
     if constexpr (sizeof(T) == 8) return __ddiv_rn(a, b);
     else return __fdiv_rn(a, b);
 }
 
-// NQ: blocks per wavefront (rows <= 128 NQ in the real view).
-template <typename T, bool CX, int NQ>
+// The words that carry X between workgroups: written and read past the caches
+// of an XCD (relaxed atomics at agent scope), each its own message.  An empty
+// place holds a signalling NaN, which no arithmetic returns, so a word that is
+// anything else has arrived and no flag or order between words is needed.
+template <typename T>
+struct Word;
+template <>
+struct Word<double> {
+    typedef unsigned long long U;
+    static constexpr U kEmpty = 0x7ff05a5a5a5a5a5aull;
+};
+template <>
+struct Word<float> {
+    typedef unsigned U;
+    static constexpr U kEmpty = 0x7f805a5au;
+};
+template <typename T>
+__device__ __forceinline__ void mail_store(T *p, T v) {
+    typedef typename Word<T>::U U;
+    __hip_atomic_store(reinterpret_cast<U *>(p), __builtin_bit_cast(U, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T mail_load(const T *p) {
+    typedef typename Word<T>::U U;
+    return __builtin_bit_cast(T, __hip_atomic_load(reinterpret_cast<const U *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+template <typename T>
+__device__ __forceinline__ bool is_empty(T v) {
+    return __builtin_bit_cast(typename Word<T>::U, v) == Word<T>::kEmpty;
+}
+
+// Empties the mail (n words) and clears the ticket counter.
+template <typename T>
+__global__ __launch_bounds__(256) void hsma_mail_empty(T *mail, int64_t n, unsigned *tickets) {
+    typedef typename Word<T>::U U;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+        reinterpret_cast<U *>(mail)[i] = Word<T>::kEmpty;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *tickets = 0;
+}
+
+// Looks at a place before a wavefront goes on without it (about a second): every
+// wait ends, whatever went wrong elsewhere.
+constexpr int kMaxPolls = 1 << 20;
+
+// NQ: blocks per wavefront (rows <= 128 NQ in the real view).  CHAIN: the panel
+// is one of a chain.
+template <typename T, bool CX, int NQ, bool CHAIN>
 struct Solve {
     static constexpr int ES = CX ? 2 : 1;
     static constexpr int NB = kWaves * NQ;          // blocks
@@ -79,12 +134,18 @@ struct Solve {
     typedef T V2 __attribute__((ext_vector_type(2), aligned(sizeof(T))));
 
     struct Shared {
-        T inv[NB][256];    // inverse of block j: element (r, k) at 16 k + (r ^ k)
-        T x[2][4 * 64];    // -X_i: element v of lane l at 64 v + l
+        // Block j: first its inverse (element (r, k) at 16 k + (r ^ k)), then
+        // P_j in the same order, both read by the owner of block j alone, then
+        // -X_j (element v of lane l at 64 v + l).
+        T blk[NB][256];
+        T left[CHAIN ? 2 : 1][CHAIN ? 2 * 256 : 1];  // two blocks of -X from before the panel
+        int ticket;
+        int done;          // blocks of X in blk
     };
 
     const GT *A;       // the panel's diagonal block of L
     int64_t lda;
+    const HSMA_GLOBAL char *at[NQ];  // this lane's row of block w + 8 q, column 4 g of the panel
     int mr, nb;        // real-view rows, blocks
     int w, lane, g, lr, arow;
     GT *col;           // this lane's column of B
@@ -92,6 +153,11 @@ struct Solve {
     Shared &sh;
     Acc acc[NQ];
     T a[D][NQ][4];     // L_ji of steps i, i + 1, ..: slot i % D
+    T *mail;           // CHAIN: this strip's blocks of -X, from block 0 of the solve
+    int left;          // blocks before the panel
+    T fi[NQ][4];       // inv(L_jj), as A fragments
+    T fp[NQ][4];       // P_j = inv(L_jj) L_{j,j-1}, as A fragments
+    Acc y;             // inv(L_jj) times the block, then X_j
 
     __device__ __forceinline__ explicit Solve(Shared &s) : sh(s) {}
 
@@ -129,39 +195,75 @@ struct Solve {
         }
     }
 
+    // This lane's part of L for block row w + 8 q and columns 16 i + 4 g .. + 3
+    // (i counts from the panel's first column, negative before it): a scalar
+    // number of bytes from the lane's place.
+    __device__ __forceinline__ void load_a(int q, int i, T (&f)[4]) const {
+        const HSMA_GLOBAL char *p = at[q] + (int64_t)i * (16 * lda * (int64_t)sizeof(T));
+        if constexpr (CX) {
+            const V2 e0 = *reinterpret_cast<const HSMA_GLOBAL V2 *>(p);
+            const V2 e1 = *reinterpret_cast<const HSMA_GLOBAL V2 *>(p + 2 * lda * (int64_t)sizeof(T));
+            f[0] = e0.x;
+            f[1] = e0.y;
+            f[2] = e1.x;
+            f[3] = e1.y;
+        } else {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) f[s] = *reinterpret_cast<const GT *>(p + s * lda * (int64_t)sizeof(T));
+        }
+    }
+
     // This lane's part of L_ji for step I and its blocks w + 8 q, q >= Q0:
     // row 16 j + arow (kept below mr), columns 16 I + 4 g .. + 3.  Complex:
     // the two complex elements that hold them, expanded at use.
     template <int I>
     __device__ __forceinline__ void load_l() {
-        constexpr int Q0 = (I + 1) / kWaves;
+        constexpr int Q0 = (I + 2) / kWaves;
         // (Past the last step: columns 0..15, which a panel of two blocks has.)
         const int i = I < nb - 1 ? I : 0;
         static_for<Q0, NQ>([&](auto Q) {
             constexpr int q = decltype(Q)::value;
-            const int r = 16 * (w + kWaves * q) + arow;
-            if constexpr (CX) {
-                const int cr = r / 2 < mr / 2 ? r / 2 : mr / 2 - 1;
-                const GT *p = A + 2 * (cr + (int64_t)(8 * i + 2 * g) * lda);
-                const V2 e0 = *reinterpret_cast<const HSMA_GLOBAL V2 *>(p);
-                const V2 e1 = *reinterpret_cast<const HSMA_GLOBAL V2 *>(p + 2 * lda);
-                a[I % D][q][0] = e0.x;
-                a[I % D][q][1] = e0.y;
-                a[I % D][q][2] = e1.x;
-                a[I % D][q][3] = e1.y;
-            } else {
-                const GT *p = A + (r < mr ? r : mr - 1) + (int64_t)(16 * i + 4 * g) * lda;
-#pragma unroll
-                for (int s = 0; s < 4; ++s) a[I % D][q][s] = p[s * lda];
-            }
+            load_a(q, i, a[I % D][q]);
         });
+    }
+
+    // This lane's part of L_{j,j-1} as a B fragment: rows 16 j + 4g .. + 3 (0
+    // beyond the panel) of column 16 (j - 1) + lr.
+    __device__ __forceinline__ void load_b(int j, T (&f)[4]) const {
+        const int r = 16 * j + 4 * g;
+        if constexpr (CX) {
+            const GT *p = A + 2 * (int64_t)(8 * (j - 1) + lr / 2) * lda;
+            const bool odd = lr & 1;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (r + 2 * h < mr) {
+                    const V2 e = *reinterpret_cast<const HSMA_GLOBAL V2 *>(p + r + 2 * h);
+                    f[2 * h] = odd ? -e.y : e.x;
+                    f[2 * h + 1] = odd ? e.x : e.y;
+                }
+            }
+        } else {
+            const GT *p = A + (int64_t)(16 * (j - 1) + lr) * lda;
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                if (r + s < mr) f[s] = p[r + s];
+        }
+    }
+
+    // The A fragments of a 16 x 16 block in LDS.
+    __device__ __forceinline__ void read_a(const T *blk, T (&f)[4]) const {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) f[s] = blk[16 * (4 * g + s) + (arow ^ (4 * g + s))];
     }
 
     // acc_q += L_ji (-X_i).
     template <int I, int Q>
     __device__ __forceinline__ void update(const T (&xb)[4]) {
+        multiply<Q>(a[I % D][Q], xb);
+    }
+    template <int Q>
+    __device__ __forceinline__ void multiply(const T (&e)[4], const T (&xb)[4]) {
         T f[4];
-        const T(&e)[4] = a[I % D][Q];
         if constexpr (CX) {
             // Real row r, real column 2c + q of the expansion: component
             // (r ^ q) & 1, negated where q = 1 and r is even.
@@ -178,63 +280,156 @@ struct Solve {
         for (int s = 0; s < 4; ++s) acc[Q] = Mma<T>::mma(f[s], xb[s], acc[Q]);
     }
 
-    // X_J = inv(L_JJ) acc, published and stored (by its owner).
-    template <int J>
-    __device__ __forceinline__ void finish() {
-        constexpr int q = J / kWaves;
-        T f[4];
+    // CHAIN: the products with every X before the panel, two blocks (a group)
+    // at a time: a wavefront fetches a quarter of a block from the mail and LDS
+    // hands it round.  Four groups are on their way at once, and one that came
+    // back empty is asked for again two rounds before it is needed: a look costs
+    // 1.6 us, so with one group on its way the panel falls ever further behind
+    // the one before it.  L is loaded four blocks ahead.
+    __device__ __forceinline__ void apply_left() {
+        const int groups = left / 2;  // a multiple of 8: panels have 16 blocks
+        T l[4][NQ][4], nx[4];
+        const T *src = mail + 256 * (w >> 2) + 64 * (w & 3) + lane;
+        static_for<0, 4>([&](auto K) {
+            constexpr int k = decltype(K)::value;
+            nx[k] = mail_load(src + 512 * k);
+            static_for<0, NQ>([&](auto Q) { load_a(decltype(Q)::value, k - left, l[k][decltype(Q)::value]); });
+        });
+        for (int t4 = 0; t4 < groups; t4 += 4) {
+            static_for<0, 4>([&](auto H) {
+                constexpr int h = decltype(H)::value;
+                const int t = t4 + h;
+                for (int polls = 0; __any(is_empty(nx[h])) && polls < kMaxPolls; ++polls)
+                    nx[h] = mail_load(src + 512 * (int64_t)t);
+                T *buf = sh.left[h & 1];
+                buf[256 * (w >> 2) + 64 * (w & 3) + lane] = nx[h];
+                constexpr int s2 = (h + 2) % 4;
+                if (t + 2 < groups && __any(is_empty(nx[s2]))) nx[s2] = mail_load(src + 512 * (int64_t)(t + 2));
+                if (t + 4 < groups) nx[h] = mail_load(src + 512 * (int64_t)(t + 4));
+                __syncthreads();
+                static_for<0, 2>([&](auto K) {
+                    constexpr int k = decltype(K)::value, slot = (2 * h + k) % 4;
+                    T xb[4];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) f[s] = sh.inv[J][16 * (4 * g + s) + (arow ^ (4 * g + s))];
+                    for (int s = 0; s < 4; ++s) xb[s] = buf[256 * k + 64 * s + lane];
+                    static_for<0, NQ>([&](auto Q) {
+                        constexpr int q = decltype(Q)::value;
+                        multiply<q>(l[slot][q], xb);
+                        // (Beyond the last: the first columns again.)
+                        load_a(q, (t + 2 < groups ? 2 * t + 4 : 0) + k - left, l[slot][q]);
+                    });
+                });
+            });
+        }
+    }
+
+    // CHAIN: block J of the panel into the mail (by its owner).
+    __device__ __forceinline__ void mail_send(int J, const Acc &x) {
+        T *dst = mail + 256 * (int64_t)(left + J) + lane;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) mail_store(dst + 64 * v, -x[v]);
+    }
+
+    // y = inv(L_JJ) acc (by the owner of block J, X_0 .. X_{J-2} applied).
+    template <int J>
+    __device__ __forceinline__ void prepare() {
+        constexpr int q = J / kWaves;
         if (16 * J + 16 > mr) {  // rows beyond the panel hold no numbers
 #pragma unroll
             for (int v = 0; v < 4; ++v)
                 if (16 * J + 4 * g + v >= mr) acc[q][v] = 0;
         }
-        Acc x = {0, 0, 0, 0};
+        y = Acc{0, 0, 0, 0};
 #pragma unroll
-        for (int s = 0; s < 4; ++s) x = Mma<T>::mma(f[s], acc[q][s], x);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) sh.x[J & 1][64 * v + lane] = -x[v];
-        store4(16 * J + 4 * g, x);
+        for (int s = 0; s < 4; ++s) y = Mma<T>::mma(fi[q][s], acc[q][s], y);
     }
 
-    // Step I: X_I is in LDS once the barrier is passed.
+    // X_J = y to the other wavefronts (by its owner): LDS takes a wavefront's
+    // writes in order.
+    template <int J>
+    __device__ __forceinline__ void publish() {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) sh.blk[J][64 * v + lane] = -y[v];
+        asm volatile("" ::: "memory");
+        __hip_atomic_store(&sh.done, J + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __device__ __forceinline__ void await_block(int i) const {
+        for (int polls = 0; polls < kMaxPolls; ++polls)
+            if (__hip_atomic_load(&sh.done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > i) break;
+        asm volatile("" ::: "memory");
+    }
+
+    // Step I: everything X_I is for.
     template <int I>
     __device__ __forceinline__ void step() {
         if constexpr (I + 1 < NB) {
             if (I + 1 < nb) {
                 constexpr int W1 = (I + 1) % kWaves, Q1 = (I + 1) / kWaves;
-                __syncthreads();
+                constexpr int W2 = (I + 2) % kWaves, Q2 = (I + 2) / kWaves;
+                const bool chain = w == W1;
+                if (chain) __builtin_amdgcn_s_setprio(3);
+                await_block(I);
                 T xb[4];
 #pragma unroll
-                for (int s = 0; s < 4; ++s) xb[s] = sh.x[I & 1][64 * s + lane];
-                if (w == W1) {
-                    update<I, Q1>(xb);
-                    finish<I + 1>();
-                } else if (w > W1) {
-                    update<I, Q1>(xb);
+                for (int s = 0; s < 4; ++s) xb[s] = sh.blk[I][64 * s + lane];
+                Acc mine = y;  // X_I at its owner
+                if (chain) {
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) y = Mma<T>::mma(fp[Q1][s], xb[s], y);
+                    publish<I + 1>();
+                    __builtin_amdgcn_s_setprio(0);
                 }
-                static_for<Q1 + 1, NQ>([&](auto Q) { update<I, decltype(Q)::value>(xb); });
-                if constexpr (I + D + 1 < NB) load_l<I + D>();
+                if constexpr (I + 2 < NB) {
+                    // Blocks I + 2 and up; the owner of I + 2 readies it, and
+                    // leaves its later blocks until it has formed X_{I+2}.
+                    if (w == W2) {
+                        __builtin_amdgcn_s_setprio(2);
+                        update<I, Q2>(xb);
+                        if (I + 2 < nb) prepare<I + 2>();
+                        __builtin_amdgcn_s_setprio(0);
+                    } else {
+                        if constexpr (I > 0) {
+                            if (chain) {
+                                T xp[4];
+#pragma unroll
+                                for (int s = 0; s < 4; ++s) xp[s] = sh.blk[I - 1][64 * s + lane];
+                                static_for<Q1 + 1, NQ>([&](auto Q) { update<I - 1, decltype(Q)::value>(xp); });
+                            }
+                        }
+                        if (w > W2) update<I, Q2>(xb);
+                        static_for<Q2 + 1, NQ>([&](auto Q) { update<I, decltype(Q)::value>(xb); });
+                    }
+                }
+                // X_I leaves from its owner.
+                if (w == I % kWaves) {
+                    if constexpr (CHAIN) mail_send(I, mine);
+                    store4(16 * I + 4 * g, mine);
+                }
+                if constexpr (I + D + 1 < NB) load_l<I + D - 1>();
                 step<I + 1>();
             }
+        }
+    }
+
+    // What the steps have left: the last block (nothing waits for it here).
+    __device__ __forceinline__ void drain() {
+        const int J = nb - 1;
+        if (w == J % kWaves) {
+            if constexpr (CHAIN) mail_send(J, y);
+            store4(16 * J + 4 * g, y);
         }
     }
 
     // Inverses of this wavefront's diagonal blocks, one per 16-lane row: lane
     // c holds row c of the block and solves for column c of the inverse, the
     // coefficients reaching the lanes by row broadcasts.
-    __device__ __forceinline__ void invert(bool unit) {
-        constexpr int N = 16 / ES;  // order of a block
-        const int q = g < NQ ? g : NQ - 1;
-        const int j = w + kWaves * q;
-        const int rows = mr / ES;
-        const int c = lane & (N - 1);
-        const int d0 = N * j < rows ? N * j : 0;  // (a block beyond the panel is not used)
+    static constexpr int N = 16 / ES;  // order of a block in elements
+    __device__ __forceinline__ int inv_block() const { return w + kWaves * (g < NQ ? g : NQ - 1); }
+    __device__ __forceinline__ void load_diag(T (&lre)[N], T (&lim)[N]) const {
+        const int rows = mr / ES, c = lane & (N - 1);
+        const int d0 = N * inv_block() < rows ? N * inv_block() : 0;  // (a block beyond the panel is not used)
         const int row = d0 + c < rows ? d0 + c : rows - 1;
-        const bool in = d0 + c < rows;
         const GT *p = A + (int64_t)ES * row;
-        T lre[N], lim[N];
 #pragma unroll
         for (int k = 0; k < N; ++k) {
             // Only the strict lower triangle and the diagonal are read.
@@ -248,6 +443,11 @@ struct Solve {
                 lim[k] = 0;
             }
         }
+    }
+    __device__ __forceinline__ void invert(bool unit, T (&lre)[N], T (&lim)[N]) {
+        const int j = inv_block(), c = lane & (N - 1);
+        const int d0 = N * j < mr / ES ? N * j : 0;
+        const bool in = d0 + c < mr / ES;
         T dr = 1, di = 0;
         if (!unit && in) {
             // Column c holds the diagonal (row - d0 == c here).
@@ -302,7 +502,7 @@ struct Solve {
             });
         });
         if (g >= NQ || (CX && (lane & 8))) return;
-        T *dst = sh.inv[j];
+        T *dst = sh.blk[j];
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             if constexpr (CX) {
@@ -318,8 +518,8 @@ struct Solve {
     }
 
     __device__ __forceinline__ void run(const PanelParams<T> &p, int tile) {
-        A = (const GT *)p.A;
-        lda = p.lda;
+        A = (const GT *)uniform(p.A);
+        lda = (int64_t)uniform((const void *)p.lda);
         mr = ES * p.rows;
         nb = (mr + 15) / 16;
         lane = threadIdx.x & 63;
@@ -327,23 +527,49 @@ struct Solve {
         g = lane >> 4;
         lr = lane & 15;
         arow = Mma<T>::a_row(lr);
+        static_for<0, NQ>([&](auto Q) {
+            constexpr int q = decltype(Q)::value;
+            const int r = 16 * (w + kWaves * q) + arow;
+            if constexpr (CX) at[q] = (const HSMA_GLOBAL char *)(A + 2 * (r / 2 < mr / 2 ? r / 2 : mr / 2 - 1) + 4 * g * lda);
+            else at[q] = (const HSMA_GLOBAL char *)(A + (r < mr ? r : mr - 1) + 4 * g * lda);
+        });
         const int64_t c = 16 * (int64_t)tile + lr;
         col_ok = c < p.n;
         col = (GT *)p.B + (int64_t)ES * (col_ok ? c : p.n - 1) * p.ldb;
 
-        invert(p.unit);
+        if constexpr (CHAIN) {
+            left = p.left;
+            mail = p.mail + 256 * (int64_t)p.nblk * tile;
+        }
+        {
+            T lre[N], lim[N], lb[NQ][4];
+            load_diag(lre, lim);
+            static_for<0, NQ>([&](auto Q) {
+                constexpr int q = decltype(Q)::value;
+                const int j = w + kWaves * q;
+#pragma unroll
+                for (int s = 0; s < 4; ++s) lb[q][s] = 0;
+                if (j > 0 && j < nb) load_b(j, lb[q]);
+            });
+            invert(p.unit, lre, lim);
+            static_for<0, NQ>([&](auto Q) {
+                constexpr int q = decltype(Q)::value;
+                const int j = w + kWaves * q;
+                read_a(sh.blk[j], fi[q]);
+                Acc t = {0, 0, 0, 0};
+#pragma unroll
+                for (int s = 0; s < 4; ++s) t = Mma<T>::mma(fi[q][s], lb[q][s], t);
+                // Row 4g + v, column lr, to the A fragments' order through LDS.
+#pragma unroll
+                for (int v = 0; v < 4; ++v) sh.blk[j][16 * lr + ((4 * g + v) ^ lr)] = t[v];
+                read_a(sh.blk[j], fp[q]);
+            });
+        }
         __builtin_amdgcn_sched_barrier(0);
         static_for<0, NQ>([&](auto Q) {
             constexpr int q = decltype(Q)::value;
             acc[q] = load4(16 * (w + kWaves * q) + 4 * g);
         });
-        // (A panel of one block has nothing below it: its L may end before
-        // column 15.)
-        if (nb > 1) {
-            static_for<0, D>([&](auto I) {
-                if constexpr (decltype(I)::value + 1 < NB) load_l<decltype(I)::value>();
-            });
-        }
         if (p.alpha_re != 1 || p.alpha_im != 0) {
             static_for<0, NQ>([&](auto Q) {
                 Acc &v = acc[decltype(Q)::value];
@@ -360,29 +586,87 @@ struct Solve {
                 }
             });
         }
-        if (w == 0) finish<0>();
+        // (A panel of one block has nothing below it: its L may end before
+        // column 15.)
+        if (nb > 1) {
+            static_for<0, D - 1>([&](auto I) {
+                if constexpr (decltype(I)::value + 2 < NB) load_l<decltype(I)::value>();
+            });
+        }
+        if constexpr (CHAIN) {
+            if (left > 0) apply_left();
+        }
+        if (w == 0) {
+            prepare<0>();
+            publish<0>();
+        } else if (w == 1 && nb > 1) {
+            prepare<1>();
+        }
         step<0>();
+        drain();
     }
 };
 
 // One panel (descs == nullptr), or many: descriptor d owns workgroups
 // [tile0, tile0 + ceil(n / 16)), found by binary search.
+template <typename T>
+__device__ __forceinline__ int find(const PanelParams<T> *__restrict__ descs, int nd, int tile) {
+    int lo = 0, hi = nd - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (descs[mid].tile0 <= tile) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
 template <typename T, bool CX, int NQ>
 __global__ __launch_bounds__(64 * kWaves, 2) void hsma_panel(const PanelParams<T> one,
                                                              const PanelParams<T> *__restrict__ descs, int nd) {
-    typedef Solve<T, CX, NQ> S;
+    typedef Solve<T, CX, NQ, false> S;
     __shared__ typename S::Shared sh;
     PanelParams<T> p = one;
     int tile = blockIdx.x;
     if (descs) {
-        int lo = 0, hi = nd - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (descs[mid].tile0 <= tile) lo = mid;
-            else hi = mid - 1;
-        }
-        p = descs[lo];
+        p = descs[find(descs, nd, tile)];
         tile -= p.tile0;
+    }
+    if (threadIdx.x == 0) sh.done = 0;
+    __syncthreads();
+    S s(sh);
+    s.run(p, tile);
+}
+
+// A chain: workgroups take tickets, and ticket t of one solve is panel t /
+// strips, strip t % strips, so a workgroup waits only for workgroups that
+// started before it.  `one` describes panel 0 with the solve's row count in
+// `rows`; with descs each descriptor is one panel, listed so that a solve's
+// panels come in order.
+template <typename T, bool CX>
+__global__ __launch_bounds__(64 * kWaves, 2) void hsma_chain(const PanelParams<T> one,
+                                                             const PanelParams<T> *__restrict__ descs, int nd,
+                                                             unsigned *__restrict__ tickets) {
+    typedef Solve<T, CX, kChainRows / (16 * kWaves), true> S;
+    __shared__ typename S::Shared sh;
+    if (threadIdx.x == 0) {
+        sh.done = 0;
+        sh.ticket = (int)atomicAdd(tickets, 1u);
+    }
+    __syncthreads();
+    int tile = __builtin_amdgcn_readfirstlane(sh.ticket);
+    PanelParams<T> p = one;
+    if (descs) {
+        p = descs[find(descs, nd, tile)];
+        tile -= p.tile0;
+    } else {
+        constexpr int ES = CX ? 2 : 1, H = kChainRows / ES;
+        const int strips = (int)((p.n + 15) / 16);
+        const int r = tile / strips;
+        tile -= r * strips;
+        p.left = r * (kChainRows / 16);
+        p.A = one.A + ES * ((int64_t)r * H) * (1 + one.lda);
+        p.B = one.B + ES * (int64_t)r * H;
+        p.rows = one.rows - r * H < H ? one.rows - r * H : H;
     }
     S s(sh);
     s.run(p, tile);
@@ -403,6 +687,47 @@ hsma_status launch(const PanelParams<T> &one, const PanelParams<T> *descs, int n
 
 }  // namespace
 
+// Mail of every strip, then a ticket counter.
+template <typename T>
+size_t chain_bytes(bool cx, int64_t m, int64_t n) {
+    const int64_t blocks = (m * (cx ? 2 : 1) + 15) / 16, strips = (n + 15) / 16;
+    return (size_t)(blocks * strips) * 256 * sizeof(T) + 256;
+}
+template size_t chain_bytes<double>(bool, int64_t, int64_t);
+template size_t chain_bytes<float>(bool, int64_t, int64_t);
+
+template <typename T>
+hsma_status empty_mail(T *mail, int64_t words, unsigned *tickets, hipStream_t s) {
+    const int64_t blocks = std::min<int64_t>((words + 1023) / 1024, 4096);
+    ProfScope prof(HSMA_PHASE_OTHER, 0.0, s);
+    hipLaunchKernelGGL(hsma_mail_empty<T>, dim3((unsigned)blocks), dim3(256), 0, s, mail, words, tickets);
+    HSMA_HIP(hipGetLastError());
+    return HSMA_SUCCESS;
+}
+
+template <typename T>
+hsma_status launch_chain(bool cx, const PanelParams<T> &q, int64_t m, void *ws, hipStream_t s) {
+    const int es = cx ? 2 : 1;
+    const int64_t blocks = (m * es + 15) / 16, strips = (q.n + 15) / 16;
+    const int64_t panels = (m * es + kChainRows - 1) / kChainRows;
+    if (panels * strips > 0x7fffffff || blocks * strips > 0x7fffffff) return HSMA_INVALID_SIZE;
+    PanelParams<T> p = q;
+    p.rows = (int)m;
+    p.nblk = (int)blocks;
+    p.mail = static_cast<T *>(ws);
+    const int64_t words = 256 * blocks * strips;
+    unsigned *tickets = reinterpret_cast<unsigned *>(p.mail + words);
+    HSMA_TRY(empty_mail<T>(p.mail, words, tickets, s));
+    ProfScope prof(HSMA_PHASE_LEAF, (cx ? 4.0 : 1.0) * m * (double)m * (double)p.n, s);
+    const dim3 grid((unsigned)(panels * strips)), block(64 * kWaves);
+    if (cx) hipLaunchKernelGGL((hsma_chain<T, true>), grid, block, 0, s, p, nullptr, 0, tickets);
+    else hipLaunchKernelGGL((hsma_chain<T, false>), grid, block, 0, s, p, nullptr, 0, tickets);
+    HSMA_HIP(hipGetLastError());
+    return HSMA_SUCCESS;
+}
+template hsma_status launch_chain<double>(bool, const PanelParams<double> &, int64_t, void *, hipStream_t);
+template hsma_status launch_chain<float>(bool, const PanelParams<float> &, int64_t, void *, hipStream_t);
+
 template <typename T>
 hsma_status launch_panel(bool cx, const PanelParams<T> &p, hipStream_t s) {
     if (p.rows <= 0 || p.n <= 0) return HSMA_SUCCESS;
@@ -412,6 +737,21 @@ hsma_status launch_panel(bool cx, const PanelParams<T> &p, hipStream_t s) {
 }
 template hsma_status launch_panel<double>(bool, const PanelParams<double> &, hipStream_t);
 template hsma_status launch_panel<float>(bool, const PanelParams<float> &, hipStream_t);
+
+hsma_status launch_chain_grouped(bool cx, const PanelParams<double> *descs, int nd, int64_t tiles, double *mail,
+                                 int64_t words, double flops, hipStream_t s) {
+    if (nd <= 0 || tiles <= 0) return HSMA_SUCCESS;
+    if (tiles > 0x7fffffff) return HSMA_INVALID_SIZE;
+    unsigned *tickets = reinterpret_cast<unsigned *>(mail + words);
+    HSMA_TRY(empty_mail<double>(mail, words, tickets, s));
+    ProfScope prof(HSMA_PHASE_LEAF, flops, s);
+    const PanelParams<double> none{};
+    const dim3 grid((unsigned)tiles), block(64 * kWaves);
+    if (cx) hipLaunchKernelGGL((hsma_chain<double, true>), grid, block, 0, s, none, descs, nd, tickets);
+    else hipLaunchKernelGGL((hsma_chain<double, false>), grid, block, 0, s, none, descs, nd, tickets);
+    HSMA_HIP(hipGetLastError());
+    return HSMA_SUCCESS;
+}
 
 hsma_status launch_panel_grouped(bool cx, const PanelParams<double> *descs, int nd, int max_rows, int64_t tiles,
                                  double flops, hipStream_t s) {

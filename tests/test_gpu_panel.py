@@ -89,3 +89,43 @@ def test_mixed_products_exact():
         hs.trsm(Ls.t(), B, 1.0, mixed=True)
         torch.cuda.synchronize()
         assert torch.equal(B, want), (m, m1, n)
+
+
+@pytest.mark.parametrize("dt", list("dzsc"))
+def test_chains_on_two_streams_and_with_infinities(dt):
+    """Chains (one launch, workgroups handing X on): several at once on two
+    streams give the bits each gives alone, and infinities and NaNs in B stay
+    in their columns and end where a lone solve ends."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+    cases = []
+    for m, n in ((1300, 40), (2049, 17), (700, 333)):
+        Ls = torch.triu(_ints((m, m), dt, -2, 2, g), 1) / m   # row j: column j of L
+        Ls.diagonal().fill_(1.5)
+        B = hs.colmajor(m, n, DT[dt])
+        B.copy_(_ints((m, n), dt, -3, 3, g))
+        B[m // 3, 2] = float("inf")
+        B[m // 2, 5] = float("nan")
+        alone = B.clone()
+        hs.trsm(Ls.t(), alone, 1.0)
+        cases.append((Ls, B, alone))
+    torch.cuda.synchronize()
+    sides = [torch.cuda.Stream() for _ in range(2)]
+    outs = []
+    for rep in range(4):
+        for k, (Ls, B, _) in enumerate(cases):
+            X = B.clone()
+            torch.cuda.synchronize()
+            hs.trsm(Ls.t(), X, 1.0, stream=sides[(rep + k) % 2])
+            outs.append((k, X))
+    torch.cuda.synchronize()
+    for k, X in outs:
+        a, b = (torch.view_as_real(t.resolve_conj()) if t.is_complex() else t for t in (X, cases[k][2]))
+        assert torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(torch.nan_to_num(a), torch.nan_to_num(b)), (dt, k)
+    for Ls, B, alone in cases:
+        fine = [c for c in range(B.shape[1]) if c not in (2, 5)]
+        ref = torch.linalg.solve_triangular(Ls.t().to(DT["z" if dt in "zc" else "d"]).contiguous(),
+                                            B[:, fine].to(DT["z" if dt in "zc" else "d"]).contiguous(), upper=False)
+        # forward error of a solve with kappa < 10: a few units in the last place times m
+        eps = 2.0 ** (-52 if dt in "dz" else -23)
+        assert (alone[:, fine] - ref).abs().max().item() <= 10 * B.shape[0] * eps * ref.abs().max().item()
+        assert not torch.isfinite(alone[B.shape[0] // 3, 2].abs()) and torch.isnan(alone[B.shape[0] // 2, 5].abs())
