@@ -48,17 +48,14 @@ hsma_status launch_role(GemmRole role, const GemmParams &p, hipStream_t s) {
         if (best == 3) return tiles64<CX, 64, 32, 32, 2, 2>(p, role, s);
         return tiles64<CX, 32, 32, 64, 2, 2>(p, role, s);
     }
-    // Trailing updates.  Those of the deepest recursion levels are thin (M =
-    // K = one or two block sizes): below four workgroups per CU, narrower
-    // tiles keep every CU busy.  Each element's K order is the same in every
-    // shape.
-    const int64_t want = 4 * cus;
-    const int64_t rows128 = (p.M + 127) / 128, rows64 = (p.M + 63) / 64;
-    if (rows128 * ((p.N + 127) / 128) >= want) return tiles64<CX, 128, 128, 16, 2, 2>(p, role, s);
-    if (rows128 * ((p.N + 63) / 64) >= want) return tiles64<CX, 128, 64, 16, 2, 2>(p, role, s);
-    if (rows64 * ((p.N + 63) / 64) >= want) return tiles64<CX, 64, 64, 32, 2, 2>(p, role, s);
-    if (rows64 * ((p.N + 31) / 32) >= want) return tiles64<CX, 64, 32, 32, 2, 2>(p, role, s);
-    return tiles64<CX, 32, 32, 64, 2, 2>(p, role, s);
+    // Trailing updates.  Each element's K order is the same in every shape.
+    switch (update_tile_shape(p.M, p.N, cus)) {
+        case 0: return tiles64<CX, 128, 128, 16, 2, 2>(p, role, s);
+        case 1: return tiles64<CX, 128, 64, 16, 2, 2>(p, role, s);
+        case 2: return tiles64<CX, 64, 64, 32, 2, 2>(p, role, s);
+        case 3: return tiles64<CX, 64, 32, 32, 2, 2>(p, role, s);
+        default: return tiles64<CX, 32, 32, 64, 2, 2>(p, role, s);
+    }
 }
 
 // Mixed precision (real data): operands rounded to FP32 (round to nearest

@@ -63,4 +63,43 @@ inline int lower_tile_shape(int64_t M, int64_t N, bool cx, int count, int64_t cu
     return best;
 }
 
+// Tile of a plain product.  A tile alone on its CU cannot hide its own
+// latencies and runs at `solo` of the matrix rate; with `wg` of them resident
+// the CU reaches `full` of it.  Measured on MI355X in FP64 at K = 1024, TF/s
+// with one tile per CU and with many (the units give 76): 128 x 128 56 and 67,
+// 128 x 64 47 and 67, 64 x 64 38 and 60, 64 x 32 32 and 57, 32 x 32 29 and 48.  A
+// launch takes its full rounds of cus * wg tiles and then what the rest needs.
+// Against "at least four tiles per CU or the next smaller shape": 2500 x 1777
+// from the right 333 us to 310.
+struct UpdateShape {
+    int bm, bn, wg;
+    double solo, full;
+};
+constexpr int kNumUpdateShapes = 5;
+constexpr UpdateShape kUpdateShapes[kNumUpdateShapes] = {{128, 128, 2, 0.74, 0.89},
+                                                         {128, 64, 3, 0.62, 0.88},
+                                                         {64, 64, 2, 0.50, 0.79},
+                                                         {64, 32, 3, 0.42, 0.75},
+                                                         {32, 32, 2, 0.38, 0.63}};
+
+// Index into kUpdateShapes for an M x N product on `cus` CUs (M in real-view
+// rows); ties go to the larger tile.
+inline int update_tile_shape(int64_t M, int64_t N, int64_t cus) {
+    int best = 0;
+    double best_cost = 0.0;
+    for (int k = 0; k < kNumUpdateShapes; ++k) {
+        const UpdateShape &t = kUpdateShapes[k];
+        const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+        const int64_t rounds = tiles / (cus * t.wg), rest = tiles - rounds * cus * t.wg;
+        const double area = (double)t.bm * t.bn;
+        double cost = (double)rounds * t.wg * area / t.full;
+        if (rest > 0) cost += std::max(area / t.solo, (double)((rest + cus - 1) / cus) * area / t.full);
+        if (k == 0 || cost < best_cost) {
+            best = k;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
 }  // namespace hsma
