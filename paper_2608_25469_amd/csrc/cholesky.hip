@@ -8,18 +8,17 @@
 //     L21 = A21 inv(L11)^H            the right-side, conjugate-transpose TRSM
 //     A22 <- A22 - L21 L21^H          lower triangle only, FP64 matrix cores
 //     L22 = chol(A22)
-// with diagonal blocks of at most 64 rows factored by one wavefront, a row
-// per lane in registers.
-// The split point is a multiple of 64, so every base block is whole except
-// the last.  The solve L L^H X = B is two TRSMs: L Y = B, then L^H X = Y.
+// with diagonal blocks of at most 256 rows (128 complex) factored by one
+// workgroup in registers.  The solve L L^H X = B is two TRSMs: L Y = B, then L^H X = Y.
 //
 // No definiteness check is made: a non-positive pivot gives NaN (the square
 // root of a negative number), which propagates, as the TRSM propagates a zero
 // diagonal.  The strict upper triangle of A is neither read nor written.
 
 #include <algorithm>
+#include <type_traits>
 
-#include "internal.h"
+#include "gemm_core.h"
 
 namespace hsma {
 
@@ -30,142 +29,281 @@ hsma_status trsm_impl(hsma_diag diag, int64_t m, int64_t n, const void *alpha, c
 
 namespace {
 
-constexpr int kBase = 64;
+using gemmk::Mma;
 
-template <bool CX>
-struct Z;
-template <>
-struct Z<false> {
-    typedef double V;
-    static __device__ __forceinline__ V ld(const double *p, int64_t i) { return p[i]; }
-    static __device__ __forceinline__ void st(double *p, int64_t i, V v) { p[i] = v; }
-    static __device__ __forceinline__ double re(V v) { return v; }
-    static __device__ __forceinline__ V scale(V v, double s) { return v * s; }
-    // a - b conj(c)
-    static __device__ __forceinline__ V fnms_conj(V a, V b, V c) { return __fma_rn(-b, c, a); }
-    static __device__ __forceinline__ V real(double d) { return d; }
-};
-template <>
-struct Z<true> {
-    typedef dbl2u V;
-    static __device__ __forceinline__ V ld(const double *p, int64_t i) {
-        return *reinterpret_cast<const dbl2u *>(p + 2 * i);
-    }
-    static __device__ __forceinline__ void st(double *p, int64_t i, V v) {
-        *reinterpret_cast<dbl2u *>(p + 2 * i) = v;
-    }
-    static __device__ __forceinline__ double re(V v) { return v.x; }
-    static __device__ __forceinline__ V scale(V v, double s) { return V{v.x * s, v.y * s}; }
-    static __device__ __forceinline__ V fnms_conj(V a, V b, V c) {
-        // b conj(c) = (br cr + bi ci, bi cr - br ci), as four fused steps
-        const double x = __fma_rn(-b.y, c.y, __fma_rn(-b.x, c.x, a.x));
-        const double y = __fma_rn(b.x, c.y, __fma_rn(-b.y, c.x, a.y));
-        return V{x, y};
-    }
-    static __device__ __forceinline__ V real(double d) { return V{d, 0.0}; }
-};
+// Rows of the base kernel in the real view: 16 blocks of 16 rows.
+constexpr int kBaseRows = 256;
+constexpr int kBaseWaves = 8;
+constexpr int kBaseSlots = 17;  // 136 blocks on or below the diagonal, over 8 wavefronts
 
-// Lane l's value of v, to every lane (a wavefront-uniform scalar).
-__device__ __forceinline__ double from_lane(double v, int l) {
-    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, l);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), l);
-    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+int base_order(bool cx) { return kBaseRows / (cx ? 2 : 1); }
+
+template <int B, int E, typename F>
+__device__ __forceinline__ void static_for(F &&f) {
+    if constexpr (B < E) {
+        f(std::integral_constant<int, B>{});
+        static_for<B + 1, E>(f);
+    }
 }
 
-// One n x n diagonal block (n <= 64), right-looking, on four wavefronts:
-// lane i of every wavefront holds row i, and wavefront w the columns c with
-// c % 4 == w (16 of them, c = 4u + w in slot u).  At step j the wavefront
-// that owns column j takes lane j's a_jj (a lane read), forms d = sqrt(a_jj)
-// and 1/d, scales its a_ij by 1/d in the lanes below j (lane j keeps d), and
-// publishes the column in LDS; after one barrier every wavefront updates its
-// own columns c > j, a_ic -= l_ij conj(l_cj), with l_ij and l_cj read from
-// that LDS column (a broadcast for l_cj).  The column buffer alternates
-// between two copies, so a step's writes never meet the previous step's
-// reads and one barrier per step suffices.  Entries right of a lane's
-// diagonal and rows at or beyond n take values that are never stored and
-// never read as l_cj (only rows c > j are read at step j).  Rows are loaded
-// and stored column by column, consecutive lanes on consecutive rows.
-template <bool CX>
-__global__ __launch_bounds__(256) void hsma_potrf_base(double *__restrict__ A, int64_t lda, int n) {
-    typedef Z<CX> O;
-    typedef typename O::V V;
-    constexpr int NW = 4, NU = kBase / NW;
-    __shared__ V col[2][kBase];
-    const int i = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool row_ok = i < n;
-    V r[NU];
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-        const int c = NW * u + w;
-        r[u] = (row_ok && c <= i && c < n) ? O::ld(A, i + (int64_t)c * lda) : O::real(0.0);
+// Lane N of each 16-lane row, to the 16 lanes of that row.
+template <int N>
+__device__ __forceinline__ double bcast(double v) {
+    return __builtin_amdgcn_mov_dpp(v, 0x150 + N, 0xf, 0xf, false);  // row_newbcast:N
+}
+
+// e -= bcast<R>(l) l and x -= bcast<R>(l) xl.  (A broadcast reads a register two
+// states after it was written at the earliest.)
+template <int R>
+__device__ __forceinline__ void fnma_pair(double &e, double &x, double l, double xl) {
+    asm volatile(
+        "s_nop 1\n"
+        "v_fmac_f64_dpp %0, -%2, %2 row_newbcast:%4 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %1, -%2, %3 row_newbcast:%4 row_mask:0xf bank_mask:0xf\n"
+        : "+v"(e), "+v"(x)
+        : "v"(l), "v"(xl), "n"(R));
+}
+
+// The square root d of a pivot p and its reciprocal, in dependent stages: a
+// third-order step from the hardware's estimate of 1/sqrt(p) (about 2^-23), a
+// correction of d against p, and one of the reciprocal against d; both end
+// within an ulp where nothing on the way over- or underflows.
+struct Root {
+    double p, y, q, r, t, u, d, inv;
+    static constexpr int kStages = 10;
+    static __device__ __forceinline__ bool in_range(double p) { return p > 0x1p-900 && p < 0x1p900; }
+    template <int S>
+    __device__ __forceinline__ void stage() {
+        if constexpr (S == 0) y = __builtin_amdgcn_rsq(p);
+        if constexpr (S == 1) q = p * y;
+        if constexpr (S == 2) r = __fma_rn(-q, y, 1.0);
+        if constexpr (S == 3) {
+            t = __fma_rn(r, 0.375, 0.5);
+            u = r * y;
+        }
+        if constexpr (S == 4) y = __fma_rn(t, u, y);
+        if constexpr (S == 5) {
+            q = p * y;
+            u = 0.5 * y;
+        }
+        if constexpr (S == 6) r = __fma_rn(-q, q, p);
+        if constexpr (S == 7) d = __fma_rn(r, u, q);
+        if constexpr (S == 8) r = __fma_rn(-d, y, 1.0);
+        if constexpr (S == 9) inv = __fma_rn(r, y, y);
     }
+};
+
+// The sixteen steps of a block column: each the root of the pivot, the scaled
+// column, and its product off the columns behind it, in the 16 rows of the
+// diagonal block (e, a copy per 16-lane row) and in this lane's own row (x;
+// `diag`: a row of the diagonal block).  The next pivot's column comes first,
+// and the others fill the waits of the next root's stages.  False: a pivot was
+// out of the root's range, and the values are not to be used.
+__device__ __forceinline__ bool eliminate(double (&e)[16], double (&x)[16], int lr, bool diag) {
+    Root z;
+    z.p = bcast<0>(e[0]);
+    bool ok = Root::in_range(z.p);
+    static_for<0, Root::kStages>([&](auto S) { z.stage<decltype(S)::value>(); });
+    static_for<0, 16>([&](auto K) {
+        constexpr int c = decltype(K)::value;
+        const double l = e[c] * z.inv, xl = x[c] * z.inv;
+        x[c] = diag && lr == c ? z.d : xl;
+        if constexpr (c < 15) {
+            fnma_pair<c + 1>(e[c + 1], x[c + 1], l, xl);
+            z.p = bcast<c + 1>(e[c + 1]);
+            ok &= Root::in_range(z.p);
+            constexpr int rest = 14 - c, NS = Root::kStages;
+            static_for<0, NS>([&](auto S) {
+                constexpr int i = decltype(S)::value;
+                __builtin_amdgcn_sched_barrier(0);
+                z.stage<i>();
+                __builtin_amdgcn_sched_barrier(0);
+                static_for<i * rest / NS, (i + 1) * rest / NS>([&](auto T) {
+                    constexpr int k = c + 2 + decltype(T)::value;
+                    fnma_pair<k>(e[k], x[k], l, xl);
+                });
+            });
+        }
+    });
+    return ok;
+}
+
+// The same for any pivots (zero, negative, NaN, the ends of the range), with
+// the library's root and division.
+__device__ __forceinline__ void eliminate_any(double (&e)[16], double (&x)[16], int lr, bool diag) {
+    static_for<0, 16>([&](auto K) {
+        constexpr int c = decltype(K)::value;
+        const double d = sqrt(bcast<c>(e[c])), inv = 1.0 / d;
+        const double l = e[c] * inv, xl = x[c] * inv;
+        x[c] = diag && lr == c ? d : xl;
+        static_for<c + 1, 16>([&](auto T) {
+            constexpr int k = decltype(T)::value;
+            fnma_pair<k>(e[k], x[k], l, xl);
+        });
+    });
+}
+
+// One diagonal block of at most 256 rows in the real view (256 real, 128
+// complex), right-looking over 16-column blocks, by one workgroup of eight
+// wavefronts.  A complex factor is the real view's factor: a Hermitian A's real
+// view is symmetric, and that of L has a positive diagonal and zeros above it.
+//
+// The whole lower triangle is in registers as 16 x 16 accumulators: lane (g,
+// lr) holds row lr, columns 4g .. 4g + 3 of its blocks, negated, and blocks are
+// dealt to the wavefronts in the order of their columns, so whatever is still to
+// be updated is spread evenly at every step.  Step j: block column j is in LDS.
+// Four wavefronts eliminate its sixteen columns, a row per lane and a block row
+// per 16 lanes, each 16 lanes with a copy of the diagonal block's rows, so a
+// pivot, its root and its column reach every row by row broadcasts and the
+// sixteen steps need no barrier.  The factored column goes to memory and to
+// LDS, every wavefront subtracts its blocks' products on the matrix cores (a
+// row of L as it lies is both operands), and column j + 1 goes to LDS.
+//
+// What bounds it: the sixteen dependent pivots of a step and two barriers.
+template <bool CX>
+__global__ __launch_bounds__(64 * kBaseWaves, 2) void hsma_potrf_base(double *__restrict__ A_, int64_t lda, int n) {
+    constexpr int ES = CX ? 2 : 1;
+    typedef double V2 __attribute__((ext_vector_type(2), aligned(8)));
+    typedef typename Mma<double>::Acc Acc;
+    __shared__ double col[kBaseRows * 16];   // block column j as it stands
+    __shared__ double fac[kBaseRows * 16];   // ... and factored
+    HSMA_GLOBAL double *A = (HSMA_GLOBAL double *)A_;
+    const int lane = threadIdx.x & 63, g = lane >> 4, lr = lane & 15;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int mr = ES * n, nb = (mr + 15) / 16;
+    // Column c of a block in LDS: columns 4 apart on different banks.
+    auto at = [](int c) { return 16 * (c ^ ((c >> 2) & 1)); };
+    auto put = [&](const Acc &v, int i) {
 #pragma unroll
-    for (int j = 0; j < kBase; ++j) {
-        if (j < n) {
-            V *cj = col[j & 1];
-            if (w == (j % NW)) {
-                const int uj = j / NW;
-                const double d = sqrt(from_lane(O::re(r[uj]), j));
-                const double inv = 1.0 / d;
-                const V rj = r[uj];
-                r[uj] = i > j ? O::scale(rj, inv) : (i == j ? O::real(d) : rj);
-                cj[i] = r[uj];
+        for (int h = 0; h < 4; ++h) col[256 * i + at(4 * g + h) + lr] = -v[h];
+    };
+
+    // Block (bi, bm) of each slot (bm < 0: none).
+    int bi[kBaseSlots], bm[kBaseSlots];
+    Acc acc[kBaseSlots];
+    int m = 0, rem = w;
+#pragma unroll
+    for (int u = 0; u < kBaseSlots; ++u) {
+        while (m < nb && rem >= nb - m) {
+            rem -= nb - m;
+            ++m;
+        }
+        bm[u] = m < nb ? m : -1;
+        bi[u] = m + rem;
+        rem += kBaseWaves;
+        acc[u] = Acc{0, 0, 0, 0};
+        if (bm[u] >= 0) {
+            const int R = 16 * bi[u] + lr, C0 = 16 * bm[u] + 4 * g;
+            if constexpr (CX) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int r = R / 2, c = C0 / 2 + h;
+                    if (r < n && c <= r) {
+                        V2 z = *reinterpret_cast<const HSMA_GLOBAL V2 *>(A + 2 * (r + c * lda));
+                        if (c == r) z.y = 0;
+                        acc[u][2 * h] = R & 1 ? -z.y : -z.x;
+                        acc[u][2 * h + 1] = R & 1 ? -z.x : z.y;
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int h = 0; h < 4; ++h)
+                    if (R < n && C0 + h <= R) acc[u][h] = -A[R + (C0 + h) * lda];
             }
-            __syncthreads();
-            const V lij = cj[i];
-            // Slot u holds columns NW u .. NW u + NW - 1 across the
-            // wavefronts: once the loops are unrolled, "all of them beyond
-            // j" and "none of them" are constants, and only the one slot
-            // that straddles j tests this wavefront's column.  Every live
-            // slot's l_cj is read first and the multiply-adds follow, so the
-            // LDS reads overlap instead of waiting one by one.
-            V lc[NU];
 #pragma unroll
-            for (int u = 0; u < NU; ++u)
-                if (NW * u + NW - 1 > j) lc[u] = cj[NW * u + w];
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int u = 0; u < NU; ++u) {
-                const int c = NW * u + w;
-                const bool all_after = NW * u > j;
-                const bool straddles = !all_after && NW * u + NW - 1 > j;
-                if (all_after || (straddles && c > j)) r[u] = O::fnms_conj(r[u], lij, lc[u]);
-            }
+            for (int h = 0; h < 4; ++h)
+                if (R >= mr && C0 + h == R) acc[u][h] = -1.0;  // beyond the matrix: the identity
         }
     }
 #pragma unroll
-    for (int u = 0; u < NU; ++u) {
-        const int c = NW * u + w;
-        if (row_ok && c <= i && c < n) O::st(A, i + (int64_t)c * lda, r[u]);
+    for (int u = 0; u < kBaseSlots; ++u)
+        if (bm[u] == 0) put(acc[u], bi[u]);
+    __syncthreads();
+
+    for (int j = 0; j < nb; ++j) {
+        if (w < 4 && 4 * w + 3 >= j && 4 * w < nb) {
+            const int i = 4 * w + g;
+            const bool in = i >= j && i < nb;
+            const double *own = col + 256 * (in ? i : j);
+            double e[16], x[16];
+            auto load = [&] {
+#pragma unroll
+                for (int c = 0; c < 16; ++c) e[c] = col[256 * j + at(c) + lr];
+#pragma unroll
+                for (int c = 0; c < 16; ++c) x[c] = own[at(c) + lr];
+            };
+            load();
+            if (!__all(eliminate(e, x, lr, i == j))) {
+                load();
+                eliminate_any(e, x, lr, i == j);
+            }
+            if (in) {
+#pragma unroll
+                for (int c = 0; c < 16; ++c) fac[256 * i + at(c) + lr] = x[c];
+                const int R = 16 * i + lr;
+                if (R < mr) {
+#pragma unroll
+                    for (int c = 0; c < 16; c += ES) {
+                        const int C = 16 * j + c;
+                        // (Complex: component R & 1 of element (R / 2, C / 2).)
+                        if (C / ES <= R / ES) {
+                            if constexpr (CX) A[R + C * lda] = (R & 1) && C / 2 == R / 2 ? 0.0 : x[c];
+                            else A[R + C * lda] = x[c];
+                        }
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        if (j + 1 == nb) break;
+        // (The columns 4g .. 4g + 3 in the order they lie in, the same for both
+        // operands.  The places are formed anew at each step: 34 of them do not
+        // fit beside the blocks.)
+        int fa0 = 64 * g + Mma<double>::a_row(lr), fb0 = 64 * g + lr;
+        asm volatile("" : "+v"(fa0), "+v"(fb0));
+#pragma unroll
+        for (int u = 0; u < kBaseSlots; ++u) {
+            if (bm[u] > j) {
+                double fa[4], fb[4];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    fa[s] = fac[256 * bm[u] + fa0 + 16 * s];
+                    fb[s] = fac[256 * bi[u] + fb0 + 16 * s];
+                }
+#pragma unroll
+                for (int s = 0; s < 4; ++s) acc[u] = Mma<double>::mma(fa[s], fb[s], acc[u]);
+                if (bm[u] == j + 1) put(acc[u], bi[u]);
+            }
+        }
+        __syncthreads();
     }
 }
 
 hsma_status potrf_base(bool cx, int n, double *A, int64_t lda, hipStream_t s) {
     ProfScope prof(HSMA_PHASE_FACTOR, (cx ? 4.0 : 1.0) * n * (double)n * n / 3.0, s);
-    if (cx) hipLaunchKernelGGL(hsma_potrf_base<true>, dim3(1), dim3(256), 0, s, A, lda, n);
-    else hipLaunchKernelGGL(hsma_potrf_base<false>, dim3(1), dim3(256), 0, s, A, lda, n);
+    const dim3 block(64 * kBaseWaves);
+    if (cx) hipLaunchKernelGGL(hsma_potrf_base<true>, dim3(1), block, 0, s, A, lda, n);
+    else hipLaunchKernelGGL(hsma_potrf_base<false>, dim3(1), block, 0, s, A, lda, n);
     HSMA_HIP(hipGetLastError());
     return HSMA_SUCCESS;
 }
 
 // The split of an order-n step: n1 is n/2 rounded up to a multiple of 64.
-int64_t split(int64_t n) { return ((n / 2 + kBase - 1) / kBase) * kBase; }
+int64_t split(int64_t n) { return (n / 2 + 63) / 64 * 64; }
 
 // Largest n1 * n2 over every step of the recursion (the first half can be
 // larger than n/2, so a step inside it can need more than the top one).
-int64_t max_split_product(int64_t n) {
-    if (n <= kBase) return 0;
+int64_t max_split_product(bool cx, int64_t n) {
+    if (n <= base_order(cx)) return 0;
     const int64_t n1 = split(n), n2 = n - n1;
-    return std::max(n1 * n2, std::max(max_split_product(n1), max_split_product(n2)));
+    return std::max(n1 * n2, std::max(max_split_product(cx, n1), max_split_product(cx, n2)));
 }
 
 // `work` holds at least es * n1 * n2 doubles for every split of the
 // recursion (the copy of L21^H that the trailing update reads as its right
 // operand).
 hsma_status potrf_rec(bool cx, int64_t n, double *A, int64_t lda, double *work, hipStream_t s) {
-    if (n <= kBase) return potrf_base(cx, (int)n, A, lda, s);
+    if (n <= base_order(cx)) return potrf_base(cx, (int)n, A, lda, s);
     const int es = cx ? 2 : 1;
     const int64_t n1 = split(n), n2 = n - n1;
     double *A11 = A, *A21 = A + es * n1, *A22 = A + es * (n1 + n1 * lda);
@@ -201,9 +339,9 @@ extern "C" hsma_status hsma_potrf(int64_t n, void *A, int64_t lda, hsma_dtype dt
     const bool cx = dtype == HSMA_C64F;
     const int es = cx ? 2 : 1;
     double *Ad = static_cast<double *>(A);
-    if (n <= kBase) return potrf_base(cx, (int)n, Ad, lda, s);
+    if (n <= base_order(cx)) return potrf_base(cx, (int)n, Ad, lda, s);
     void *ws = nullptr;
-    HSMA_TRY(ws_alloc(&ws, (size_t)es * max_split_product(n) * sizeof(double), s));
+    HSMA_TRY(ws_alloc(&ws, (size_t)es * max_split_product(cx, n) * sizeof(double), s));
     hsma_status st = potrf_rec(cx, n, Ad, lda, static_cast<double *>(ws), s);
     hsma_status st2 = ws_free(ws, s);
     return st != HSMA_SUCCESS ? st : st2;

@@ -98,3 +98,42 @@ def test_potrf_validation():
     with pytest.raises(hs.HsmaError) as e:
         hs.potrf(A.float())
     assert e.value.status in (2, 6)
+
+
+@pytest.mark.parametrize("cx", [False, True], ids=["dpotrf", "zpotrf"])
+def test_potrf_base_sizes(cx):
+    """Orders around the base kernel's blocks and its largest order: residual
+    ||L L^H - A|| <= 10 n u ||A||, the triangle above neither read nor written."""
+    for n in (2, 7, 8, 9, 15, 16, 31, 33, 63, 127, 129, 255, 256, 257, 513):
+        A = hpd(n, cx, 300 + n)
+        Ap = A.copy(order="F")
+        Ap[np.triu_indices(n, 1)] = np.nan
+        Ad = hs.to_colmajor(Ap, ld=n + n % 3)
+        hs.potrf(Ad)
+        torch.cuda.synchronize()
+        G = hs.from_colmajor(Ad)
+        assert np.all(np.isnan(G[np.triu_indices(n, 1)])), ("upper touched", n, cx)
+        L = np.tril(G)
+        res = np.linalg.norm(L @ L.conj().T - A, np.inf) / np.linalg.norm(A, np.inf)
+        assert res <= 10 * n * U, (n, cx, res)
+        if cx:
+            assert np.all(np.diag(G).imag == 0)
+
+
+@pytest.mark.parametrize("cx", [False, True], ids=["dpotrf", "zpotrf"])
+def test_potrf_pivots_at_the_ends(cx):
+    """Pivots of 2^-1040 and 2^1020 come out as their roots; a zero pivot is a
+    zero on the diagonal, a negative one NaN, and the columns before it stand."""
+    for n in (20, 40):
+        for k, p in ((0, 2.0 ** -1040), (17, 2.0 ** 1020), (3, 0.0), (18, -1.0)):
+            A = np.eye(n, dtype=np.complex128 if cx else np.float64) * 4
+            A[k, k] = p
+            Ad = hs.to_colmajor(np.asfortranarray(A))
+            hs.potrf(Ad)
+            torch.cuda.synchronize()
+            G = np.diag(np.tril(hs.from_colmajor(Ad))).real
+            assert np.all(G[:k] == 2), (n, k, p)
+            if p < 0:
+                assert np.isnan(G[k])
+            else:
+                assert G[k] == np.sqrt(p), (n, k, p, G[k])
