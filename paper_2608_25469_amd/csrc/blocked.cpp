@@ -159,6 +159,28 @@ hsma_status blocked_trsm32(bool cx, bool unit, int64_t m, int64_t n, cplx alpha,
     return blocked_t<float>(cx, unit, m, n, alpha, A, lda, B, ldb, span, ws, s, false);
 }
 
+// A right-hand side that is read and written through strides: a transposed or
+// reversed B, where the recursion's products would need a copy.  One panel, or a
+// chain, touches each element once on the way in and once on the way out, so
+// the strides cost nothing and the two copies (two launches, four passes over
+// B) go.
+bool solves_in_one(bool cx, int64_t m, int64_t n) {
+    return m > 64 && (m * (cx ? 2 : 1) <= kPanelRows || chain_rule(cx, sizeof(double), m, n));
+}
+
+hsma_status blocked_in_one(bool cx, int64_t m, PanelParams<double> p, hipStream_t s) {
+    p.at = 1;
+    if (m * (cx ? 2 : 1) <= kPanelRows) {
+        p.rows = (int)m;
+        return launch_panel<double>(cx, p, s);
+    }
+    void *ws = nullptr;
+    HSMA_TRY(ws_alloc(&ws, chain_bytes<double>(cx, m, p.n), s));
+    const hsma_status st = launch_chain<double>(cx, p, m, ws, s);
+    const hsma_status st2 = ws_free(ws, s);
+    return st != HSMA_SUCCESS ? st : st2;
+}
+
 // R <- R - tril(L) X, the residual of refinement and of the backward-error
 // report (FP64 products).  One product over the whole triangle: each row
 // tile accumulates its full row of L times X in one FP64 accumulator chain

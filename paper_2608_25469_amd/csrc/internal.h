@@ -189,6 +189,13 @@ struct PanelParams {
     // columns.
     int left, nblk;
     T *mail;
+    // `at` != 0: element (r, c) of the right-hand side lies at B + r rs + c cs
+    // (elements; rs and cs may be negative), conjugated if `conj`, and keep, if
+    // given, receives X as well (leading dimension ldkeep).
+    int at, conj;
+    int64_t rs, cs;
+    T *keep;
+    int64_t ldkeep;
 };
 template <typename T>
 hsma_status launch_panel(bool cx, const PanelParams<T> &p, hipStream_t s);
@@ -201,6 +208,10 @@ size_t chain_bytes(bool cx, int64_t m, int64_t n);
 // Device memory a blocked solve in panels of `span` rows needs (0: none).
 template <typename T>
 size_t blocked_bytes(bool cx, int64_t m, int64_t n, int span, bool mixed);
+// A right-hand side at strides (PanelParams::at) solved where it lies, in one
+// launch; allowed where solves_in_one says so.
+bool solves_in_one(bool cx, int64_t m, int64_t n);
+hsma_status blocked_in_one(bool cx, int64_t m, PanelParams<double> p, hipStream_t s);
 // Whether such a solve runs as a chain (blocked.cpp); elem: bytes of a component.
 bool chain_rule(bool cx, int elem, int64_t m, int64_t n);
 template <typename T>

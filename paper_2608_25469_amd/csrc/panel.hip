@@ -121,8 +121,8 @@ __global__ __launch_bounds__(256) void hsma_mail_empty(T *mail, int64_t n, unsig
 constexpr int kMaxPolls = 1 << 20;
 
 // NQ: blocks per wavefront (rows <= 128 NQ in the real view).  CHAIN: the panel
-// is one of a chain.
-template <typename T, bool CX, int NQ, bool CHAIN>
+// is one of a chain.  AT: the right-hand side lies at strides.
+template <typename T, bool CX, int NQ, bool CHAIN, bool AT = false>
 struct Solve {
     static constexpr int ES = CX ? 2 : 1;
     static constexpr int NB = kWaves * NQ;          // blocks
@@ -150,6 +150,9 @@ struct Solve {
     int w, lane, g, lr, arow;
     GT *col;           // this lane's column of B
     bool col_ok;
+    int64_t rs;        // AT: from one row to the next, in components
+    bool conj;
+    GT *keep;          // AT: this lane's column of the copy of X
     Shared &sh;
     Acc acc[NQ];
     T a[D][NQ][4];     // L_ji of steps i, i + 1, ..: slot i % D
@@ -164,7 +167,21 @@ struct Solve {
     // Four values of column `col` at rows r..r+3 (0 at or beyond mr).
     __device__ __forceinline__ Acc load4(int r) const {
         Acc v = {0, 0, 0, 0};
-        if (r + 4 <= mr) {
+        if constexpr (AT) {
+#pragma unroll
+            for (int h = 0; h < 4; h += ES) {
+                if (r + h < mr) {
+                    const GT *e = col + (r + h) / ES * rs;
+                    if constexpr (CX) {
+                        const V2 z = *reinterpret_cast<const HSMA_GLOBAL V2 *>(e);
+                        v[h] = z.x;
+                        v[h + 1] = conj ? -z.y : z.y;
+                    } else {
+                        v[h] = *e;
+                    }
+                }
+            }
+        } else if (r + 4 <= mr) {
 #pragma unroll
             for (int h = 0; h < 4; h += V) {
                 const VG t = *reinterpret_cast<const HSMA_GLOBAL VG *>(col + r + h);
@@ -180,7 +197,21 @@ struct Solve {
     }
     __device__ __forceinline__ void store4(int r, Acc v) const {
         if (!col_ok) return;
-        if (r + 4 <= mr) {
+        if constexpr (AT) {
+#pragma unroll
+            for (int h = 0; h < 4; h += ES) {
+                if (r + h < mr) {
+                    GT *e = col + (r + h) / ES * rs;
+                    if constexpr (CX) {
+                        *reinterpret_cast<HSMA_GLOBAL V2 *>(e) = V2{v[h], conj ? -v[h + 1] : v[h + 1]};
+                        if (keep) *reinterpret_cast<HSMA_GLOBAL V2 *>(keep + r + h) = V2{v[h], v[h + 1]};
+                    } else {
+                        *e = v[h];
+                        if (keep) keep[r + h] = v[h];
+                    }
+                }
+            }
+        } else if (r + 4 <= mr) {
 #pragma unroll
             for (int h = 0; h < 4; h += V) {
                 VG t;
@@ -535,7 +566,12 @@ struct Solve {
         });
         const int64_t c = 16 * (int64_t)tile + lr;
         col_ok = c < p.n;
-        col = (GT *)p.B + (int64_t)ES * (col_ok ? c : p.n - 1) * p.ldb;
+        col = (GT *)p.B + (int64_t)ES * (col_ok ? c : p.n - 1) * (AT ? p.cs : p.ldb);
+        if constexpr (AT) {
+            rs = ES * p.rs;
+            conj = p.conj;
+            keep = p.keep ? (GT *)p.keep + (int64_t)ES * (col_ok ? c : p.n - 1) * p.ldkeep : nullptr;
+        }
 
         if constexpr (CHAIN) {
             left = p.left;
@@ -620,10 +656,10 @@ __device__ __forceinline__ int find(const PanelParams<T> *__restrict__ descs, in
     return lo;
 }
 
-template <typename T, bool CX, int NQ>
+template <typename T, bool CX, int NQ, bool AT>
 __global__ __launch_bounds__(64 * kWaves, 2) void hsma_panel(const PanelParams<T> one,
                                                              const PanelParams<T> *__restrict__ descs, int nd) {
-    typedef Solve<T, CX, NQ, false> S;
+    typedef Solve<T, CX, NQ, false, AT> S;
     __shared__ typename S::Shared sh;
     PanelParams<T> p = one;
     int tile = blockIdx.x;
@@ -642,11 +678,11 @@ __global__ __launch_bounds__(64 * kWaves, 2) void hsma_panel(const PanelParams<T
 // started before it.  `one` describes panel 0 with the solve's row count in
 // `rows`; with descs each descriptor is one panel, listed so that a solve's
 // panels come in order.
-template <typename T, bool CX>
+template <typename T, bool CX, bool AT>
 __global__ __launch_bounds__(64 * kWaves, 2) void hsma_chain(const PanelParams<T> one,
                                                              const PanelParams<T> *__restrict__ descs, int nd,
                                                              unsigned *__restrict__ tickets) {
-    typedef Solve<T, CX, kChainRows / (16 * kWaves), true> S;
+    typedef Solve<T, CX, kChainRows / (16 * kWaves), true, AT> S;
     __shared__ typename S::Shared sh;
     if (threadIdx.x == 0) {
         sh.done = 0;
@@ -665,7 +701,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void hsma_chain(const PanelParams<T
         tile -= r * strips;
         p.left = r * (kChainRows / 16);
         p.A = one.A + ES * ((int64_t)r * H) * (1 + one.lda);
-        p.B = one.B + ES * (int64_t)r * H;
+        p.B = one.B + ES * (int64_t)r * H * (AT ? one.rs : 1);
+        if constexpr (AT)
+            if (p.keep) p.keep += ES * (int64_t)r * H;
         p.rows = one.rows - r * H < H ? one.rows - r * H : H;
     }
     S s(sh);
@@ -678,9 +716,19 @@ hsma_status launch(const PanelParams<T> &one, const PanelParams<T> *descs, int n
     const int mr = max_rows * (CX ? 2 : 1);
     if (mr > kPanelRows || tiles > 0x7fffffff) return HSMA_INVALID_SIZE;
     const dim3 grid((unsigned)tiles), block(64 * kWaves);
-    if (mr <= 128) hipLaunchKernelGGL((hsma_panel<T, CX, 1>), grid, block, 0, s, one, descs, nd);
-    else if (mr <= 256) hipLaunchKernelGGL((hsma_panel<T, CX, 2>), grid, block, 0, s, one, descs, nd);
-    else hipLaunchKernelGGL((hsma_panel<T, CX, 4>), grid, block, 0, s, one, descs, nd);
+    auto go = [&](auto AT) {
+        constexpr bool at = decltype(AT)::value;
+        if (mr <= 128) hipLaunchKernelGGL((hsma_panel<T, CX, 1, at>), grid, block, 0, s, one, descs, nd);
+        else if (mr <= 256) hipLaunchKernelGGL((hsma_panel<T, CX, 2, at>), grid, block, 0, s, one, descs, nd);
+        else hipLaunchKernelGGL((hsma_panel<T, CX, 4, at>), grid, block, 0, s, one, descs, nd);
+    };
+    if constexpr (sizeof(T) == 8) {
+        if (one.at) go(std::true_type{});
+        else go(std::false_type{});
+    } else {
+        if (one.at) return HSMA_NOT_SUPPORTED;
+        go(std::false_type{});
+    }
     HSMA_HIP(hipGetLastError());
     return HSMA_SUCCESS;
 }
@@ -720,8 +768,18 @@ hsma_status launch_chain(bool cx, const PanelParams<T> &q, int64_t m, void *ws, 
     HSMA_TRY(empty_mail<T>(p.mail, words, tickets, s));
     ProfScope prof(HSMA_PHASE_LEAF, (cx ? 4.0 : 1.0) * m * (double)m * (double)p.n, s);
     const dim3 grid((unsigned)(panels * strips)), block(64 * kWaves);
-    if (cx) hipLaunchKernelGGL((hsma_chain<T, true>), grid, block, 0, s, p, nullptr, 0, tickets);
-    else hipLaunchKernelGGL((hsma_chain<T, false>), grid, block, 0, s, p, nullptr, 0, tickets);
+    auto go = [&](auto AT) {
+        constexpr bool at = decltype(AT)::value;
+        if (cx) hipLaunchKernelGGL((hsma_chain<T, true, at>), grid, block, 0, s, p, nullptr, 0, tickets);
+        else hipLaunchKernelGGL((hsma_chain<T, false, at>), grid, block, 0, s, p, nullptr, 0, tickets);
+    };
+    if constexpr (sizeof(T) == 8) {
+        if (p.at) go(std::true_type{});
+        else go(std::false_type{});
+    } else {
+        if (p.at) return HSMA_NOT_SUPPORTED;
+        go(std::false_type{});
+    }
     HSMA_HIP(hipGetLastError());
     return HSMA_SUCCESS;
 }
@@ -747,8 +805,8 @@ hsma_status launch_chain_grouped(bool cx, const PanelParams<double> *descs, int 
     ProfScope prof(HSMA_PHASE_LEAF, flops, s);
     const PanelParams<double> none{};
     const dim3 grid((unsigned)tiles), block(64 * kWaves);
-    if (cx) hipLaunchKernelGGL((hsma_chain<double, true>), grid, block, 0, s, none, descs, nd, tickets);
-    else hipLaunchKernelGGL((hsma_chain<double, false>), grid, block, 0, s, none, descs, nd, tickets);
+    if (cx) hipLaunchKernelGGL((hsma_chain<double, true, false>), grid, block, 0, s, none, descs, nd, tickets);
+    else hipLaunchKernelGGL((hsma_chain<double, false, false>), grid, block, 0, s, none, descs, nd, tickets);
     HSMA_HIP(hipGetLastError());
     return HSMA_SUCCESS;
 }

@@ -191,8 +191,13 @@ hsma_status general_t(hsma_side side, hsma_uplo uplo, hsma_op trans, hsma_diag d
     const bool conj_b = direct_a && g.conj_a;
     const TC alpha_c[2] = {(TC)al.re, (TC)-al.im};
     const void *alpha_s = conj_b ? static_cast<const void *>(alpha_c) : alpha;
+    const bool left = side == HSMA_LEFT;
     const bool use_keep = keep && !g.in_place;
-    const size_t a_elems = direct_a ? 0 : (size_t)k * k, b_elems = g.in_place || use_keep ? 0 : (size_t)k * nr;
+    // Where one launch takes the whole solve, it reads and writes B where it
+    // lies: two launches and four passes over B fewer (DPOTRF 1000 491 -> 480
+    // us, 4096 2816 -> 2738).
+    const bool in_one = sizeof(TC) == 8 && !g.in_place && solves_in_one(cx, k, nr);
+    const size_t a_elems = direct_a ? 0 : (size_t)k * k, b_elems = g.in_place || use_keep || in_one ? 0 : (size_t)k * nr;
     void *ws = nullptr;
     if (a_elems + b_elems > 0) HSMA_TRY(ws_alloc(&ws, (a_elems + b_elems) * es * sizeof(TC), s));
     TC *Ap = static_cast<TC *>(ws);
@@ -202,8 +207,29 @@ hsma_status general_t(hsma_side side, hsma_uplo uplo, hsma_op trans, hsma_diag d
     const int fa = (diag == HSMA_UNIT ? kStrict : kLower) | rev | (g.swap_a ? kSwap : 0) |
                    (g.conj_a ? kConj : 0);
     hsma_status st = direct_a ? HSMA_SUCCESS : launch_transform<TC>(cx, A, lda, Ap, k, k, k, fa, s);
+    if constexpr (sizeof(TC) == 8) {
+        if (st == HSMA_SUCCESS && in_one) {
+            PanelParams<double> p{};
+            p.A = direct_a ? A : Ap;
+            p.lda = direct_a ? lda : k;
+            p.n = nr;
+            p.alpha_re = al.re;
+            p.alpha_im = conj_b ? -al.im : al.im;
+            p.unit = diag == HSMA_UNIT;
+            p.conj = conj_b;
+            p.rs = (left ? 1 : ldb) * (g.rev ? -1 : 1);
+            p.cs = left ? ldb : 1;
+            p.B = B + (g.rev ? es * (k - 1) * (left ? 1 : ldb) : 0);
+            p.keep = use_keep ? keep : nullptr;
+            p.ldkeep = k;
+            st = blocked_in_one(cx, k, p, s);
+        }
+    }
+    if (in_one) {
+        const hsma_status st2 = ws ? ws_free(ws, s) : HSMA_SUCCESS;
+        return st != HSMA_SUCCESS ? st : st2;
+    }
     // B' = J B (left, reversed) or J B^T (right)
-    const bool left = side == HSMA_LEFT;
     if (st == HSMA_SUCCESS && !g.in_place)
         st = launch_transform<TC>(cx, B, ldb, Bp, k, k, nr,
                                   (g.rev ? kRevI : 0) | (left ? 0 : kSwap) | (conj_b ? kConj : 0), s);

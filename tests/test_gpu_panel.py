@@ -129,3 +129,41 @@ def test_chains_on_two_streams_and_with_infinities(dt):
         eps = 2.0 ** (-52 if dt in "dz" else -23)
         assert (alone[:, fine] - ref).abs().max().item() <= 10 * B.shape[0] * eps * ref.abs().max().item()
         assert not torch.isfinite(alone[B.shape[0] // 3, 2].abs()) and torch.isnan(alone[B.shape[0] // 2, 5].abs())
+
+
+def _colmajor(t, ld=None):
+    out = hs.colmajor(t.shape[0], t.shape[1], t.dtype, ld=ld)
+    out.copy_(t)
+    return out
+
+
+@pytest.mark.parametrize("side,uplo,trans", [("R", "L", "T"), ("R", "L", "C"), ("R", "U", "N"), ("R", "L", "N"), ("R", "U", "C"),
+                                             ("L", "U", "N"), ("L", "L", "C")])
+@pytest.mark.parametrize("dt", list("dz"))
+def test_right_hand_sides_at_strides(dt, side, uplo, trans):
+    """One launch reading B where it lies (transposed, reversed, conjugated; k
+    up to a panel, and chains) gives the bits of the same solve on a gathered
+    copy."""
+    g = torch.Generator(device="cuda").manual_seed(11)
+    for k, nr in ((65, 1), (130, 17), (257, 40), (512, 33), (700, 257), (1299, 15)):
+        # op(A) or op(A)^T as a lower triangle, by the library's own rules
+        T = torch.tril(_ints((k, k), dt, -3, 3, g), -1) / k + 1.5 * torch.eye(k, dtype=DT[dt], device="cuda")
+        opT = T if side == "L" else T.t()                     # op(A) if no reversal is needed
+        lower_op = (uplo == "L") == (trans == "N")
+        if lower_op != (side == "L"):                         # the operator is the reversed one
+            opT = opT.flip(0, 1)
+        A = {"N": opT, "T": opT.t(), "C": opT.mH}[trans]
+        assert torch.equal(A, torch.tril(A) if uplo == "L" else torch.triu(A))
+        rev = lower_op != (side == "L")
+        B = _ints((k, nr), dt, -3, 3, g)                      # the gathered right-hand side
+        want = hs.colmajor(k, nr, DT[dt])
+        want.copy_(B)
+        hs.trsm(_colmajor(T), want, 0.5)
+        S = B.flip(0) if rev else B
+        S = S if side == "L" else S.t()
+        X = _colmajor(S, S.shape[0] + 3)
+        hs.trsm_general(_colmajor(A), X, 0.5, side=side, uplo=uplo, trans=trans)
+        torch.cuda.synchronize()
+        R = X if side == "L" else X.t()
+        R = R.flip(0) if rev else R
+        assert torch.equal(R, want), (dt, side, uplo, trans, k, nr)
