@@ -18,6 +18,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "dpp_fma.h"
 #include "gemm_core.h"
 
 namespace hsma {
@@ -52,95 +53,50 @@ __device__ __forceinline__ double bcast(double v) {
     return __builtin_amdgcn_mov_dpp(v, 0x150 + N, 0xf, 0xf, false);  // row_newbcast:N
 }
 
-// e -= bcast<R>(l) l and x -= bcast<R>(l) xl.  (A broadcast reads a register two
-// states after it was written at the earliest.)
-template <int R>
-__device__ __forceinline__ void fnma_pair(double &e, double &x, double l, double xl) {
-    asm volatile(
-        "s_nop 1\n"
-        "v_fmac_f64_dpp %0, -%2, %2 row_newbcast:%4 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %1, -%2, %3 row_newbcast:%4 row_mask:0xf bank_mask:0xf\n"
-        : "+v"(e), "+v"(x)
-        : "v"(l), "v"(xl), "n"(R));
+// The square root d of a pivot p and its reciprocal: a third-order step from
+// the hardware's estimate of 1/sqrt(p) (about 2^-23), a correction of d against
+// p, and one of the reciprocal against d; both end within an ulp where nothing
+// on the way over- or underflows.
+__device__ __forceinline__ void root(double p, double &d, double &inv) {
+    double y = __builtin_amdgcn_rsq(p);
+    const double r = __fma_rn(-(p * y), y, 1.0);
+    y = __fma_rn(__fma_rn(r, 0.375, 0.5), r * y, y);
+    const double q = p * y;
+    d = __fma_rn(__fma_rn(-q, q, p), 0.5 * y, q);
+    inv = __fma_rn(__fma_rn(-d, y, 1.0), y, y);
 }
-
-// The square root d of a pivot p and its reciprocal, in dependent stages: a
-// third-order step from the hardware's estimate of 1/sqrt(p) (about 2^-23), a
-// correction of d against p, and one of the reciprocal against d; both end
-// within an ulp where nothing on the way over- or underflows.
-struct Root {
-    double p, y, q, r, t, u, d, inv;
-    static constexpr int kStages = 10;
-    static __device__ __forceinline__ bool in_range(double p) { return p > 0x1p-900 && p < 0x1p900; }
-    template <int S>
-    __device__ __forceinline__ void stage() {
-        if constexpr (S == 0) y = __builtin_amdgcn_rsq(p);
-        if constexpr (S == 1) q = p * y;
-        if constexpr (S == 2) r = __fma_rn(-q, y, 1.0);
-        if constexpr (S == 3) {
-            t = __fma_rn(r, 0.375, 0.5);
-            u = r * y;
-        }
-        if constexpr (S == 4) y = __fma_rn(t, u, y);
-        if constexpr (S == 5) {
-            q = p * y;
-            u = 0.5 * y;
-        }
-        if constexpr (S == 6) r = __fma_rn(-q, q, p);
-        if constexpr (S == 7) d = __fma_rn(r, u, q);
-        if constexpr (S == 8) r = __fma_rn(-d, y, 1.0);
-        if constexpr (S == 9) inv = __fma_rn(r, y, y);
-    }
-};
 
 // The sixteen steps of a block column: each the root of the pivot, the scaled
 // column, and its product off the columns behind it, in the 16 rows of the
-// diagonal block (e, a copy per 16-lane row) and in this lane's own row (x;
-// `diag`: a row of the diagonal block).  The next pivot's column comes first,
-// and the others fill the waits of the next root's stages.  False: a pivot was
-// out of the root's range, and the values are not to be used.
+// diagonal block (e, a copy per 16-lane row, so pivots and columns move by row
+// broadcasts) and in this lane's own row (x; `diag`: a row of the diagonal
+// block).  FAST: by `root`; false comes back if a pivot was outside 2^-900 ..
+// 2^900 (zero, negative, NaN), and the values are not to be used.  Otherwise by
+// the library's root and division, for any pivots.
+template <bool FAST>
 __device__ __forceinline__ bool eliminate(double (&e)[16], double (&x)[16], int lr, bool diag) {
-    Root z;
-    z.p = bcast<0>(e[0]);
-    bool ok = Root::in_range(z.p);
-    static_for<0, Root::kStages>([&](auto S) { z.stage<decltype(S)::value>(); });
+    constexpr unsigned kLow = (1023u - 900u) << 20, kSpan = 1800u << 20;
+    unsigned most = 0;  // over the pivots' high words, from that of 2^-900
     static_for<0, 16>([&](auto K) {
         constexpr int c = decltype(K)::value;
-        const double l = e[c] * z.inv, xl = x[c] * z.inv;
-        x[c] = diag && lr == c ? z.d : xl;
-        if constexpr (c < 15) {
-            fnma_pair<c + 1>(e[c + 1], x[c + 1], l, xl);
-            z.p = bcast<c + 1>(e[c + 1]);
-            ok &= Root::in_range(z.p);
-            constexpr int rest = 14 - c, NS = Root::kStages;
-            static_for<0, NS>([&](auto S) {
-                constexpr int i = decltype(S)::value;
-                __builtin_amdgcn_sched_barrier(0);
-                z.stage<i>();
-                __builtin_amdgcn_sched_barrier(0);
-                static_for<i * rest / NS, (i + 1) * rest / NS>([&](auto T) {
-                    constexpr int k = c + 2 + decltype(T)::value;
-                    fnma_pair<k>(e[k], x[k], l, xl);
-                });
-            });
+        const double p = bcast<c>(e[c]);
+        double d, inv, unused[16];
+        if constexpr (FAST) {
+            const unsigned above = (unsigned)__double2hiint(p) - kLow;
+            most = above > most ? above : most;
+            root(p, d, inv);
+        } else {
+            d = sqrt(p);
+            inv = 1.0 / d;
         }
-    });
-    return ok;
-}
-
-// The same for any pivots (zero, negative, NaN, the ends of the range), with
-// the library's root and division.
-__device__ __forceinline__ void eliminate_any(double (&e)[16], double (&x)[16], int lr, bool diag) {
-    static_for<0, 16>([&](auto K) {
-        constexpr int c = decltype(K)::value;
-        const double d = sqrt(bcast<c>(e[c])), inv = 1.0 / d;
         const double l = e[c] * inv, xl = x[c] * inv;
+        if constexpr (c < 15) {
+            smallk::fnma_rows<false, c + 1>(e, unused, l, 0, l, 0);
+            smallk::fnma_rows<false, c + 1>(x, unused, l, 0, xl, 0);
+        }
         x[c] = diag && lr == c ? d : xl;
-        static_for<c + 1, 16>([&](auto T) {
-            constexpr int k = decltype(T)::value;
-            fnma_pair<k>(e[k], x[k], l, xl);
-        });
     });
+    return most < kSpan;
 }
 
 // One diagonal block of at most 256 rows in the real view (256 real, 128
@@ -155,18 +111,24 @@ __device__ __forceinline__ void eliminate_any(double (&e)[16], double (&x)[16], 
 // Four wavefronts eliminate its sixteen columns, a row per lane and a block row
 // per 16 lanes, each 16 lanes with a copy of the diagonal block's rows, so a
 // pivot, its root and its column reach every row by row broadcasts and the
-// sixteen steps need no barrier.  The factored column goes to memory and to
-// LDS, every wavefront subtracts its blocks' products on the matrix cores (a
-// row of L as it lies is both operands), and column j + 1 goes to LDS.
+// sixteen steps need no barrier.  The factored column goes to LDS (and from
+// there to memory, by the other four while the next column is eliminated), every
+// wavefront subtracts its blocks' products on the matrix cores (a row of L as it
+// lies is both operands), and column j + 1 goes to LDS.
 //
-// What bounds it: the sixteen dependent pivots of a step and two barriers.
+// What bounds it: the sixteen dependent pivots of a step (about 4100 cycles, two
+// thirds of them the two rows' multiply-adds) and the products (64 cycles a
+// block of those left, 4300 on average).  Letting four wavefronts eliminate
+// while the others subtract the step before is slower (70 us against 64): both
+// use the FP64 units.  256 rows: 60 us, 64 rows 10; the 64-row kernel
+// with a barrier, a root and a division per column took 22.
 template <bool CX>
 __global__ __launch_bounds__(64 * kBaseWaves, 2) void hsma_potrf_base(double *__restrict__ A_, int64_t lda, int n) {
     constexpr int ES = CX ? 2 : 1;
     typedef double V2 __attribute__((ext_vector_type(2), aligned(8)));
     typedef typename Mma<double>::Acc Acc;
     __shared__ double col[kBaseRows * 16];   // block column j as it stands
-    __shared__ double fac[kBaseRows * 16];   // ... and factored
+    __shared__ double both[2][kBaseRows * 16];   // ... and factored, j even and odd
     HSMA_GLOBAL double *A = (HSMA_GLOBAL double *)A_;
     const int lane = threadIdx.x & 63, g = lane >> 4, lr = lane & 15;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -193,22 +155,42 @@ __global__ __launch_bounds__(64 * kBaseWaves, 2) void hsma_potrf_base(double *__
         rem += kBaseWaves;
         acc[u] = Acc{0, 0, 0, 0};
         if (bm[u] >= 0) {
+            // (Every block on its way before the first is looked at; places beyond
+            // the matrix or above its diagonal read a value below.)
             const int R = 16 * bi[u] + lr, C0 = 16 * bm[u] + 4 * g;
             if constexpr (CX) {
+                const int r = R / 2 < n ? R / 2 : n - 1;
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    const int r = R / 2, c = C0 / 2 + h;
-                    if (r < n && c <= r) {
-                        V2 z = *reinterpret_cast<const HSMA_GLOBAL V2 *>(A + 2 * (r + c * lda));
-                        if (c == r) z.y = 0;
-                        acc[u][2 * h] = R & 1 ? -z.y : -z.x;
-                        acc[u][2 * h + 1] = R & 1 ? -z.x : z.y;
-                    }
+                    const int c = C0 / 2 + h < r ? C0 / 2 + h : r;
+                    const V2 z = *reinterpret_cast<const HSMA_GLOBAL V2 *>(A + 2 * (r + c * lda));
+                    acc[u][2 * h] = z.x;
+                    acc[u][2 * h + 1] = z.y;
                 }
             } else {
+                const int r = R < n ? R : n - 1;
 #pragma unroll
-                for (int h = 0; h < 4; ++h)
-                    if (R < n && C0 + h <= R) acc[u][h] = -A[R + (C0 + h) * lda];
+                for (int h = 0; h < 4; ++h) acc[u][h] = A[r + (C0 + h < r ? C0 + h : r) * lda];
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kBaseSlots; ++u) {
+        if (bm[u] >= 0) {
+            const int R = 16 * bi[u] + lr, C0 = 16 * bm[u] + 4 * g;
+#pragma unroll
+            for (int h = 0; h < 4; h += ES) {
+                const int C = C0 + h;
+                if constexpr (CX) {
+                    // Component (R ^ C) & 1 of element (R / 2, C / 2), the
+                    // diagonal's second taken as zero.
+                    const double re = acc[u][h], im = C / 2 == R / 2 ? 0.0 : acc[u][h + 1];
+                    acc[u][h] = R & 1 ? -im : -re;
+                    acc[u][h + 1] = R & 1 ? -re : im;
+                    if (R >= mr || C / 2 > R / 2) acc[u][h] = acc[u][h + 1] = 0;
+                } else {
+                    acc[u][h] = R >= mr || C > R ? 0 : -acc[u][h];
+                }
             }
 #pragma unroll
             for (int h = 0; h < 4; ++h)
@@ -220,7 +202,22 @@ __global__ __launch_bounds__(64 * kBaseWaves, 2) void hsma_potrf_base(double *__
         if (bm[u] == 0) put(acc[u], bi[u]);
     __syncthreads();
 
+    // Block column j of the factor to memory, by wavefronts 4..7 while the others
+    // work on the next.
+    auto store = [&](int j) {
+        const int i = 4 * (w - 4) + g, R = 16 * i + lr;
+        if (i < j || R >= mr) return;
+#pragma unroll
+        for (int c = 0; c < 16; c += ES) {
+            const int C = 16 * j + c;
+            const double x = both[j & 1][256 * i + at(c) + lr];
+            // (Complex: component R & 1 of element (R / 2, C / 2).)
+            if (C / ES <= R / ES) A[R + C * lda] = CX && (R & 1) && C / 2 == R / 2 ? 0.0 : x;
+        }
+    };
+
     for (int j = 0; j < nb; ++j) {
+        double *fac = both[j & 1];
         if (w < 4 && 4 * w + 3 >= j && 4 * w < nb) {
             const int i = 4 * w + g;
             const bool in = i >= j && i < nb;
@@ -233,26 +230,16 @@ __global__ __launch_bounds__(64 * kBaseWaves, 2) void hsma_potrf_base(double *__
                 for (int c = 0; c < 16; ++c) x[c] = own[at(c) + lr];
             };
             load();
-            if (!__all(eliminate(e, x, lr, i == j))) {
+            if (__builtin_expect(!__all(eliminate<true>(e, x, lr, i == j)), 0)) {
                 load();
-                eliminate_any(e, x, lr, i == j);
+                eliminate<false>(e, x, lr, i == j);
             }
             if (in) {
 #pragma unroll
                 for (int c = 0; c < 16; ++c) fac[256 * i + at(c) + lr] = x[c];
-                const int R = 16 * i + lr;
-                if (R < mr) {
-#pragma unroll
-                    for (int c = 0; c < 16; c += ES) {
-                        const int C = 16 * j + c;
-                        // (Complex: component R & 1 of element (R / 2, C / 2).)
-                        if (C / ES <= R / ES) {
-                            if constexpr (CX) A[R + C * lda] = (R & 1) && C / 2 == R / 2 ? 0.0 : x[c];
-                            else A[R + C * lda] = x[c];
-                        }
-                    }
-                }
             }
+        } else if (w >= 4 && j > 0) {
+            store(j - 1);
         }
         __syncthreads();
         if (j + 1 == nb) break;
@@ -277,6 +264,7 @@ __global__ __launch_bounds__(64 * kBaseWaves, 2) void hsma_potrf_base(double *__
         }
         __syncthreads();
     }
+    if (w >= 4) store(nb - 1);
 }
 
 hsma_status potrf_base(bool cx, int n, double *A, int64_t lda, hipStream_t s) {
