@@ -164,9 +164,10 @@ struct Solve {
 
     __device__ __forceinline__ explicit Solve(Shared &s) : sh(s) {}
 
-    // Four values of column `col` at rows r..r+3 (0 at or beyond mr).
-    __device__ __forceinline__ Acc load4(int r) const {
+    // Four values of column `col` at rows r..r+3, r = r0 + dr (0 at or beyond mr).
+    __device__ __forceinline__ Acc load4(int r0, int dr) const {
         Acc v = {0, 0, 0, 0};
+        const int r = r0 + dr;
         if constexpr (AT) {
 #pragma unroll
             for (int h = 0; h < 4; h += ES) {
@@ -181,7 +182,7 @@ struct Solve {
                     }
                 }
             }
-        } else if (r + 4 <= mr) {
+        } else if (r0 + 16 <= mr) {
 #pragma unroll
             for (int h = 0; h < 4; h += V) {
                 const VG t = *reinterpret_cast<const HSMA_GLOBAL VG *>(col + r + h);
@@ -275,9 +276,18 @@ struct Solve {
             }
         } else {
             const GT *p = A + (int64_t)(16 * (j - 1) + lr) * lda;
+            if (16 * j + 16 <= mr) {
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
-                if (r + s < mr) f[s] = p[r + s];
+                for (int s = 0; s < 4; s += V) {
+                    const VG t = *reinterpret_cast<const HSMA_GLOBAL VG *>(p + r + s);
+#pragma unroll
+                    for (int e = 0; e < V; ++e) f[s + e] = t[e];
+                }
+            } else {
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    if (r + s < mr) f[s] = p[r + s];
+            }
         }
     }
 
@@ -460,17 +470,18 @@ struct Solve {
         const int rows = mr / ES, c = lane & (N - 1);
         const int d0 = N * inv_block() < rows ? N * inv_block() : 0;  // (a block beyond the panel is not used)
         const int row = d0 + c < rows ? d0 + c : rows - 1;
-        const GT *p = A + (int64_t)ES * row;
+        // Only the strict lower triangle and the diagonal are read.
+        const HSMA_GLOBAL char *p = (const HSMA_GLOBAL char *)(A + (int64_t)ES * (row + d0 * lda));
+        const int64_t step = ES * lda * (int64_t)sizeof(T), last = (row - d0) * step;
 #pragma unroll
         for (int k = 0; k < N; ++k) {
-            // Only the strict lower triangle and the diagonal are read.
-            const int cc = d0 + k < row ? d0 + k : row;
+            const int64_t to = d0 + k < row ? k * step : last;
             if constexpr (CX) {
-                const V2 e = *reinterpret_cast<const HSMA_GLOBAL V2 *>(p + 2 * (int64_t)cc * lda);
+                const V2 e = *reinterpret_cast<const HSMA_GLOBAL V2 *>(p + to);
                 lre[k] = e.x;
                 lim[k] = e.y;
             } else {
-                lre[k] = p[(int64_t)cc * lda];
+                lre[k] = *reinterpret_cast<const GT *>(p + to);
                 lim[k] = 0;
             }
         }
@@ -577,6 +588,12 @@ struct Solve {
             left = p.left;
             mail = p.mail + 256 * (int64_t)p.nblk * tile;
         }
+        // The right-hand side, the diagonal blocks and the blocks before them are
+        // all on their way before the first is waited for.
+        static_for<0, NQ>([&](auto Q) {
+            constexpr int q = decltype(Q)::value;
+            acc[q] = load4(16 * (w + kWaves * q), 4 * g);
+        });
         {
             T lre[N], lim[N], lb[NQ][4];
             load_diag(lre, lim);
@@ -602,10 +619,6 @@ struct Solve {
             });
         }
         __builtin_amdgcn_sched_barrier(0);
-        static_for<0, NQ>([&](auto Q) {
-            constexpr int q = decltype(Q)::value;
-            acc[q] = load4(16 * (w + kWaves * q) + 4 * g);
-        });
         if (p.alpha_re != 1 || p.alpha_im != 0) {
             static_for<0, NQ>([&](auto Q) {
                 Acc &v = acc[decltype(Q)::value];
