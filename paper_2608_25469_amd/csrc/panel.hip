@@ -329,7 +329,8 @@ struct Solve {
     // the one before it.  L is loaded four blocks ahead.
     __device__ __forceinline__ void apply_left() {
         const int groups = left / 2;  // a multiple of 8: panels have 16 blocks
-        T l[4][NQ][4], nx[4];
+        T l[4][NQ][4], nx[4], again = 0;
+        bool behind = false;  // the last group had to be waited for
         const T *src = mail + 256 * (w >> 2) + 64 * (w & 3) + lane;
         static_for<0, 4>([&](auto K) {
             constexpr int k = decltype(K)::value;
@@ -340,8 +341,12 @@ struct Solve {
             static_for<0, 4>([&](auto H) {
                 constexpr int h = decltype(H)::value;
                 const int t = t4 + h;
+                const bool late = __any(is_empty(nx[h]));
+                if (late && behind) nx[h] = again;
                 for (int polls = 0; __any(is_empty(nx[h])) && polls < kMaxPolls; ++polls)
                     nx[h] = mail_load(src + 512 * (int64_t)t);
+                behind = late;
+                if (late && t + 1 < groups) again = mail_load(src + 512 * (int64_t)(t + 1));
                 T *buf = sh.left[h & 1];
                 buf[256 * (w >> 2) + 64 * (w & 3) + lane] = nx[h];
                 constexpr int s2 = (h + 2) % 4;
