@@ -187,7 +187,8 @@ def measured_traffic(name, sources, ok=True):
     return rec.get("hbm_bytes_per_launch")
 
 
-GEMM_SOURCES = ["paper_2608_25469_amd/csrc/gemm.hip"]
+GEMM_SOURCES = ["paper_2608_25469_amd/csrc/gemm_core.h", "paper_2608_25469_amd/csrc/gemm.hip",
+                "paper_2608_25469_amd/csrc/tile_choice.h"]
 SMALL_SOURCES = ["paper_2608_25469_amd/csrc/small_kernels.h", "paper_2608_25469_amd/csrc/dpp_fma.h",
                  "paper_2608_25469_amd/csrc/strip.hip", "paper_2608_25469_amd/csrc/batched.cpp",
                  "paper_2608_25469_amd/csrc/strip_pack.h"]

@@ -1,11 +1,13 @@
 """Offline block-size tuner for the blocked path (paper Sec. 4.3.2).
 
 Pre-build phase of the paper's adaptive blocking: for every (data type, m, n)
-scale point, time the blocked solve with each candidate diagonal-block edge
-I_B and keep the fastest.  The results go to a JSON file (written after every
+scale point, time the blocked solve with each candidate I_B (the rows of a
+panel) and keep the fastest.  The results go to a JSON file (written after every
 measurement, so an interrupted sweep resumes) and are turned into the
 compiled-in table ``csrc/tuning_gfx950.h``; at run time the library picks the
-entry of the nearest tested scale (``hsma_lookup_block_size``).
+entry of the nearest tested scale (``hsma_lookup_block_size``).  A solve that
+is given no block size reports that entry and sizes its footprint by it; its
+panels are as tall as the kernel takes.
 
   python -m paper_2608_25469_amd.autotune sweep  --out results.json   (GPU)
   python -m paper_2608_25469_amd.autotune header --json results.json  (CPU)

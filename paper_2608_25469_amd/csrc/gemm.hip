@@ -1,10 +1,10 @@
 // FP64 and mixed-precision matrix-core products of the blocked path (the
-// kernel is gemm_core.h): tile shapes per role, single, batched and grouped
-// launches.
+// kernel is gemm_core.h): tile shapes per role, single and grouped launches.
 //
-// Paper, Sec. 4.3: after the diagonal blocks are inverted, the large solve is
-// a sequence of matrix products: the trailing update B_r <- B_r - A_{r,:} X
-// and the diagonal solve X_r = inv(D_r) B_r.
+// Paper, Sec. 4.3: the large solve is a sequence of matrix products, the
+// trailing updates B_r <- B_r - A_{r,:} X between the panel solves (panel.hip);
+// Cholesky's lower-triangular update and the residual of refinement run on
+// the same kernel.
 
 #include <algorithm>
 

@@ -10,7 +10,7 @@
 //
 // One workgroup of eight wavefronts solves 16 columns.  The rows are cut into
 // 16-row blocks, dealt to the wavefronts in turn (wavefront w holds blocks w,
-// w + 8, ...), each block of the right-hand side one 16 x 16 accumulator.
+// w + 8, ...), each block's products one 16 x 16 accumulator.
 // Step i: X_i is in LDS; every wavefront adds L_ji (-X_i) to its blocks j > i +
 // 1 (the owner of block i + 2 then multiplies that block by its inverse: y),
 // while the owner of block i + 1 forms X_{i+1} = y - P X_i with P =
@@ -138,6 +138,7 @@ struct Solve {
         // P_j in the same order, both read by the owner of block j alone, then
         // -X_j (element v of lane l at 64 v + l).
         T blk[NB][256];
+        T diag[NB][16];    // reciprocals of L_jj's diagonal (complex: (re, im) of the 8 elements)
         T left[CHAIN ? 2 : 1][CHAIN ? 2 * 256 : 1];  // two blocks of -X from before the panel
         int ticket;
         int done;          // blocks of X in blk
@@ -154,13 +155,17 @@ struct Solve {
     bool conj;
     GT *keep;          // AT: this lane's column of the copy of X
     Shared &sh;
-    Acc acc[NQ];
+    Acc acc[NQ];       // L X of the blocks solved so far, negated, from zero
+    Acc rhs;           // the right-hand side of this wavefront's next block, before alpha
+    T are, aim;        // alpha
+    bool scaled;
     T a[D][NQ][4];     // L_ji of steps i, i + 1, ..: slot i % D
     T *mail;           // CHAIN: this strip's blocks of -X, from block 0 of the solve
     int left;          // blocks before the panel
-    T fi[NQ][4];       // inv(L_jj), as A fragments
+    T fi[NQ][4];       // inv(L_jj) without its diagonal, as A fragments
     T fp[NQ][4];       // P_j = inv(L_jj) L_{j,j-1}, as A fragments
-    Acc y;             // inv(L_jj) times the block, then X_j
+    Acc y;             // the sums of inv(L_jj) beside its diagonal, and of P; then X_j
+    Acc main;          // the diagonal's part
 
     __device__ __forceinline__ explicit Solve(Shared &s) : sh(s) {}
 
@@ -376,24 +381,56 @@ struct Solve {
         for (int v = 0; v < 4; ++v) mail_store(dst + 64 * v, -x[v]);
     }
 
-    // y = inv(L_JJ) acc (by the owner of block J, X_0 .. X_{J-2} applied).
+    // y + main = inv(L_JJ) (alpha B_J + acc) (by the owner of block J, X_0 ..
+    // X_{J-2} applied).  The products meet the right-hand side here and not at
+    // their start, and the diagonal's part stays apart from the sums: added to
+    // them one by one, each of the small terms would be rounded at its size.
     template <int J>
     __device__ __forceinline__ void prepare() {
         constexpr int q = J / kWaves;
+        Acc b = rhs;
+        if (scaled) {
+            if constexpr (CX) {
+#pragma unroll
+                for (int h = 0; h < 4; h += 2) {
+                    b[h] = fma_rn(are, rhs[h], -mul_rn(aim, rhs[h + 1]));
+                    b[h + 1] = fma_rn(are, rhs[h + 1], mul_rn(aim, rhs[h]));
+                }
+            } else {
+#pragma unroll
+                for (int h = 0; h < 4; ++h) b[h] = mul_rn(are, rhs[h]);
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < 4; ++h) b[h] += acc[q][h];
         if (16 * J + 16 > mr) {  // rows beyond the panel hold no numbers
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                if (16 * J + 4 * g + v >= mr) acc[q][v] = 0;
+                if (16 * J + 4 * g + v >= mr) b[v] = 0;
         }
         y = Acc{0, 0, 0, 0};
 #pragma unroll
-        for (int s = 0; s < 4; ++s) y = Mma<T>::mma(fi[q][s], acc[q][s], y);
+        for (int s = 0; s < 4; ++s) y = Mma<T>::mma(fi[q][s], b[s], y);
+        const T *d = sh.diag[J] + 4 * g;
+        if constexpr (CX) {
+#pragma unroll
+            for (int h = 0; h < 4; h += 2) {
+                main[h] = fma_rn(b[h], d[h], -mul_rn(b[h + 1], d[h + 1]));
+                main[h + 1] = fma_rn(b[h], d[h + 1], mul_rn(b[h + 1], d[h]));
+            }
+        } else {
+#pragma unroll
+            for (int h = 0; h < 4; ++h) main[h] = mul_rn(d[h], b[h]);
+        }
+        if constexpr (q + 1 < NQ) rhs = load4(16 * (w + kWaves * (q + 1)), 4 * g);
     }
 
-    // X_J = y to the other wavefronts (by its owner): LDS takes a wavefront's
+    // X_J to the other wavefronts (by its owner): LDS takes a wavefront's
     // writes in order.
     template <int J>
     __device__ __forceinline__ void publish() {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) y[v] += main[v];
 #pragma unroll
         for (int v = 0; v < 4; ++v) sh.blk[J][64 * v + lane] = -y[v];
         asm volatile("" ::: "memory");
@@ -513,6 +550,10 @@ struct Solve {
                 dr = div_rn((T)1, er);
             }
         }
+        if (g < NQ && !(CX && (lane & 8))) {
+            sh.diag[j][ES * c] = dr;
+            if constexpr (CX) sh.diag[j][2 * c + 1] = di;
+        }
         T yr[N], yi[N];
 #pragma unroll
         for (int k = 0; k < N; ++k) {
@@ -595,10 +636,11 @@ struct Solve {
         }
         // The right-hand side, the diagonal blocks and the blocks before them are
         // all on their way before the first is waited for.
-        static_for<0, NQ>([&](auto Q) {
-            constexpr int q = decltype(Q)::value;
-            acc[q] = load4(16 * (w + kWaves * q), 4 * g);
-        });
+        rhs = load4(16 * w, 4 * g);
+        are = p.alpha_re;
+        aim = p.alpha_im;
+        scaled = are != 1 || aim != 0;
+        static_for<0, NQ>([&](auto Q) { acc[decltype(Q)::value] = Acc{0, 0, 0, 0}; });
         {
             T lre[N], lim[N], lb[NQ][4];
             load_diag(lre, lim);
@@ -621,25 +663,12 @@ struct Solve {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) sh.blk[j][16 * lr + ((4 * g + v) ^ lr)] = t[v];
                 read_a(sh.blk[j], fp[q]);
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    if (arow / ES == (4 * g + s) / ES) fi[q][s] = 0;
             });
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (p.alpha_re != 1 || p.alpha_im != 0) {
-            static_for<0, NQ>([&](auto Q) {
-                Acc &v = acc[decltype(Q)::value];
-                if constexpr (CX) {
-#pragma unroll
-                    for (int h = 0; h < 4; h += 2) {
-                        const T re = v[h], im = v[h + 1];
-                        v[h] = fma_rn(p.alpha_re, re, -mul_rn(p.alpha_im, im));
-                        v[h + 1] = fma_rn(p.alpha_re, im, mul_rn(p.alpha_im, re));
-                    }
-                } else {
-#pragma unroll
-                    for (int h = 0; h < 4; ++h) v[h] = mul_rn(p.alpha_re, v[h]);
-                }
-            });
-        }
         // (A panel of one block has nothing below it: its L may end before
         // column 15.)
         if (nb > 1) {

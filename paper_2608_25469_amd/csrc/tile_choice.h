@@ -1,8 +1,8 @@
 // Tile shapes of the FP64 product (host code, no HIP dependency).
 //
-// A workgroup stages its A and B tiles through a two-stage LDS ring of
-// BK-deep slices; the ring's size sets how many workgroups a CU holds (160 KB
-// of LDS, at most three).  For a lower-triangular C only the tiles on or
+// A workgroup stages its A and B tiles through an LDS ring of two slices; the
+// ring's size sets how many workgroups a CU holds (160 KB of LDS, at most
+// three; lower_tile_shape counts 16-deep slices).  For a lower-triangular C only the tiles on or
 // below the diagonal run, and each runs the whole K, so a launch takes about
 // ceil(non-empty tiles / resident slots) rounds of one tile's time;
 // lower_tile_shape picks the shape with the fewest rounds times tile area,
