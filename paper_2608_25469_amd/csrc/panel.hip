@@ -134,10 +134,10 @@ struct Solve {
     typedef T V2 __attribute__((ext_vector_type(2), aligned(sizeof(T))));
 
     struct Shared {
-        // Block j: first its inverse (element (r, k) at 16 k + (r ^ k)), then
-        // P_j in the same order, both read by the owner of block j alone, then
-        // -X_j (element v of lane l at 64 v + l).
+        // Block j: P_j (element (r, k) at 16 k + (r ^ k)), then -X_j (element v of
+        // lane l at 64 v + l).
         T blk[NB][256];
+        T inv[NB][256];    // inv(L_jj), laid out as P_j; both are read by j's owner alone
         T diag[NB][16];    // reciprocals of L_jj's diagonal (complex: (re, im) of the 8 elements)
         T left[CHAIN ? 2 : 1][CHAIN ? 2 * 256 : 1];  // two blocks of -X from before the panel
         int ticket;
@@ -156,14 +156,16 @@ struct Solve {
     GT *keep;          // AT: this lane's column of the copy of X
     Shared &sh;
     Acc acc[NQ];       // L X of the blocks solved so far, negated, from zero
-    Acc rhs;           // the right-hand side of this wavefront's next block, before alpha
+    Acc rhs[NQ > 1 ? 2 : 1];  // the right-hand side of blocks w + 8 q, before alpha: place q % 2
     T are, aim;        // alpha
     bool scaled;
     T a[D][NQ][4];     // L_ji of steps i, i + 1, ..: slot i % D
     T *mail;           // CHAIN: this strip's blocks of -X, from block 0 of the solve
     int left;          // blocks before the panel
-    T fi[NQ][4];       // inv(L_jj) without its diagonal, as A fragments
-    T fp[NQ][4];       // P_j = inv(L_jj) L_{j,j-1}, as A fragments
+    // Of this wavefront's next block, read from LDS a step before their use (a
+    // set for each of its blocks does not fit beside them):
+    T fi[4];           // inv(L_jj) without its diagonal, as A fragments
+    T fp[4];           // P_j = inv(L_jj) L_{j,j-1}, as A fragments
     Acc y;             // the sums of inv(L_jj) beside its diagonal, and of P; then X_j
     Acc main;          // the diagonal's part
 
@@ -302,6 +304,13 @@ struct Solve {
         for (int s = 0; s < 4; ++s) f[s] = blk[16 * (4 * g + s) + (arow ^ (4 * g + s))];
     }
 
+    __device__ __forceinline__ void read_inverse(int j) {
+        read_a(sh.inv[j], fi);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            if (arow / ES == (4 * g + s) / ES) fi[s] = 0;
+    }
+
     // acc_q += L_ji (-X_i).
     template <int I, int Q>
     __device__ __forceinline__ void update(const T (&xb)[4]) {
@@ -388,17 +397,18 @@ struct Solve {
     template <int J>
     __device__ __forceinline__ void prepare() {
         constexpr int q = J / kWaves;
-        Acc b = rhs;
+        const Acc r = rhs[q % 2];
+        Acc b = r;
         if (scaled) {
             if constexpr (CX) {
 #pragma unroll
                 for (int h = 0; h < 4; h += 2) {
-                    b[h] = fma_rn(are, rhs[h], -mul_rn(aim, rhs[h + 1]));
-                    b[h + 1] = fma_rn(are, rhs[h + 1], mul_rn(aim, rhs[h]));
+                    b[h] = fma_rn(are, r[h], -mul_rn(aim, r[h + 1]));
+                    b[h + 1] = fma_rn(are, r[h + 1], mul_rn(aim, r[h]));
                 }
             } else {
 #pragma unroll
-                for (int h = 0; h < 4; ++h) b[h] = mul_rn(are, rhs[h]);
+                for (int h = 0; h < 4; ++h) b[h] = mul_rn(are, r[h]);
             }
         }
 #pragma unroll
@@ -410,7 +420,7 @@ struct Solve {
         }
         y = Acc{0, 0, 0, 0};
 #pragma unroll
-        for (int s = 0; s < 4; ++s) y = Mma<T>::mma(fi[q][s], b[s], y);
+        for (int s = 0; s < 4; ++s) y = Mma<T>::mma(fi[s], b[s], y);
         const T *d = sh.diag[J] + 4 * g;
         if constexpr (CX) {
 #pragma unroll
@@ -422,7 +432,6 @@ struct Solve {
 #pragma unroll
             for (int h = 0; h < 4; ++h) main[h] = mul_rn(d[h], b[h]);
         }
-        if constexpr (q + 1 < NQ) rhs = load4(16 * (w + kWaves * (q + 1)), 4 * g);
     }
 
     // X_J to the other wavefronts (by its owner): LDS takes a wavefront's
@@ -450,6 +459,8 @@ struct Solve {
                 constexpr int W1 = (I + 1) % kWaves, Q1 = (I + 1) / kWaves;
                 constexpr int W2 = (I + 2) % kWaves, Q2 = (I + 2) / kWaves;
                 const bool chain = w == W1;
+                if constexpr (I + 2 < NB)
+                    if (w == W2) read_inverse(I + 2);
                 if (chain) __builtin_amdgcn_s_setprio(3);
                 await_block(I);
                 T xb[4];
@@ -458,7 +469,7 @@ struct Solve {
                 Acc mine = y;  // X_I at its owner
                 if (chain) {
 #pragma unroll
-                    for (int s = 0; s < 4; ++s) y = Mma<T>::mma(fp[Q1][s], xb[s], y);
+                    for (int s = 0; s < 4; ++s) y = Mma<T>::mma(fp[s], xb[s], y);
                     publish<I + 1>();
                     __builtin_amdgcn_s_setprio(0);
                 }
@@ -469,6 +480,7 @@ struct Solve {
                         __builtin_amdgcn_s_setprio(2);
                         update<I, Q2>(xb);
                         if (I + 2 < nb) prepare<I + 2>();
+                        read_a(sh.blk[I + 2], fp);
                         __builtin_amdgcn_s_setprio(0);
                     } else {
                         if constexpr (I > 0) {
@@ -489,6 +501,11 @@ struct Solve {
                     store4(16 * I + 4 * g, mine);
                 }
                 if constexpr (I + D + 1 < NB) load_l<I + D - 1>();
+                // The next row of blocks, six steps before the first of them is
+                // readied; all wavefronts at once, so that the counts of loads
+                // on their way agree and none waits for more than it needs.
+                if constexpr (I % kWaves == 0 && I / kWaves + 1 < NQ)
+                    rhs[(I / kWaves + 1) % 2] = load4(16 * (w + I + kWaves), 4 * g);
                 step<I + 1>();
             }
         }
@@ -590,7 +607,7 @@ struct Solve {
             });
         });
         if (g >= NQ || (CX && (lane & 8))) return;
-        T *dst = sh.blk[j];
+        T *dst = sh.inv[j];
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             if constexpr (CX) {
@@ -636,7 +653,7 @@ struct Solve {
         }
         // The right-hand side, the diagonal blocks and the blocks before them are
         // all on their way before the first is waited for.
-        rhs = load4(16 * w, 4 * g);
+        rhs[0] = load4(16 * w, 4 * g);
         are = p.alpha_re;
         aim = p.alpha_im;
         scaled = are != 1 || aim != 0;
@@ -655,17 +672,14 @@ struct Solve {
             static_for<0, NQ>([&](auto Q) {
                 constexpr int q = decltype(Q)::value;
                 const int j = w + kWaves * q;
-                read_a(sh.blk[j], fi[q]);
+                T f[4];
+                read_a(sh.inv[j], f);
                 Acc t = {0, 0, 0, 0};
 #pragma unroll
-                for (int s = 0; s < 4; ++s) t = Mma<T>::mma(fi[q][s], lb[q][s], t);
+                for (int s = 0; s < 4; ++s) t = Mma<T>::mma(f[s], lb[q][s], t);
                 // Row 4g + v, column lr, to the A fragments' order through LDS.
 #pragma unroll
                 for (int v = 0; v < 4; ++v) sh.blk[j][16 * lr + ((4 * g + v) ^ lr)] = t[v];
-                read_a(sh.blk[j], fp[q]);
-#pragma unroll
-                for (int s = 0; s < 4; ++s)
-                    if (arow / ES == (4 * g + s) / ES) fi[q][s] = 0;
             });
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -680,10 +694,13 @@ struct Solve {
             if (left > 0) apply_left();
         }
         if (w == 0) {
+            read_inverse(0);
             prepare<0>();
             publish<0>();
         } else if (w == 1 && nb > 1) {
+            read_inverse(1);
             prepare<1>();
+            read_a(sh.blk[1], fp);
         }
         step<0>();
         drain();
