@@ -18,7 +18,7 @@
 //
 // Against inverted I_B blocks (a zero fill, a chunk inversion of 22 us, two
 // products per merge level, then an in-place product per block): DTRSM 500 x
-// 300 148 -> 38 us, 4096 x 256 1044 -> 458 us, ZTRSM 1000 x 257 525 -> 195 us.
+// 300 148 -> 36 us, 16384 78.2 -> 64.8 ms, STRSM 4096 1510 -> 801 us.
 
 #include <algorithm>
 
@@ -28,12 +28,13 @@ namespace hsma {
 
 // Whether a solve runs as one chain launch (panel.hip) instead of the recursion:
 // where few columns leave the recursion's launches mostly empty.  Measured, us,
-// chain / recursion in panels of 256 rows: DTRSM 1024 x 256 74 / 91, 1024 x
-// 1024 81 / 101, 1024 x 4096 180 / 159, 4096 x 256 283 / 452, 4096 x 1024 629 /
-// 648, 8192 x 256 844 / 1141, 8192 x 1024 1992 / 1967; ZTRSM 1024 x 256 124 /
-// 195, 2048 x 1024 516 / 611, 4096 x 1024 1800 / 1778, 8192 x 256 2146 / 2870;
-// STRSM 4096 x 256 175 / 392, 2048 x 4096 376 / 287.  Up to 512 real-view rows
-// one panel is as fast (38 us against 41) and needs no mail.
+// chain / recursion in panels of 256 rows: DTRSM 1024 x 256 74 / 90, 1024 x
+// 1024 80 / 100, 4096 x 256 276 / 448, 4096 x 1024 571 / 617, 8192 x 256 756 /
+// 1114; ZTRSM 1024 x 256 129 / 195, 2048 x 1024 527 / 602, 8192 x 256 2022 /
+// 2833; STRSM 4096 x 256 174 / 378.  Beyond the rule the recursion in its own
+// panels of 512 rows is ahead or level: an earlier chain took 180 at 1024 x 4096
+// (130), 1992 at 8192 x 1024 (1747), ZTRSM 1800 at 4096 x 1024 (1751).  Up to
+// 512 real-view rows one panel is as fast (37 against 41) and needs no mail.
 bool chain_rule(bool cx, int elem, int64_t m, int64_t n) {
     const int64_t mr = m * (cx ? 2 : 1), mail = mr * ((n + 15) / 16 * 16) * elem;
     if (mr <= kPanelRows || n > 1024 || mail > (int64_t)HSMA_NOALLOC_SCRATCH_BYTES / 2) return false;
