@@ -182,6 +182,24 @@ hsma_status blocked_in_one(bool cx, int64_t m, PanelParams<double> p, hipStream_
     return st != HSMA_SUCCESS ? st : st2;
 }
 
+// B <- inv(L) B by one panel or chain whose wavefronts look at most `looks` + 1
+// times (looks >= 1) at what they wait for.  Not in the public header: this is how
+// the end of a wait that gives up is tested.
+extern "C" hsma_status hsma_internal_short_waits(int cx, int64_t m, int64_t n, const double *A, int64_t lda,
+                                                 double *B, int64_t ldb, int looks, hsma_stream_t stream) {
+    if (!solves_in_one(cx, m, n) || looks < 1) return HSMA_NOT_SUPPORTED;
+    PanelParams<double> p{};
+    p.A = A;
+    p.lda = lda;
+    p.B = B;
+    p.n = n;
+    p.alpha_re = 1;
+    p.rs = 1;
+    p.cs = ldb;
+    p.looks = looks;
+    return blocked_in_one(cx, m, p, static_cast<hipStream_t>(stream));
+}
+
 // R <- R - tril(L) X, the residual of refinement and of the backward-error
 // report (FP64 products).  One product over the whole triangle: each row
 // tile accumulates its full row of L times X in one FP64 accumulator chain

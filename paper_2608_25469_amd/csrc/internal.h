@@ -175,6 +175,7 @@ hsma_status launch_gemm(bool cplx_, GemmRole role, int M, int N, int K, cplx alp
 // One panel solve (panel.hip): X = alpha inv(L) B in place for `rows` rows, L
 // at A, unit or not; at most kPanelRows real-view rows.
 constexpr int kPanelRows = 512;
+constexpr int kMaxLooks = 1 << 20;
 template <typename T>
 struct PanelParams {
     const T *A;
@@ -196,6 +197,7 @@ struct PanelParams {
     int64_t rs, cs;
     T *keep;
     int64_t ldkeep;
+    int looks = kMaxLooks;  // of a wavefront at what it waits for, before it takes NaN instead
 };
 template <typename T>
 hsma_status launch_panel(bool cx, const PanelParams<T> &p, hipStream_t s);

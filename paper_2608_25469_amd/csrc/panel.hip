@@ -118,9 +118,10 @@ __global__ __launch_bounds__(256) void hsma_mail_empty(T *mail, int64_t n, unsig
     if (blockIdx.x == 0 && threadIdx.x == 0) *tickets = 0;
 }
 
-// Looks at a place before a wavefront goes on without it (about a second): every
-// wait ends, whatever went wrong elsewhere.
-constexpr int kMaxPolls = 1 << 20;
+// Every wait ends, whatever went wrong elsewhere: after PanelParams::looks looks a
+// wavefront goes on, every X that it forms is NaN, and it looks once and no more at
+// whatever it needs later.  2^20 looks are 1.7 s at the mail (1.6 us each) and
+// about 50 ms in LDS (some 100 cycles); what they wait for takes microseconds.
 
 // NQ: blocks per wavefront (rows <= 128 NQ in the real view).  CHAIN: the panel
 // is one of a chain.  AT: the right-hand side lies at strides.
@@ -164,6 +165,7 @@ struct Solve {
     T a[D][NQ][4];     // L_ji of steps i, i + 1, ..: slot i % D
     T *mail;           // CHAIN: this strip's blocks of -X, from block 0 of the solve
     int left;          // blocks before the panel
+    int looks;         // of a wait; 0: one has given up
     // Of this wavefront's next block, read from LDS a step before their use (a
     // set for each of its blocks does not fit beside them):
     T fi[4];           // inv(L_jj) without its diagonal, as A fragments
@@ -359,8 +361,9 @@ struct Solve {
                 const int t = t4 + h;
                 const bool late = __any(is_empty(nx[h]));
                 if (late && behind) nx[h] = again;
-                for (int polls = 0; __any(is_empty(nx[h])) && polls < kMaxPolls; ++polls)
-                    nx[h] = mail_load(src + 512 * (int64_t)t);
+                int polls = 0;
+                for (; __any(is_empty(nx[h])) && polls < looks; ++polls) nx[h] = mail_load(src + 512 * (int64_t)t);
+                if (polls == looks) looks = 0;
                 behind = late;
                 if (late && t + 1 < groups) again = mail_load(src + 512 * (int64_t)(t + 1));
                 T *buf = sh.left[h & 1];
@@ -442,14 +445,28 @@ struct Solve {
     __device__ __forceinline__ void publish() {
 #pragma unroll
         for (int v = 0; v < 4; ++v) y[v] += main[v];
+        if (__builtin_expect(looks == 0, 0)) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                y[v] = (T)__builtin_nan("");
+                asm volatile("" : "+v"(y[v]));  // (a branch, not a selection on the chain)
+            }
+        }
 #pragma unroll
         for (int v = 0; v < 4; ++v) sh.blk[J][64 * v + lane] = -y[v];
         asm volatile("" ::: "memory");
         __hip_atomic_store(&sh.done, J + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
-    __device__ __forceinline__ void await_block(int i) const {
-        for (int polls = 0; polls < kMaxPolls; ++polls)
-            if (__hip_atomic_load(&sh.done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > i) break;
+    // X_i is in its place, or this wavefront's further X are NaN (publish).
+    __device__ __forceinline__ void await_block(int i) {
+        int polls = looks;
+        while (__builtin_amdgcn_readfirstlane(
+                   __hip_atomic_load(&sh.done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) <= i) {
+            if (--polls < 0) {
+                looks = 0;
+                break;
+            }
+        }
         asm volatile("" ::: "memory");
     }
 
@@ -659,6 +676,7 @@ struct Solve {
         are = p.alpha_re;
         aim = p.alpha_im;
         scaled = are != 1 || aim != 0;
+        looks = __builtin_amdgcn_readfirstlane(p.looks);
         static_for<0, NQ>([&](auto Q) { acc[decltype(Q)::value] = Acc{0, 0, 0, 0}; });
         {
             T lre[N], lim[N], lb[NQ][4];

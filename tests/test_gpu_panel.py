@@ -167,3 +167,27 @@ def test_right_hand_sides_at_strides(dt, side, uplo, trans):
         R = X if side == "L" else X.t()
         R = R.flip(0) if rev else R
         assert torch.equal(R, want), (dt, side, uplo, trans, k, nr)
+
+
+@pytest.mark.parametrize("cx", [False, True], ids=["real", "complex"])
+@pytest.mark.parametrize("m,n", [(500, 33), (1300, 40)])
+def test_waits_that_give_up_leave_nan(cx, m, n):
+    """A wavefront that gives up its wait (here after two looks) forms NaN
+    from then on: whatever then is not NaN is what a whole solve gives."""
+    import ctypes
+    m //= 2 if cx else 1
+    L, B = W.problem(7, m, n, cx)
+    Ld, Bd, want = hs.to_colmajor(L), hs.to_colmajor(B), hs.to_colmajor(B)
+    hs.trsm(Ld, want)
+    f = hs.lib().hsma_internal_short_waits
+    i64, vp = ctypes.c_int64, ctypes.c_void_p
+    f.argtypes = [ctypes.c_int, i64, i64, vp, i64, vp, i64, ctypes.c_int, vp]
+    for looks, gives_up in ((1, True), (1 << 20, False)):
+        X = Bd.clone()
+        assert X.stride() == Bd.stride()
+        assert f(cx, m, n, Ld.data_ptr(), m, X.data_ptr(), m, looks, torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        a, b = (torch.view_as_real(t) if cx else t for t in (X, want))
+        there = ~torch.isnan(a)
+        assert torch.equal(a[there], b[there]), (m, n, cx, looks)
+        assert bool(there.all()) != gives_up, (m, n, cx, looks)
