@@ -429,9 +429,10 @@ hsma_status hsma_generate_inputs(hsma_dtype dtype, int64_t m, int64_t n, uint64_
  *     its own completion event: the small class on the queue's small stream,
  *     the four blocked classes round-robin over the queue's other streams.  Synthetic
  *     inputs of a class are drawn in one launch on the class's stream first.
- * A request's footprint is a share for its descriptors and scheduling (4 KiB
- * for small requests, ceil(m/I_B) I_B^2 + (ceil(m/2) + I_B) I_B elements for
- * larger ones) plus, for synthetic requests, its L and B.
+ * A request's footprint is the device memory its solve takes (a share of 4 KiB
+ * and, for m > 64, its descriptors and the workspace of a chained launch, which
+ * is B's size with rows and columns rounded up to 16) plus, for synthetic
+ * requests, its L and B.
  */
 typedef enum { HSMA_BACKEND_HIP = 0, HSMA_BACKEND_SIMULATED = 1 } hsma_backend;
 typedef enum { HSMA_INPUT_DEVICE = 0, HSMA_INPUT_SYNTHETIC = 1 } hsma_input_kind;

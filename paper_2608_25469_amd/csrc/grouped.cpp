@@ -154,7 +154,20 @@ GemmParams op_update(const Prob &p, const Op &o) {
                 o.touched ? cplx{1.0, 0.0} : p.alpha, p.B + es * o.r1, es * p.ldb);
 }
 
+// A launch's descriptors start at a multiple of 256 bytes.
+size_t padded(size_t bytes) { return (bytes + 255) / 256 * 256; }
+
 }  // namespace
+
+// What one problem (m > 64) adds at most to the device memory of a grouped
+// call: its mail, and its descriptors as if no launch took another's.
+size_t grouped_bytes(bool cx, int64_t m, int64_t n) {
+    const int64_t mr = m * (cx ? 2 : 1);
+    if (chain_rule(cx, sizeof(double), m, n))
+        return chain_bytes<double>(cx, m, n) + 512 + padded((mr + kChainRows - 1) / kChainRows * sizeof(PanelParams<double>));
+    const size_t panels = (mr + kPanelRows - 1) / kPanelRows;
+    return panels * padded(sizeof(PanelParams<double>)) + (panels - 1) * padded(sizeof(GemmParams)) + 512;
+}
 
 // Enqueue every problem (validated; m > 64; alpha != 0) on stream s.
 hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_t s) {
@@ -201,7 +214,7 @@ hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_
         if (l.tiles > 0x7fffffff) return HSMA_INVALID_SIZE;
         l.cx = cxi;
         l.img_off = img_bytes;
-        img_bytes += (l.panels.size() * sizeof(PanelParams<double>) + 255) / 256 * 256;
+        img_bytes += padded(l.panels.size() * sizeof(PanelParams<double>));
         launches.push_back(std::move(l));
     }
     for (size_t k = 0; k < steps; ++k) {
@@ -241,8 +254,7 @@ hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_
             }
             if (l.tiles > 0x7fffffff) return HSMA_INVALID_SIZE;
             l.img_off = img_bytes;
-            img_bytes += l.panels.size() * sizeof(PanelParams<double>) + l.gemms.size() * sizeof(GemmParams);
-            img_bytes = (img_bytes + 255) / 256 * 256;
+            img_bytes += padded(l.panels.size() * sizeof(PanelParams<double>) + l.gemms.size() * sizeof(GemmParams));
             launches.push_back(std::move(l));
         }
     }
@@ -253,7 +265,6 @@ hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_
         else std::memcpy(img.data() + l.img_off, l.gemms.data(), l.gemms.size() * sizeof(GemmParams));
     }
     void *dev = nullptr;
-    img_bytes = (img_bytes + 255) / 256 * 256;
     HSMA_TRY(ws_alloc(&dev, img_bytes + (mail_words[0] + mail_words[1]) * sizeof(double) + 512, s));
     unsigned char *base = static_cast<unsigned char *>(dev);
     // Mail of the real chains, then of the complex ones, 256 bytes after each.

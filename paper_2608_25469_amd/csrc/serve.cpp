@@ -37,8 +37,7 @@
 
 namespace hsma {
 
-size_t blocked_workspace_bytes(bool cx, int64_t m, int ib);
-int lookup_block_size(bool cx, int64_t m, int64_t n);
+size_t grouped_bytes(bool cx, int64_t m, int64_t n);
 hsma_status trsm_batched_serial(const hsma_problem *probs, int64_t count, hipStream_t s);
 
 namespace {
@@ -51,7 +50,7 @@ double clock_ns() {
 
 enum State { PENDING = 0, RUNNING = 1, DONE = 2, FAILED = 3 };
 
-constexpr size_t kSmallShare = 4096;  // descriptor share of a small request
+constexpr size_t kShare = 4096;  // a request's share of its class's descriptors and stages
 #ifndef HSMA_SMALL_CU_STRIDE
 #define HSMA_SMALL_CU_STRIDE 16
 #endif
@@ -66,8 +65,7 @@ size_t footprint(const hsma_request &r) {
     const hsma_problem &p = r.prob;
     const bool cx = p.dtype == HSMA_C64F;
     size_t f = r.input == HSMA_INPUT_SYNTHETIC ? data_bytes(p) : 0;
-    f += p.m > 64 ? blocked_workspace_bytes(cx, p.m, lookup_block_size(cx, p.m, p.n)) : kSmallShare;
-    return f;
+    return f + kShare + (p.m > 64 ? grouped_bytes(cx, p.m, p.n) : 0);
 }
 
 // Device memory shared by the auto-released synthetic requests of one size

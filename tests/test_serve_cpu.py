@@ -355,3 +355,25 @@ def test_default_budget_is_32_gib():
         assert hs.request_footprint(ok) < 32 * 2**30
         t = q.submit(ok)
         assert q.wait(t, 60)["status"] == 0
+
+
+def test_footprint_covers_what_a_solve_takes():
+    """The budget bounds what is allocated: a request's footprint is at least
+    the workspace its solve takes, and, beyond that, no more than descriptors
+    (256 bytes an operation) and the share that every request pays."""
+    f = hs.lib()["_ZN4hsma13blocked_bytesIdEEmbllib"]   # blocked_bytes<double>
+    f.argtypes = [ctypes.c_bool, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_bool]
+    f.restype = ctypes.c_size_t
+    chains = 0
+    for cx in (False, True):
+        for m in (65, 200, 257, 512, 513, 1000, 1024, 2048, 4096, 8192, 16384, 40000):
+            for n in (1, 15, 16, 17, 256, 257, 512, 1000, 1024, 1025, 4096):
+                ws = f(cx, m, n, 0, False)
+                chains += ws > 0
+                most = ws + 4096 + 512 + 512 * (m * (2 if cx else 1) // 256 + 2)
+                fp = hs.request_footprint(dev_req(m, n, cx))
+                assert ws + 4096 <= fp <= most, (m, n, cx, ws, fp)
+                data = (16 if cx else 8) * (m * m + m * n)
+                assert hs.request_footprint(syn_req(m, n, cx=cx)) == fp + data
+    assert chains > 50
+    assert hs.request_footprint(dev_req(64, 64)) == 4096
