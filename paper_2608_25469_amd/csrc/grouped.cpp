@@ -4,7 +4,7 @@
 // gives it (a chain, or the same panels and the same recursive sequence of
 // panel solves and trailing updates), so every result is bit-for-bit the one
 // the problem gets alone.  What changes is how the work is launched: all chains
-// of a data type are one launch, and of the recursions the k-th operation of
+// of a data type are one launch (or a few, where their mail is large), and of the recursions the k-th operation of
 // every problem goes into one grouped launch, so a batch of hundreds of
 // mid-sized solves costs a few launches instead of a few per problem.  The
 // in-order walk of the recursion alternates panel, update, panel, ..., so step
@@ -80,6 +80,7 @@ struct Launch {
     bool cx = false;
     size_t img_off = 0;
     int64_t tiles = 0;
+    size_t words = 0;  // of mail
     int max_rows = 0, bm = 0, bn = 0;
     double flops = 0;
     std::vector<GemmParams> gemms;
@@ -103,27 +104,35 @@ PanelParams<double> op_panel(const Prob &p, const Op &o) {
     return q;
 }
 
-// Every panel of every chain, as one launch.  Panels are listed by their place
-// in their chain (all first panels, all second ones, ...), the longest chains
+// The mail of the chains of one launch, which every launch of a call uses in
+// turn.  It holds 32768 workgroups' blocks, many times what the chip runs at
+// once, so that nothing is lost between two launches; without a bound a batch
+// of large chains takes as much again as its B matrices.
+constexpr size_t kMailWords = ((size_t)1 << 30) / sizeof(double);
+
+// The panels of chains [first, end) of ps as one launch, where end is as far as
+// their mail fits (one chain always does).  Panels are listed by their place in
+// their chain (all first panels, all second ones, ...), the longest chains
 // first: a panel waits only for the one before it, so each round of the list
 // is work that can start once the round before it is under way, and no solve
 // holds the chip with panels that wait while another has not begun.  A
 // descriptor's mail is an offset until the mail has a place.
-void chain_launch(std::vector<Prob> &ps, Launch *l, size_t *words) {
-    std::stable_sort(ps.begin(), ps.end(), [](const Prob &a, const Prob &b) { return a.m > b.m; });
+size_t chain_launch(const std::vector<Prob> &ps, size_t first, Launch *l) {
     l->chain = l->panel = true;
     std::vector<size_t> mail;
-    size_t at = 0;
-    for (const Prob &p : ps) {
-        mail.push_back(at);
-        at += chain_bytes<double>(p.cx, p.m, p.n) / sizeof(double);
+    size_t end = first;
+    for (; end < ps.size(); ++end) {
+        const Prob &p = ps[end];
+        const size_t words = chain_bytes<double>(p.cx, p.m, p.n) / sizeof(double);
+        if (end > first && l->words + words > kMailWords) break;
+        mail.push_back(l->words);
+        l->words += words;
         l->flops += (p.cx ? 4.0 : 1.0) * p.m * (double)p.m * (double)p.n;
     }
-    *words = at;
     for (int64_t r = 0, more = 1; more; ++r) {
         more = 0;
-        for (size_t i = 0; i < ps.size(); ++i) {
-            const Prob &p = ps[i];
+        for (size_t i = 0; i < mail.size(); ++i) {
+            const Prob &p = ps[first + i];
             const int64_t h = kChainRows / p.es(), r0 = r * h;
             if (r0 >= p.m) continue;
             more = 1;
@@ -145,6 +154,7 @@ void chain_launch(std::vector<Prob> &ps, Launch *l, size_t *words) {
             l->panels.push_back(q);
         }
     }
+    return end;
 }
 
 GemmParams op_update(const Prob &p, const Op &o) {
@@ -206,16 +216,20 @@ hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_
     // served mix (n log-uniform in [1, 512]) cost more than the columns the
     // wide tiles leave idle.
     std::vector<Launch> launches;
-    size_t img_bytes = 0, mail_words[2] = {0, 0};
+    size_t img_bytes = 0, mail_words = 0;
     for (int cxi = 0; cxi < 2; ++cxi) {
-        Launch l;
-        chain_launch(chains[cxi], &l, &mail_words[cxi]);
-        if (l.panels.empty()) continue;
-        if (l.tiles > 0x7fffffff) return HSMA_INVALID_SIZE;
-        l.cx = cxi;
-        l.img_off = img_bytes;
-        img_bytes += padded(l.panels.size() * sizeof(PanelParams<double>));
-        launches.push_back(std::move(l));
+        std::vector<Prob> &cs = chains[cxi];
+        std::stable_sort(cs.begin(), cs.end(), [](const Prob &a, const Prob &b) { return a.m > b.m; });
+        for (size_t first = 0; first < cs.size();) {
+            Launch l;
+            first = chain_launch(cs, first, &l);
+            if (l.tiles > 0x7fffffff) return HSMA_INVALID_SIZE;
+            l.cx = cxi;
+            l.img_off = img_bytes;
+            img_bytes += padded(l.panels.size() * sizeof(PanelParams<double>));
+            mail_words = std::max(mail_words, l.words);
+            launches.push_back(std::move(l));
+        }
     }
     for (size_t k = 0; k < steps; ++k) {
         for (int cxi = 0; cxi < 2; ++cxi) {
@@ -265,18 +279,16 @@ hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_
         else std::memcpy(img.data() + l.img_off, l.gemms.data(), l.gemms.size() * sizeof(GemmParams));
     }
     void *dev = nullptr;
-    HSMA_TRY(ws_alloc(&dev, img_bytes + (mail_words[0] + mail_words[1]) * sizeof(double) + 512, s));
+    // (The tickets of a launch of chains follow its mail.)
+    HSMA_TRY(ws_alloc(&dev, img_bytes + (mail_words ? mail_words * sizeof(double) + 256 : 0), s));
     unsigned char *base = static_cast<unsigned char *>(dev);
-    // Mail of the real chains, then of the complex ones, 256 bytes after each.
-    double *mail[2];
-    mail[0] = reinterpret_cast<double *>(base + img_bytes);
-    mail[1] = mail[0] + mail_words[0] + 32;
+    double *mail = reinterpret_cast<double *>(base + img_bytes);
     for (const Launch &l : launches) {
         if (!l.chain) continue;
         unsigned char *img_l = img.data() + l.img_off;
         for (size_t i = 0; i < l.panels.size(); ++i) {
             PanelParams<double> q = l.panels[i];
-            q.mail = mail[l.cx] + reinterpret_cast<uintptr_t>(q.mail) / sizeof(double);
+            q.mail = mail + reinterpret_cast<uintptr_t>(q.mail) / sizeof(double);
             std::memcpy(img_l + i * sizeof(q), &q, sizeof(q));
         }
     }
@@ -286,7 +298,7 @@ hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_
         const void *d = base + l.img_off;
         if (l.chain)
             st = launch_chain_grouped(l.cx, static_cast<const PanelParams<double> *>(d), (int)l.panels.size(), l.tiles,
-                                      mail[l.cx], (int64_t)mail_words[l.cx], l.flops, s);
+                                      mail, (int64_t)l.words, l.flops, s);
         else if (l.panel)
             st = launch_panel_grouped(l.cx, static_cast<const PanelParams<double> *>(d), (int)l.panels.size(),
                                       l.max_rows, l.tiles, l.flops, s);

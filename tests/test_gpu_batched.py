@@ -1,5 +1,7 @@
 """Batched solves on the GPU: every problem against the oracle, the batch
 against one-at-a-time calls (bit for bit), and the plan API."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -272,3 +274,29 @@ def test_fused_very_small_batch():
         X = hs.from_colmajor(Bd)
         assert X.tobytes() == hs.from_colmajor(Bs).tobytes(), ("batched differs from single", k)
         assert_parity(L, B, X, a, unit=u, tag=("fused", k, B.shape))
+
+
+def test_mail_of_large_chains_is_bounded():
+    """A batch whose chains hand on 1.3 GB of X (40 of 4096 x 1024, which share
+    one L) takes little more than 1 GiB of workspace, and every X has the bits
+    it has alone."""
+    m, n, count = 4096, 1024, 40
+    held = hs.lib()["_ZN4hsma15ws_cached_bytesEv"]
+    held.restype = ctypes.c_size_t
+    L = torch.rand((m, m), dtype=torch.float64, device="cuda").div_(m)
+    L.diagonal().fill_(1.5)
+    L = L.t()
+    B = [torch.randn((n, m), dtype=torch.float64, device="cuda").t() for _ in range(count)]
+    X = [b.clone() for b in B]
+    torch.cuda.synchronize()
+    hs.workspace_release()
+    before = held()
+    hs.trsm_batched([(L, x, 0.5) for x in X])
+    torch.cuda.synchronize()
+    taken = held() - before
+    hs.workspace_release()
+    for i in (0, 1, 30, 31, 32, 39):
+        hs.trsm(L, B[i], 0.5)
+        torch.cuda.synchronize()
+        assert torch.equal(X[i], B[i]), i
+    assert 0 < taken <= 1.13 * 2 ** 30, taken
