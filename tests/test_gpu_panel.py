@@ -191,3 +191,42 @@ def test_waits_that_give_up_leave_nan(cx, m, n):
         there = ~torch.isnan(a)
         assert torch.equal(a[there], b[there]), (m, n, cx, looks)
         assert bool(there.all()) != gives_up, (m, n, cx, looks)
+
+
+@pytest.mark.parametrize("dt", list("dzsc"))
+@pytest.mark.parametrize("m,n", [(100, 40), (256, 30), (500, 33), (1100, 20)])
+def test_error_of_a_solve(dt, m, n):
+    """Panels and chains against extended precision, where the terms beside the
+    diagonal are small (diagonal in [1, 2], N(0, 1) right-hand sides): no more
+    than four roundings of an X at its own size, of 0.425 u each in the root mean
+    square (complex: a little more, its products are not exact), so 0.85 u and
+    0.9 u.  And infinities stay where a product with the inverse of a diagonal
+    block leaves them, in their own row."""
+    if dt in "zc":
+        m //= 2
+    wide = np.clongdouble if dt in "zc" else np.longdouble
+    L, B = W.problem(m, m, n, dt in "zc")
+    cast = {"d": np.float64, "z": np.complex128, "s": np.float32, "c": np.complex64}[dt]
+    r = np.random.default_rng(m)
+    d = r.uniform(1, 2, m) + (1j * r.uniform(-0.5, 0.5, m) if dt in "zc" else 0)
+    L = (np.tril(L, -1) / np.abs(np.tril(L, -1)).max() / m + np.diag(d)).astype(cast)
+    B = (r.normal(size=(m, n)) + (1j * r.normal(size=(m, n)) if dt in "zc" else 0)).astype(cast)
+    X = B.astype(wide) * wide(-0.75)
+    for k in range(m):
+        X[k] /= wide(L[k, k])
+        X[k + 1:] -= np.outer(L[k + 1:, k].astype(wide), X[k])
+    Ld, Bd = hs.to_colmajor(L), hs.to_colmajor(B)
+    hs.trsm(Ld, Bd, -0.75, path=2)
+    torch.cuda.synchronize()
+    got = hs.from_colmajor(Bd).astype(wide)
+    err = float(np.sqrt((np.abs(got - X) ** 2).sum() / (np.abs(X) ** 2).sum()))
+    u = 2.0 ** (-53 if dt in "dz" else -24)
+    assert err <= 0.5 * (1.8 if dt in "zc" else 1.7) * u, (dt, m, n, err / u)
+    B[m // 2, 3] = np.inf
+    B[m // 3, 5] = -np.inf
+    Bd = hs.to_colmajor(B)
+    hs.trsm(Ld, Bd, path=2)
+    torch.cuda.synchronize()
+    got = hs.from_colmajor(Bd)
+    assert np.isinf(got[m // 2, 3]) and np.isinf(got[m // 3, 5]), (dt, m, n)
+    assert np.isfinite(np.delete(got, [3, 5], 1)).all(), (dt, m, n)
