@@ -66,19 +66,29 @@ __device__ __forceinline__ void root(double p, double &d, double &inv) {
     inv = __fma_rn(__fma_rn(-d, y, 1.0), y, y);
 }
 
+// What lane l ^ 1 holds, to lane l.
+__device__ __forceinline__ double swap_pair(double v) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0xb1, 0xf, 0xf, false);  // quad_perm:[1,0,3,2]
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0xb1, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
 // The sixteen steps of a block column: each the root of the pivot, the scaled
 // column, and its product off the columns behind it, in the 16 rows of the
 // diagonal block (e, a copy per 16-lane row, so pivots and columns move by row
 // broadcasts) and in this lane's own row (x; `diag`: a row of the diagonal
-// block).  FAST: by `root`; false comes back if a pivot was outside 2^-900 ..
-// 2^900 (zero, negative, NaN), and the values are not to be used.  Otherwise by
-// the library's root and division, for any pivots.
-template <bool FAST>
+// block).  Complex: eight steps; the second real column of an element is the
+// first with its components exchanged and one negated, exactly, so that what is
+// subtracted is the product of the factor that is stored, and the pivot's
+// imaginary part is zero.  FAST: by `root`; false comes back if a pivot was
+// outside 2^-900 .. 2^900 (zero, negative, NaN), and the values are not to be
+// used.  Otherwise by the library's root and division, for any pivots.
+template <bool CX, bool FAST>
 __device__ __forceinline__ bool eliminate(double (&e)[16], double (&x)[16], int lr, bool diag) {
     constexpr unsigned kLow = (1023u - 900u) << 20, kSpan = 1800u << 20;
     unsigned most = 0;  // over the pivots' high words, from that of 2^-900
-    static_for<0, 16>([&](auto K) {
-        constexpr int c = decltype(K)::value;
+    static_for<0, CX ? 8 : 16>([&](auto K) {
+        constexpr int c = (CX ? 2 : 1) * decltype(K)::value;
         const double p = bcast<c>(e[c]);
         double d, inv, unused[16];
         if constexpr (FAST) {
@@ -89,12 +99,27 @@ __device__ __forceinline__ bool eliminate(double (&e)[16], double (&x)[16], int 
             d = sqrt(p);
             inv = 1.0 / d;
         }
-        const double l = e[c] * inv, xl = x[c] * inv;
-        if constexpr (c < 15) {
-            smallk::fnma_rows<false, c + 1>(e, unused, l, 0, l, 0);
-            smallk::fnma_rows<false, c + 1>(x, unused, l, 0, xl, 0);
+        double l = e[c] * inv, xl = x[c] * inv;
+        if constexpr (CX) {
+            if (lr == c + 1) l = 0;
+            if (diag && lr == c + 1) xl = 0;
+            const double l2 = Mma<double>::flip(swap_pair(l), lr & 1 ? 0 : 0x80000000u);
+            const double xl2 = Mma<double>::flip(swap_pair(xl), lr & 1 ? 0 : 0x80000000u);
+            if constexpr (c < 14) {
+                smallk::fnma_rows<false, c + 2>(e, unused, l, 0, l, 0);
+                smallk::fnma_rows<false, c + 2>(e, unused, l2, 0, l2, 0);
+                smallk::fnma_rows<false, c + 2>(x, unused, l, 0, xl, 0);
+                smallk::fnma_rows<false, c + 2>(x, unused, l2, 0, xl2, 0);
+            }
+            x[c] = diag && lr == c ? d : xl;
+            x[c + 1] = diag && lr == c + 1 ? d : xl2;
+        } else {
+            if constexpr (c < 15) {
+                smallk::fnma_rows<false, c + 1>(e, unused, l, 0, l, 0);
+                smallk::fnma_rows<false, c + 1>(x, unused, l, 0, xl, 0);
+            }
+            x[c] = diag && lr == c ? d : xl;
         }
-        x[c] = diag && lr == c ? d : xl;
     });
     return most < kSpan;
 }
@@ -120,8 +145,14 @@ __device__ __forceinline__ bool eliminate(double (&e)[16], double (&x)[16], int 
 // thirds of them the two rows' multiply-adds) and the products (64 cycles a
 // block of those left, 4300 on average).  Letting four wavefronts eliminate
 // while the others subtract the step before is slower (70 us against 64): both
-// use the FP64 units.  256 rows: 60 us, 64 rows 10; the 64-row kernel
+// use the FP64 units.  256 rows: 62 us, 64 rows 10; the 64-row kernel
 // with a barrier, a root and a division per column took 22.
+//
+// A block's products are summed from zero and meet it once per block column: one
+// by one, 256 of them would each be rounded at the size of A.  Relative error of
+// the factor of order 1000 in the norm, added one by one / so / with the 64-row
+// kernel: real 2.9e-16, 1.1e-16, 1.6e-16; complex 2.9e-16, 1.1e-16, 2.1e-16 (60 us
+// a base without).
 template <bool CX>
 __global__ __launch_bounds__(64 * kBaseWaves, 2) void hsma_potrf_base(double *__restrict__ A_, int64_t lda, int n) {
     constexpr int ES = CX ? 2 : 1;
@@ -230,9 +261,9 @@ __global__ __launch_bounds__(64 * kBaseWaves, 2) void hsma_potrf_base(double *__
                 for (int c = 0; c < 16; ++c) x[c] = own[at(c) + lr];
             };
             load();
-            if (__builtin_expect(!__all(eliminate<true>(e, x, lr, i == j)), 0)) {
+            if (__builtin_expect(!__all(eliminate<CX, true>(e, x, lr, i == j)), 0)) {
                 load();
-                eliminate<false>(e, x, lr, i == j);
+                eliminate<CX, false>(e, x, lr, i == j);
             }
             if (in) {
 #pragma unroll
@@ -252,13 +283,16 @@ __global__ __launch_bounds__(64 * kBaseWaves, 2) void hsma_potrf_base(double *__
         for (int u = 0; u < kBaseSlots; ++u) {
             if (bm[u] > j) {
                 double fa[4], fb[4];
+                Acc t = {0, 0, 0, 0};
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
                     fa[s] = fac[256 * bm[u] + fa0 + 16 * s];
                     fb[s] = fac[256 * bi[u] + fb0 + 16 * s];
                 }
 #pragma unroll
-                for (int s = 0; s < 4; ++s) acc[u] = Mma<double>::mma(fa[s], fb[s], acc[u]);
+                for (int s = 0; s < 4; ++s) t = Mma<double>::mma(fa[s], fb[s], t);
+#pragma unroll
+                for (int h = 0; h < 4; ++h) acc[u][h] += t[h];
                 if (bm[u] == j + 1) put(acc[u], bi[u]);
             }
         }

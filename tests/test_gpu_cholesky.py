@@ -137,3 +137,29 @@ def test_potrf_pivots_at_the_ends(cx):
                 assert np.isnan(G[k])
             else:
                 assert G[k] == np.sqrt(p), (n, k, p, G[k])
+
+
+@pytest.mark.parametrize("cx,n", [(False, 64), (False, 250), (False, 300), (True, 30), (True, 125), (True, 150)])
+def test_error_of_a_factor(cx, n):
+    """Against extended precision, on a diagonal of U(2, 3) with little beside it:
+    a pivot takes a rounding at its size for each of the 16 columns of its own
+    block and one for each block column before it (32 and more, 0.29 units in the
+    last place each in the root mean square, halved by the root), its root and
+    the factor's entries two of their own: 1.05 u together.  Bound: 1.25 u."""
+    r = np.random.default_rng(n)
+    R = r.uniform(-1, 1, (n, n)) + (1j * r.uniform(-1, 1, (n, n)) if cx else 0)
+    A = (R + R.conj().T) * (0.5 / np.sqrt(n))
+    A[np.arange(n), np.arange(n)] = r.uniform(2, 3, n)
+    G = np.tril(A).astype(np.clongdouble if cx else np.longdouble)
+    for k in range(n):
+        G[k, k] = np.sqrt(G[k, k].real)
+        G[k + 1:, k] /= G[k, k]
+        G[k + 1:, k + 1:] -= np.outer(G[k + 1:, k], G[k + 1:, k].conj())
+    G = np.tril(G)
+    Ad = hs.to_colmajor(A)
+    hs.potrf(Ad)
+    torch.cuda.synchronize()
+    got = np.tril(hs.from_colmajor(Ad))
+    assert (np.diag(got).imag == 0).all()
+    err = float(np.sqrt((np.abs(got - G) ** 2).sum() / (np.abs(G) ** 2).sum()))
+    assert err <= 1.25 * 2.0 ** -53, (cx, n, err * 2.0 ** 53)
