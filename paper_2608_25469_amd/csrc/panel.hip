@@ -37,6 +37,7 @@
 
 #include "dpp_fma.h"
 #include "gemm_core.h"
+#include "panel_index.h"
 
 namespace hsma {
 namespace {
@@ -45,7 +46,7 @@ using gemmk::Mma;
 using gemmk::fma_rn;
 using gemmk::mul_rn;
 
-constexpr int kWaves = 8;
+constexpr int kWaves = kPanelWaves;
 
 template <int B, int E, typename F>
 __device__ __forceinline__ void static_for(F &&f) {
@@ -168,6 +169,7 @@ struct Solve {
     T a[D][NQ][4];     // L_ji of steps i, i + 1, ..: slot i % D
     T *mail;           // CHAIN: this strip's blocks of -X, from block 0 of the solve
     int left;          // blocks before the panel
+    int spare;         // panel_spare(left)
     int looks;         // of a wait; 0: one has given up
     bool unit;
     // Of this wavefront's next block, read from LDS a step before their use (a
@@ -261,16 +263,15 @@ struct Solve {
     }
 
     // This lane's part of L_ji for step I and its blocks w + 8 q, q >= Q0:
-    // row 16 j + arow (kept below mr), columns 16 I + 4 g .. + 3.  Complex:
-    // the two complex elements that hold them, expanded at use.
+    // row 16 j + arow (kept below mr), columns 16 I + 4 g .. + 3; where the step
+    // has no use for them, columns it may read (panel_index.h).  Complex: the two
+    // complex elements that hold them, expanded at use.
     template <int I>
     __device__ __forceinline__ void load_l() {
         constexpr int Q0 = (I + 2) / kWaves;
-        // (Past the last step: columns 0..15, which a panel of two blocks has.)
-        const int i = I < nb - 1 ? I : 0;
         static_for<Q0, NQ>([&](auto Q) {
             constexpr int q = decltype(Q)::value;
-            load_a(q, i, a[I % D][q]);
+            load_a(q, panel_column(I, q, w, nb, spare), a[I % D][q]);
         });
     }
 
@@ -688,11 +689,12 @@ struct Solve {
         g = lane >> 4;
         lr = lane & 15;
         arow = Mma<T>::a_row(lr);
+        left = CHAIN ? p.left : 0;
+        spare = panel_spare(left);
         static_for<0, NQ>([&](auto Q) {
             constexpr int q = decltype(Q)::value;
-            const int r = 16 * (w + kWaves * q) + arow;
-            if constexpr (CX) at[q] = (const HSMA_GLOBAL char *)(A + 2 * (r / 2 < mr / 2 ? r / 2 : mr / 2 - 1) + 4 * g * lda);
-            else at[q] = (const HSMA_GLOBAL char *)(A + (r < mr ? r : mr - 1) + 4 * g * lda);
+            const int r = panel_row(q, w, arow, mr, spare);
+            at[q] = (const HSMA_GLOBAL char *)(A + (CX ? r & ~1 : r) + 4 * g * lda);
         });
         const int64_t c = 16 * (int64_t)tile + lr;
         col_ok = c < p.n;
@@ -704,7 +706,6 @@ struct Solve {
         }
 
         if constexpr (CHAIN) {
-            left = p.left;
             mail = p.mail + 256 * (int64_t)p.nblk * tile;
         }
         // The right-hand side, the diagonal blocks and the blocks before them are
