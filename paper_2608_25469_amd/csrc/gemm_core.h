@@ -26,8 +26,9 @@
 // to end there (its first rows repeat the previous tile's and are not
 // stored), and columns of B beyond N read column N-1 (not stored either), so
 // every slice but a ragged last one is plain 16-byte loads from pointers that
-// only advance.  Only the last slice of a K that BK does not divide, and
-// products with fewer rows than the tile, take guarded loads and LDS stores.
+// only advance.  Only the last slice of a K that BK does not divide, the slices
+// on the diagonal of a triangular A and products with fewer rows than the tile
+// take guarded loads and LDS stores.
 //
 // LDS layout.  A direct load writes a wavefront's 1 KB contiguously, so there
 // is no padding; bank conflicts are kept away by permuting, within a column,
@@ -62,6 +63,7 @@
 #include <type_traits>
 
 #include "internal.h"
+#include "tile_choice.h"
 
 namespace hsma {
 namespace gemmk {
@@ -155,7 +157,6 @@ __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
     // alone on their CU, a fifth (32 x 32, K = 8192: 117 against 145 us).
     constexpr bool TURNS = BM * BN >= 128 * 128;
     constexpr int FILL_AT = (CX || MIXED || !TURNS) ? BK / 8 - 1 : -1;
-    static_assert(!TRI || !SWZ_A, "the triangle is masked by LDS position");
     static_assert(WM * WN == 4, "four wavefronts");
     static_assert(TMR % 16 == 0 && TNC % 16 == 0, "16x16 blocks");
     static_assert(BK % 4 == 0 && BK % V == 0 && BM % V == 0, "whole pieces and k-steps");
@@ -177,9 +178,7 @@ __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
     }
     // A lower-triangular A has nothing right of column m0 + BM - 1 here.
     const int K = (TRI && p.k_lower && m0 + BM < p.K) ? m0 + BM : p.K;
-    // First row of the tile in memory: moved up where it would hang over.
-    const int ms = (m0 + BM > M && M >= BM) ? M - BM : m0;
-    const bool whole_rows = ms + BM <= M;
+    const int ms = first_row(M, BM, m0);
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm0 = (wave % WM) * TMR, wn0 = (wave / WM) * TNC;
@@ -211,7 +210,7 @@ __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
 
     // Slice at k0 into stage `buf`.
     auto fill = [&](int k0, int buf) {
-        if (whole_rows && k0 + BK <= K) {
+        if (direct_slice(M, BM, K, BK, TRI, ms, k0)) {
 #pragma unroll
             for (int it = 0; it < A_IT; ++it)
                 if (a_on) __builtin_amdgcn_global_load_lds((const void *)pa[it],
@@ -222,7 +221,8 @@ __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
                                                      (lds_void *)&Bs[buf][V * (wave * 64 + it * 256)], 16, 0, 0);
         } else {
             // Element by element: rows kept below M, nothing read at or
-            // beyond K, where both operands are zero.
+            // beyond K, where both operands are zero, nor of a triangle above
+            // its diagonal (or on it, where that is taken as 1).
 #pragma unroll
             for (int it = 0; it < A_IT; ++it) {
                 if (!a_on) break;
@@ -232,6 +232,14 @@ __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
 #pragma unroll
                     for (int t = 0; t < V; ++t) {
                         const int r = ms + a_i(it) + t;
+                        if constexpr (TRI) {
+                            const int above = k0 / ES + a_k(it) - r / ES;  // columns right of the diagonal
+                            if (above > 0) continue;
+                            if (above == 0 && p.tri_a == 2) {
+                                v[t] = (CX && (r & 1)) ? 0 : 1;
+                                continue;
+                            }
+                        }
                         v[t] = col[r < M ? r : (CX ? M - 2 + (r & 1) : M - 1)];
                     }
                 }
@@ -295,18 +303,6 @@ __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
         if (FILL_AT < 0 && ahead) fill((kt + NS - 1) * BK, buf == 0 ? NS - 1 : buf - 1);
         const TG *as = As[buf];
         const TG *bs = Bs[buf];
-        if constexpr (TRI) {
-            // Slices that reach the tile's first row hold entries of A on or
-            // above its diagonal: nothing above it, a unit diagonal as 1.
-            if (kt * BK + BK > ms) {
-                for (int e = tid; e < KA * BM; e += 256) {
-                    const int c = kt * KA + e / BM, r = ms + e % BM;
-                    if (r / ES < c) As[buf][e] = 0;
-                    else if (p.tri_a == 2 && r / ES == c) As[buf][e] = (CX && (r & 1)) ? 0 : 1;
-                }
-                __syncthreads();
-            }
-        }
 #pragma unroll
         for (int s = 0; s < BK / 4; ++s) {
             const int ka = CX ? 2 * s + (lk >> 1) : 4 * s + lk;

@@ -1,4 +1,5 @@
-// Tile shapes of the FP64 product (host code, no HIP dependency).
+// Tile shapes of the FP64 product, and which slices a tile loads without a look at
+// each element (no HIP dependency).
 //
 // A workgroup stages its A and B tiles through an LDS ring of two slices; the
 // ring's size sets how many workgroups a CU holds (160 KB of LDS, at most
@@ -15,6 +16,17 @@
 #include <cstdint>
 
 namespace hsma {
+
+// First row in memory of the tile that begins at row m0 of M: moved up where it
+// would hang over.
+constexpr int first_row(int M, int bm, int m0) { return m0 + bm > M && M >= bm ? M - bm : m0; }
+
+// Whether the slice of columns [k0, k0 + bk) of a tile (first row ms) is loaded
+// as it lies: all of it in A, and left of the diagonal of a triangular A (of all
+// rows, since rows further down have more of it).
+constexpr bool direct_slice(int M, int bm, int K, int bk, bool tri, int ms, int k0) {
+    return ms + bm <= M && k0 + bk <= K && !(tri && k0 + bk > ms);
+}
 
 constexpr int kTileBK = 16;
 

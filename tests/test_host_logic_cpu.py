@@ -1,7 +1,8 @@
 """Host logic of the launches, on the CPU: the bucket order of the grouped
 strip launch (csrc/strip_pack.h), the tile shape of a lower-triangular
-product (csrc/tile_choice.h: five shapes, 128 x 128 down to 32 x 32) and the
-elements of L that a panel's loads read (csrc/panel_index.h).
+product (csrc/tile_choice.h: five shapes, 128 x 128 down to 32 x 32), the slices
+that a tile loads as they lie (there too) and the elements of L that a panel's
+loads read (csrc/panel_index.h).
 
 Each header is compiled with g++ into a native driver (tests/native/) under
 the address and undefined-behaviour sanitizers: random buckets (every strip
@@ -42,3 +43,7 @@ def test_lower_tile_shape(tmp_path):
 
 def test_panel_loads(tmp_path):
     run_native(tmp_path, "panel_check", "panel loads ok")
+
+
+def test_direct_slices(tmp_path):
+    run_native(tmp_path, "slice_check", "slices ok")
