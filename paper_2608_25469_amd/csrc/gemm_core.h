@@ -26,9 +26,11 @@
 // to end there (its first rows repeat the previous tile's and are not
 // stored), and columns of B beyond N read column N-1 (not stored either), so
 // every slice but a ragged last one is plain 16-byte loads from pointers that
-// only advance.  Only the last slice of a K that BK does not divide, the slices
-// on the diagonal of a triangular A and products with fewer rows than the tile
-// take guarded loads and LDS stores.
+// only advance.  Only the last slice of a K that BK does not divide, and
+// products with fewer rows than the tile, take guarded loads and LDS stores, and
+// the slices on the diagonal of a triangular A go to LDS four bytes a lane, so
+// that each element has an address of its own and none above the diagonal is
+// read (a solve of 128 x 128 with a refinement step: 68 us, by guarded loads 74).
 //
 // LDS layout.  A direct load writes a wavefront's 1 KB contiguously, so there
 // is no padding; bank conflicts are kept away by permuting, within a column,
@@ -157,6 +159,7 @@ __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
     // alone on their CU, a fifth (32 x 32, K = 8192: 117 against 145 us).
     constexpr bool TURNS = BM * BN >= 128 * 128;
     constexpr int FILL_AT = (CX || MIXED || !TURNS) ? BK / 8 - 1 : -1;
+    static_assert(!TRI || !SWZ_A, "the triangle is masked by LDS position");
     static_assert(WM * WN == 4, "four wavefronts");
     static_assert(TMR % 16 == 0 && TNC % 16 == 0, "16x16 blocks");
     static_assert(BK % 4 == 0 && BK % V == 0 && BM % V == 0, "whole pieces and k-steps");
@@ -210,19 +213,32 @@ __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
 
     // Slice at k0 into stage `buf`.
     auto fill = [&](int k0, int buf) {
-        if (direct_slice(M, BM, K, BK, TRI, ms, k0)) {
+        const bool direct = direct_slice(M, BM, K, BK, TRI, ms, k0);
+        if (direct || (TRI && k0 + BK <= K)) {
+            if (direct) {
 #pragma unroll
-            for (int it = 0; it < A_IT; ++it)
-                if (a_on) __builtin_amdgcn_global_load_lds((const void *)pa[it],
-                                                     (lds_void *)&As[buf][V * (wave * 64 + it * 256)], 16, 0, 0);
+                for (int it = 0; it < A_IT; ++it)
+                    if (a_on) __builtin_amdgcn_global_load_lds((const void *)pa[it],
+                                                         (lds_void *)&As[buf][V * (wave * 64 + it * 256)], 16, 0, 0);
+            } else if constexpr (TRI) {
+                // On the diagonal, four bytes a lane: what lies above it (and
+                // rows beyond M) takes an element of its column that may be read.
+                static_assert(sizeof(TG) == 8 && KA * BM * 2 % 256 == 0, "two lanes an element, whole passes");
+#pragma unroll
+                for (int it = 0; it < KA * BM * 2 / 256; ++it) {
+                    const int e = (tid + it * 256) / 2, c = k0 / ES + e / BM;
+                    const GD *src = Ag + (c * a_col + tri_row(ES, M, ms + e % BM, c));
+                    __builtin_amdgcn_global_load_lds((const void *)((const char *)src + 4 * (tid & 1)),
+                                                     (lds_void *)((char *)&As[buf][0] + 4 * (wave * 64 + it * 256)), 4, 0, 0);
+                }
+            }
 #pragma unroll
             for (int it = 0; it < B_IT; ++it)
                 if (b_on) __builtin_amdgcn_global_load_lds((const void *)pb[it],
                                                      (lds_void *)&Bs[buf][V * (wave * 64 + it * 256)], 16, 0, 0);
         } else {
             // Element by element: rows kept below M, nothing read at or
-            // beyond K, where both operands are zero, nor of a triangle above
-            // its diagonal (or on it, where that is taken as 1).
+            // beyond K, where both operands are zero.
 #pragma unroll
             for (int it = 0; it < A_IT; ++it) {
                 if (!a_on) break;
@@ -232,15 +248,7 @@ __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
 #pragma unroll
                     for (int t = 0; t < V; ++t) {
                         const int r = ms + a_i(it) + t;
-                        if constexpr (TRI) {
-                            const int above = k0 / ES + a_k(it) - r / ES;  // columns right of the diagonal
-                            if (above > 0) continue;
-                            if (above == 0 && p.tri_a == 2) {
-                                v[t] = (CX && (r & 1)) ? 0 : 1;
-                                continue;
-                            }
-                        }
-                        v[t] = col[r < M ? r : (CX ? M - 2 + (r & 1) : M - 1)];
+                        v[t] = col[TRI ? tri_row(ES, M, r, k0 / ES + a_k(it)) : below(ES, M, r)];
                     }
                 }
                 *reinterpret_cast<VL *>(&As[buf][V * (tid + it * 256)]) = v;
@@ -303,6 +311,18 @@ __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
         if (FILL_AT < 0 && ahead) fill((kt + NS - 1) * BK, buf == 0 ? NS - 1 : buf - 1);
         const TG *as = As[buf];
         const TG *bs = Bs[buf];
+        if constexpr (TRI) {
+            // Slices that reach the tile's first row hold places on or above the
+            // diagonal: nothing above it, a unit diagonal as 1.
+            if (kt * BK + BK > ms) {
+                for (int e = tid; e < KA * BM; e += 256) {
+                    const int c = kt * KA + e / BM, r = ms + e % BM;
+                    if (r / ES < c) As[buf][e] = 0;
+                    else if (p.tri_a == 2 && r / ES == c) As[buf][e] = (CX && (r & 1)) ? 0 : 1;
+                }
+                __syncthreads();
+            }
+        }
 #pragma unroll
         for (int s = 0; s < BK / 4; ++s) {
             const int ka = CX ? 2 * s + (lk >> 1) : 4 * s + lk;

@@ -28,6 +28,12 @@ constexpr bool direct_slice(int M, int bm, int K, int bk, bool tri, int ms, int 
     return ms + bm <= M && k0 + bk <= K && !(tri && k0 + bk > ms);
 }
 
+// Row that is read in the place of row r (real view, es of them an element): kept
+// below M; of a triangle, and at element column c, also kept at or below the
+// diagonal.
+constexpr int below(int es, int M, int r) { return r < M ? r : M - es + r % es; }
+constexpr int tri_row(int es, int M, int r, int c) { return below(es, M, r / es < c ? c * es + r % es : r); }
+
 constexpr int kTileBK = 16;
 
 constexpr int tile_lds_bytes(int bm, int bn) { return 2 * (kTileBK * (bm + 4) + bn * (kTileBK + 1)) * 8; }

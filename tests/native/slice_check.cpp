@@ -1,7 +1,7 @@
 // Host check of the slices that a product's tile loads as they lie
 // (csrc/tile_choice.h): no element outside A, and none above the diagonal of a
 // triangular A, real and complex, for every tile of sizes around the tile's
-// multiples.
+// multiples; and of the rows read in the place of those above it or beyond A.
 #include <cstdio>
 #include <initializer_list>
 
@@ -22,6 +22,12 @@ int main() {
                             bad += ms < 0 || ms > m0 || (ms < m0 && ms + bm != M);
                             const int K = tri && m0 + bm < M ? m0 + bm : M;
                             for (int k0 = 0; k0 < K; k0 += bk) {
+                                for (int r = ms; tri && r < ms + bm; ++r)
+                                    for (int c = k0 / es; c < (k0 + bk) / es && c < K / es; ++c) {
+                                        const int t = tri_row(es, M, r, c);
+                                        bad += t < 0 || t >= M || t / es < c || t % es != r % es;
+                                        bad += r < M && r / es >= c && t != r;
+                                    }
                                 if (!direct_slice(M, bm, K, bk, tri, ms, k0)) continue;
                                 ++direct;
                                 for (int r = ms; r < ms + bm; ++r)
