@@ -35,9 +35,17 @@ hsma_status tiles64(const GemmParams &p, GemmRole role, hipStream_t s) {
 
 template <bool CX>
 hsma_status launch_role(GemmRole role, const GemmParams &p, hipStream_t s) {
-    if (role == GemmRole::Residual) return tiles64<CX, 128, 128, 16, 2, 2, true>(p, role, s);
     DeviceInfo dev;
     const int64_t cus = (device_info(&dev) == HSMA_SUCCESS && dev.num_cus > 0) ? dev.num_cus : 256;
+    if (role == GemmRole::Residual) {
+        // Where 128 x 128 tiles leave CUs idle, a slice's latency counts and not
+        // its products: half as many slices, of smaller tiles.  A solve and a
+        // refinement step with smaller / larger tiles, us: 64 x 17 51 / 62, 128 x
+        // 128 43 / 68, 2000 x 300 416 / 617, complex 64 x 64 83 / 104; 2000 x 1900
+        // (240 tiles) 762 / 922.
+        if ((int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128) < cus) return tiles64<CX, 64, 64, 32, 2, 2, true>(p, role, s);
+        return tiles64<CX, 128, 128, 16, 2, 2, true>(p, role, s);
+    }
     if (role == GemmRole::Herk) {
         // Lower-triangular C: the shape with the fewest rounds of non-empty
         // tiles (tile_choice.h).
