@@ -74,9 +74,9 @@ hsma_status launch_mixed(const GemmParams &p, hipStream_t s) {
     DeviceInfo dev;
     const int64_t cus = (device_info(&dev) == HSMA_SUCCESS && dev.num_cus > 0) ? dev.num_cus : 256;
     auto tiles = [&](int bm, int bn) { return (int64_t)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
-    if (tiles(128, 128) >= 2 * cus)
+    if (p.M >= 128 && tiles(128, 128) >= 2 * cus)
         return launch_tiles<double, float, false, false, 128, 128, 16, 2, 2, 2, 2, 256>(p, HSMA_PHASE_UPDATE, s);
-    if (tiles(64, 64) >= cus)
+    if (p.M >= 64 && tiles(64, 64) >= cus)
         return launch_tiles<double, float, false, false, 64, 64, 16, 2, 2, 3, 2, 256>(p, HSMA_PHASE_UPDATE, s);
     return launch_tiles<double, float, false, false, 32, 32, 64, 2, 2, 3, 2, 256>(p, HSMA_PHASE_UPDATE, s);
 }

@@ -101,18 +101,21 @@ constexpr UpdateShape kUpdateShapes[kNumUpdateShapes] = {{128, 128, 2, 0.74, 0.8
                                                          {32, 32, 2, 0.38, 0.63}};
 
 // Index into kUpdateShapes for an M x N product on `cus` CUs (M in real-view
-// rows); ties go to the larger tile.
+// rows); ties go to the larger tile, and a tile taller than the product, which
+// loads it element by element, is out (updates of 44 and 128 rows, n = 300000: 637
+// us against 689).
 inline int update_tile_shape(int64_t M, int64_t N, int64_t cus) {
-    int best = 0;
+    int best = -1;
     double best_cost = 0.0;
     for (int k = 0; k < kNumUpdateShapes; ++k) {
         const UpdateShape &t = kUpdateShapes[k];
+        if (t.bm > M && k + 1 < kNumUpdateShapes) continue;
         const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
         const int64_t rounds = tiles / (cus * t.wg), rest = tiles - rounds * cus * t.wg;
         const double area = (double)t.bm * t.bn;
         double cost = (double)rounds * t.wg * area / t.full;
         if (rest > 0) cost += std::max(area / t.solo, (double)((rest + cus - 1) / cus) * area / t.full);
-        if (k == 0 || cost < best_cost) {
+        if (best < 0 || cost < best_cost) {
             best = k;
             best_cost = cost;
         }

@@ -35,6 +35,9 @@ int main() {
                             }
                         }
                     }
+    // No update tile taller than its product, but the smallest.
+    for (int M = 1; M <= 300; ++M)
+        for (long long N : {1, 33, 300, 4097, 300000}) bad += kUpdateShapes[update_tile_shape(M, N, 256)].bm > (M > 32 ? M : 32);
     if (bad || direct < 100) {
         std::printf("%lld wrong in %lld slices\n", bad, direct);
         return 1;
