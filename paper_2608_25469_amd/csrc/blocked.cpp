@@ -41,6 +41,17 @@ bool chain_rule(bool cx, int elem, int64_t m, int64_t n) {
     return n <= 256 || (double)mr * (double)mr * (double)n <= (double)((int64_t)1 << 35);
 }
 
+// Panels of 512 real-view rows are the shortest way through the rows.  Through many
+// columns it is panels of 128 rows (FP32: 256), which have a kernel that takes them
+// two workgroups a CU and shares its start, with products between them.  Tall /
+// short panels, us: DTRSM 300 x 65536 425 / 295, 512 x 65536 564 / 548, 512 x 16384
+// 142 / 190, 300 x 300000 2025 / 1440; ZTRSM 129 x 65536 397 / 280, 256 x 65536 580 /
+// 613; STRSM 300 x 65536 289 / 233, 300 x 300000 1320 / 792.
+constexpr int64_t kWideColumns = 65536;
+int panel_span(bool cx, int elem, int64_t n) {
+    return (n >= kWideColumns ? wide_rows(elem) : kPanelRows) / (cx ? 2 : 1);
+}
+
 namespace {
 
 // T is double (DTRSM, ZTRSM) or float (STRSM, CTRSM); complex data is
@@ -132,7 +143,7 @@ hsma_status blocked_t(bool cx, bool unit, int64_t m, int64_t n, cplx alpha, cons
     c.lda = lda;
     c.B = B;
     c.ldb = ldb;
-    c.span = span > 0 ? span : kPanelRows / (cx ? 2 : 1);
+    c.span = span > 0 ? span : panel_span(cx, sizeof(T), n);
     c.s = s;
     return recurse(c, 0, (m + c.span - 1) / c.span, false);
 }
@@ -166,12 +177,12 @@ hsma_status blocked_trsm32(bool cx, bool unit, int64_t m, int64_t n, cplx alpha,
 // the strides cost nothing and the two copies (two launches, four passes over
 // B) go.
 bool solves_in_one(bool cx, int64_t m, int64_t n) {
-    return m > 64 && (m * (cx ? 2 : 1) <= kPanelRows || chain_rule(cx, sizeof(double), m, n));
+    return m > 64 && (m <= panel_span(cx, sizeof(double), n) || chain_rule(cx, sizeof(double), m, n));
 }
 
 hsma_status blocked_in_one(bool cx, int64_t m, PanelParams<double> p, hipStream_t s) {
     p.at = 1;
-    if (m * (cx ? 2 : 1) <= kPanelRows) {
+    if (m <= panel_span(cx, sizeof(double), p.n)) {
         p.rows = (int)m;
         return launch_panel<double>(cx, p, s);
     }

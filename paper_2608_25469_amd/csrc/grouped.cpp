@@ -81,7 +81,7 @@ struct Launch {
     size_t img_off = 0;
     int64_t tiles = 0;
     size_t words = 0;  // of mail
-    int max_rows = 0, bm = 0, bn = 0;
+    int max_rows = 0, per = 1, bm = 0, bn = 0;
     double flops = 0;
     std::vector<GemmParams> gemms;
     std::vector<PanelParams<double>> panels;
@@ -175,7 +175,8 @@ size_t grouped_bytes(bool cx, int64_t m, int64_t n) {
     const int64_t mr = m * (cx ? 2 : 1);
     if (chain_rule(cx, sizeof(double), m, n))
         return chain_bytes<double>(cx, m, n) + 512 + padded((mr + kChainRows - 1) / kChainRows * sizeof(PanelParams<double>));
-    const size_t panels = (mr + kPanelRows - 1) / kPanelRows;
+    const int64_t span = panel_span(cx, sizeof(double), n);
+    const size_t panels = (m + span - 1) / span;
     return panels * padded(sizeof(PanelParams<double>)) + (panels - 1) * padded(sizeof(GemmParams)) + 512;
 }
 
@@ -184,7 +185,8 @@ hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_
     if (count <= 0) return HSMA_SUCCESS;
     std::vector<Prob> ps, chains[2];
     ps.reserve(count);
-    std::vector<std::vector<Op>> ops;
+    std::vector<Op> ops;  // of problem i of ps from first[i] on
+    std::vector<size_t> first;
     size_t steps = 0;
     for (int64_t i = 0; i < count; ++i) {
         const hsma_problem &q = probs[i];
@@ -198,17 +200,18 @@ hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_
         p.lda = q.lda;
         p.B = static_cast<double *>(q.B);
         p.ldb = q.ldb;
-        p.span = kPanelRows / (p.cx ? 2 : 1);
+        p.span = panel_span(p.cx, sizeof(double), p.n);
         p.nb = (p.m + p.span - 1) / p.span;
         if (chain_rule(p.cx, sizeof(double), p.m, p.n)) {
             chains[p.cx].push_back(p);
             continue;
         }
-        ops.emplace_back();
-        walk(p, 0, p.nb, false, ops.back());
-        steps = std::max(steps, ops.back().size());
+        first.push_back(ops.size());
+        walk(p, 0, p.nb, false, ops);
+        steps = std::max(steps, ops.size() - first.back());
         ps.push_back(p);
     }
+    first.push_back(ops.size());
 
     // Each step's products share one launch whatever their widths: the tile
     // shape follows the widest.  Separate launches for narrow right-hand
@@ -220,9 +223,9 @@ hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_
     for (int cxi = 0; cxi < 2; ++cxi) {
         std::vector<Prob> &cs = chains[cxi];
         std::stable_sort(cs.begin(), cs.end(), [](const Prob &a, const Prob &b) { return a.m > b.m; });
-        for (size_t first = 0; first < cs.size();) {
+        for (size_t at = 0; at < cs.size();) {
             Launch l;
-            first = chain_launch(cs, first, &l);
+            at = chain_launch(cs, at, &l);
             if (l.tiles > 0x7fffffff) return HSMA_INVALID_SIZE;
             l.cx = cxi;
             l.img_off = img_bytes;
@@ -237,25 +240,33 @@ hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_
             l.cx = cxi;
             l.panel = k % 2 == 0;
             int max_m = 0, max_n = 0;
+            std::vector<int64_t> strips;
             for (size_t pi = 0; pi < ps.size(); ++pi) {
                 const Prob &p = ps[pi];
-                if (p.cx != (bool)cxi || k >= ops[pi].size()) continue;
+                if (p.cx != (bool)cxi || k >= first[pi + 1] - first[pi]) continue;
+                const Op &o = ops[first[pi] + k];
                 if (l.panel) {
-                    PanelParams<double> q = op_panel(p, ops[pi][k]);
-                    if (l.tiles > 0x7fffffff) return HSMA_INVALID_SIZE;
-                    q.tile0 = (int)l.tiles;
-                    l.tiles += (q.n + 15) / 16;
+                    PanelParams<double> q = op_panel(p, o);
+                    strips.push_back((q.n + 15) / 16);
                     l.max_rows = std::max(l.max_rows, q.rows);
                     l.flops += (p.cx ? 4.0 : 1.0) * q.rows * (double)q.rows * (double)q.n;
                     l.panels.push_back(q);
                 } else {
-                    l.gemms.push_back(op_update(p, ops[pi][k]));
+                    l.gemms.push_back(op_update(p, o));
                     max_m = std::max(max_m, l.gemms.back().M);
                     max_n = std::max(max_n, l.gemms.back().N);
                 }
             }
             if (l.panels.empty() && l.gemms.empty()) continue;
-            if (!l.panel) {
+            if (l.panel) {
+                l.per = panel_per(cxi, sizeof(double), l.max_rows, strips.data(), strips.size());
+                for (PanelParams<double> &q : l.panels) {
+                    if (l.tiles > 0x7fffffff) return HSMA_INVALID_SIZE;
+                    q.per = l.per;
+                    q.tile0 = (int)l.tiles;
+                    l.tiles += panel_share((q.n + 15) / 16, &q.per);
+                }
+            } else {
                 if (!gemm_grouped_tile(max_m, max_n, &l.bm, &l.bn)) return HSMA_NOT_SUPPORTED;
                 for (GemmParams &g : l.gemms) {
                     g.tiles_m = (g.M + l.bm - 1) / l.bm;
@@ -301,7 +312,7 @@ hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_
                                       mail, (int64_t)l.words, l.flops, s);
         else if (l.panel)
             st = launch_panel_grouped(l.cx, static_cast<const PanelParams<double> *>(d), (int)l.panels.size(),
-                                      l.max_rows, l.tiles, l.flops, s);
+                                      l.max_rows, l.tiles, l.per > 1, l.flops, s);
         else
             st = launch_gemm_grouped(l.cx, l.bm, l.bn, static_cast<const GemmParams *>(d), (int)l.gemms.size(),
                                      l.tiles, l.flops, s);

@@ -197,10 +197,27 @@ struct PanelParams {
     int64_t rs, cs;
     T *keep;
     int64_t ldkeep;
+    int per;             // strips of 16 columns a workgroup solves one after another (0: one; chains: one)
     int looks = kMaxLooks;  // of a wavefront at what it waits for, before it takes NaN instead
 };
 template <typename T>
 hsma_status launch_panel(bool cx, const PanelParams<T> &p, hipStream_t s);
+// Panels of up to wide_rows real-view rows whose strips are many times what the
+// chip takes at once run on a kernel of their own, several strips a workgroup:
+// `per` for a launch whose panels have these numbers of strips and at most max_rows
+// rows (1: the other kernel).
+constexpr int wide_rows(int elem) { return elem == 8 ? 128 : 256; }
+int panel_per(bool cx, int elem, int max_rows, const int64_t *strips, size_t count);
+// The workgroups of a panel with at most *per strips each, and *per with them
+// shared out evenly.
+int64_t panel_share(int64_t strips, int *per);
+template <typename T>
+hsma_status launch_panel_wide(bool cx, const PanelParams<T> &one, const PanelParams<T> *descs, int nd, int max_rows,
+                              int64_t groups, hipStream_t s);
+// Workgroups of 512 that one launch can have (2^32 threads).
+constexpr int64_t kMaxGroups = ((int64_t)1 << 32) / 512 - 1;
+// Rows of a panel of a solve with n columns, unless the caller says (blocked.cpp).
+int panel_span(bool cx, int elem, int64_t n);
 // A whole solve as one launch: panels of kChainRows real-view rows in order, a
 // workgroup per panel and strip of 16 columns, X handed on through `ws`
 // (chain_bytes).  Rows any number.
@@ -223,8 +240,8 @@ hsma_status launch_chain(bool cx, const PanelParams<T> &p, int64_t m, void *ws, 
 // mail they point into is `words` values at `mail`, with 256 bytes more.
 hsma_status launch_chain_grouped(bool cx, const PanelParams<double> *descs, int nd, int64_t tiles, double *mail,
                                  int64_t words, double flops, hipStream_t s);
-hsma_status launch_panel_grouped(bool cx, const PanelParams<double> *descs, int nd, int max_rows, int64_t tiles,
-                                 double flops, hipStream_t s);
+hsma_status launch_panel_grouped(bool cx, const PanelParams<double> *descs, int nd, int max_rows, int64_t groups,
+                                 bool wide, double flops, hipStream_t s);
 
 // dst (R x C, ldd) = src^H for src C x R (ldsrc); the transpose for real data.
 // X L^H = B for a lower, non-unit L (m x n X and B, n x n L; FP64 real or

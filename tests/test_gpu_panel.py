@@ -230,3 +230,51 @@ def test_error_of_a_solve(dt, m, n):
     got = hs.from_colmajor(Bd)
     assert np.isinf(got[m // 2, 3]) and np.isinf(got[m // 3, 5]), (dt, m, n)
     assert np.isfinite(np.delete(got, [3, 5], 1)).all(), (dt, m, n)
+
+
+@pytest.mark.parametrize("n", [16400, 65541])
+@pytest.mark.parametrize("dt,m", [("d", 65), ("d", 128), ("d", 129), ("d", 300), ("z", 40), ("z", 64), ("z", 150),
+                                  ("s", 65), ("s", 256), ("s", 300), ("c", 64), ("c", 65), ("c", 200)])
+def test_many_columns(dt, m, n):
+    """Panels of many strips (several a workgroup, panels of another height from
+    65536 columns): the bits of the same panels on a thousand columns."""
+    span = {"d": 128, "z": 64, "s": 256, "c": 128}[dt]
+    g = torch.Generator(device="cuda").manual_seed(m)
+    Ls = torch.tril(_ints((m, m), dt, -3, 3, g), -1) / m + 1.5 * torch.eye(m, dtype=DT[dt], device="cuda")
+    L = _colmajor(Ls)
+    B = hs.colmajor(m, n, DT[dt], ld=m + 1)
+    B.copy_(_ints((m, n), dt, -3, 3, g))
+    X = hs.colmajor(m, n, DT[dt], ld=m + 1)
+    X.copy_(B)
+    hs.trsm(L, X, 0.5, path=2, unit=m == 129)
+    for c in (0, n // 2, n - 1000):
+        want = _colmajor(B[:, c:c + 1000])
+        hs.trsm(L, want, 0.5, path=2, unit=m == 129, block_size=span if n >= 65536 and m > span else 0)
+        torch.cuda.synchronize()
+        assert torch.equal(X[:, c:c + 1000], want), (dt, m, n, c)
+
+
+@pytest.mark.parametrize("dt,k", [("d", 100), ("z", 66), ("d", 200)])
+def test_many_rows_from_the_right(dt, k):
+    """The same where B is read at strides (X L^H = B)."""
+    nr, g = 70001, torch.Generator(device="cuda").manual_seed(k)
+    L = _colmajor(torch.tril(_ints((k, k), dt, -3, 3, g), -1) / k + 1.5 * torch.eye(k, dtype=DT[dt], device="cuda"))
+    B = _ints((nr, k), dt, -3, 3, g)
+    X, want = _colmajor(B), _colmajor(B.mH)
+    hs.trsm_general(L, X, 0.5, side="R", uplo="L", trans="C")
+    hs.trsm(L, want, 0.5)
+    torch.cuda.synchronize()
+    assert torch.equal(X, want.mH), (dt, k)
+
+
+def test_more_columns_than_one_launch_of_strips():
+    """2^27 columns and more: a workgroup of 512 for each strip of 16 would be
+    more threads than a launch can have."""
+    m, n = 65, (1 << 27) + 17
+    Ls = torch.eye(m, device="cuda") + torch.diag(torch.ones(m - 1, device="cuda"), 1)   # row j: column j of L
+    B = torch.ones((n, m), device="cuda").t()
+    hs.trsm(Ls.t(), B)
+    torch.cuda.synchronize()
+    want = (1 - torch.arange(m, device="cuda") % 2).float()
+    for c in range(0, n, 1 << 24):
+        assert bool((B[:, c:c + (1 << 24)] == want[:, None]).all()), c
