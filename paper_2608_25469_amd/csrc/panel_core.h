@@ -408,7 +408,7 @@ struct Solve {
     // residual over the diagonal and joins the sums, so that an X is rounded about
     // as often as in a division: 500 x 300 is 6.7e-17 off the exact result in the
     // norm (1.06e-16 without; inverted blocks of 64 rows 8.5e-17; rounding the
-    // exact one 4.7e-17), for 0.4 us of 36.9.
+    // exact one 4.7e-17), in the same 36.3 us.
     template <int J>
     __device__ __forceinline__ void prepare() {
         constexpr int q = J / kWaves;
@@ -429,49 +429,66 @@ struct Solve {
             for (int v = 0; v < 4; ++v)
                 if (16 * J + 4 * g + v >= mr) b[v] = 0;
         }
+        // (A unit diagonal's reciprocals and pivots are 1 and nothing is rounded;
+        // real data takes the same way, in the shadow of the products.)
+        if (CX && unit) {
+            y = Acc{0, 0, 0, 0};
+#pragma unroll
+            for (int s = 0; s < 4; ++s) y = Mma<T>::mma(fi[s], b[s], y);
+            main = b;
+            // (As below: alone where it is not finite.)
+            if (__builtin_expect(__ballot(!finite((b[0] - b[0]) + (b[1] - b[1]) + (b[2] - b[2]) + (b[3] - b[3]))) != 0, 0)) {
+#pragma unroll
+                for (int h = 0; h < 4; ++h)
+                    if (!finite(b[h])) y[h] = 0;
+            }
+            return;
+        }
+        const T *d = sh.diag[J] + 4 * g, *l = sh.pivot[J] + 4 * g;
+        T dv[4], lv[4], rest[4];
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            dv[h] = d[h];
+            lv[h] = l[h];
+        }
         y = Acc{0, 0, 0, 0};
 #pragma unroll
         for (int s = 0; s < 4; ++s) y = Mma<T>::mma(fi[s], b[s], y);
-        if (unit) {
-            main = b;
+        if constexpr (CX) {
+#pragma unroll
+            for (int h = 0; h < 4; h += 2) {
+                main[h] = fma_rn(b[h], dv[h], -mul_rn(b[h + 1], dv[h + 1]));
+                main[h + 1] = fma_rn(b[h], dv[h + 1], mul_rn(b[h + 1], dv[h]));
+                const T e0 = fma_rn(lv[h + 1], main[h + 1], fma_rn(-lv[h], main[h], b[h]));
+                const T e1 = fma_rn(-lv[h + 1], main[h], fma_rn(-lv[h], main[h + 1], b[h + 1]));
+                rest[h] = fma_rn(e0, dv[h], -mul_rn(e1, dv[h + 1]));
+                rest[h + 1] = fma_rn(e0, dv[h + 1], mul_rn(e1, dv[h]));
+            }
         } else {
-            const T *d = sh.diag[J] + 4 * g, *l = sh.pivot[J] + 4 * g;
-            Acc rest;
-            if constexpr (CX) {
 #pragma unroll
-                for (int h = 0; h < 4; h += 2) {
-                    main[h] = fma_rn(b[h], d[h], -mul_rn(b[h + 1], d[h + 1]));
-                    main[h + 1] = fma_rn(b[h], d[h + 1], mul_rn(b[h + 1], d[h]));
-                    const T e0 = fma_rn(l[h + 1], main[h + 1], fma_rn(-l[h], main[h], b[h]));
-                    const T e1 = fma_rn(-l[h + 1], main[h], fma_rn(-l[h], main[h + 1], b[h + 1]));
-                    rest[h] = fma_rn(e0, d[h], -mul_rn(e1, d[h + 1]));
-                    rest[h + 1] = fma_rn(e0, d[h + 1], mul_rn(e1, d[h]));
-                }
-            } else {
-#pragma unroll
-                for (int h = 0; h < 4; ++h) {
-                    main[h] = mul_rn(d[h], b[h]);
-                    rest[h] = mul_rn(fma_rn(-l[h], main[h], b[h]), d[h]);
-                }
-            }
-#pragma unroll
-            for (int h = 0; h < 4; ++h) y[h] += rest[h];
-        }
-        // Columns that hold an infinity or a NaN, or overflow here: the whole
-        // product with the inverse, its diagonal in its place (apart, infinity
-        // less infinity would make an infinite X a NaN).
-        const uint64_t bad = __ballot(!(finite(main[0]) && finite(main[1]) && finite(main[2]) && finite(main[3])));
-        if (__builtin_expect(bad != 0, 0)) {
-            T f[4];
-            read_a(sh.inv[J], f);
-            Acc whole = {0, 0, 0, 0};
-#pragma unroll
-            for (int s = 0; s < 4; ++s) whole = Mma<T>::mma(f[s], b[s], whole);
-            if ((bad | bad >> 16 | bad >> 32 | bad >> 48) >> lr & 1) {
-                y = whole;
-                main = Acc{0, 0, 0, 0};
+            for (int h = 0; h < 4; ++h) {
+                main[h] = mul_rn(dv[h], b[h]);
+                rest[h] = mul_rn(fma_rn(-lv[h], main[h], b[h]), dv[h]);
             }
         }
+        const T all = (rest[0] + rest[1]) + (rest[2] + rest[3]);
+        // (The diagonal's part in the shadow of the products.)
+        static_for<0, 4>([&](auto) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, CX ? 8 : 4, 0);
+        });
+        // An infinity or a NaN in B, an overflow or an infinite pivot leaves no
+        // number as the residual.  The diagonal's part then stands as it is, and
+        // alone where it is not finite (the sums hold 0 times infinity there).
+        if (__builtin_expect(__ballot(!finite(all)) != 0, 0)) {
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                if (!finite(rest[h])) rest[h] = 0;
+                if (!finite(main[h])) y[h] = 0;
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < 4; ++h) y[h] += rest[h];
     }
 
     // X_J to the other wavefronts (by its owner): LDS takes a wavefront's

@@ -230,6 +230,20 @@ def test_error_of_a_solve(dt, m, n):
     got = hs.from_colmajor(Bd)
     assert np.isinf(got[m // 2, 3]) and np.isinf(got[m // 3, 5]), (dt, m, n)
     assert np.isfinite(np.delete(got, [3, 5], 1)).all(), (dt, m, n)
+    Bd = hs.to_colmajor(B)
+    hs.trsm(Ld, Bd, path=2, unit=True)
+    torch.cuda.synchronize()
+    got = hs.from_colmajor(Bd)
+    assert np.isinf(got[m // 2, 3]) and np.isinf(got[m // 3, 5]), (dt, m, n)
+    assert np.isfinite(np.delete(got, [3, 5], 1)).all(), (dt, m, n)
+    if dt in "ds":   # an infinite pivot: its X is 0, and what follows stands
+        L[m // 2, m // 2] = np.inf
+        B[m // 2, 3] = B[m // 3, 5] = 1
+        Bd = hs.to_colmajor(B)
+        hs.trsm(hs.to_colmajor(L), Bd, path=2)
+        torch.cuda.synchronize()
+        got = hs.from_colmajor(Bd)
+        assert (got[m // 2] == 0).all() and np.isfinite(got).all(), (dt, m, n)
 
 
 @pytest.mark.parametrize("n", [16400, 65541])
