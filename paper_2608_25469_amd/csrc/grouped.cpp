@@ -110,13 +110,18 @@ PanelParams<double> op_panel(const Prob &p, const Op &o) {
 // of large chains takes as much again as its B matrices.
 constexpr size_t kMailWords = ((size_t)1 << 30) / sizeof(double);
 
+// Strips of chains that are listed side by side.
+constexpr int64_t kSideBySide = 768;
+
 // The panels of chains [first, end) of ps as one launch, where end is as far as
 // their mail fits (one chain always does).  Panels are listed by their place in
 // their chain (all first panels, all second ones, ...), the longest chains
 // first: a panel waits only for the one before it, so each round of the list
 // is work that can start once the round before it is under way, and no solve
-// holds the chip with panels that wait while another has not begun.  A
-// descriptor's mail is an offset until the mail has a place.
+// holds the chip with panels that wait while another has not begun.  Of a batch
+// that is many times the chip, as many solves at a time as fill it: what a panel
+// mails is then read again while it is in the caches.  A descriptor's mail is an
+// offset until the mail has a place.
 size_t chain_launch(const std::vector<Prob> &ps, size_t first, Launch *l) {
     l->chain = l->panel = true;
     std::vector<size_t> mail;
@@ -129,30 +134,35 @@ size_t chain_launch(const std::vector<Prob> &ps, size_t first, Launch *l) {
         l->words += words;
         l->flops += (p.cx ? 4.0 : 1.0) * p.m * (double)p.m * (double)p.n;
     }
-    for (int64_t r = 0, more = 1; more; ++r) {
-        more = 0;
-        for (size_t i = 0; i < mail.size(); ++i) {
-            const Prob &p = ps[first + i];
-            const int64_t h = kChainRows / p.es(), r0 = r * h;
-            if (r0 >= p.m) continue;
-            more = 1;
-            PanelParams<double> q{};
-            q.A = p.A + p.es() * (r0 + r0 * p.lda);
-            q.lda = p.lda;
-            q.B = p.B + p.es() * r0;
-            q.ldb = p.ldb;
-            q.n = p.n;
-            q.alpha_re = p.alpha.re;
-            q.alpha_im = p.alpha.im;
-            q.rows = (int)std::min(h, p.m - r0);
-            q.unit = p.unit;
-            q.left = (int)(r * (kChainRows / 16));
-            q.nblk = (int)((p.m * p.es() + 15) / 16);
-            q.mail = reinterpret_cast<double *>(mail[i] * sizeof(double));
-            q.tile0 = (int)std::min<int64_t>(l->tiles, 0x7fffffff);
-            l->tiles += (p.n + 15) / 16;
-            l->panels.push_back(q);
+    for (size_t from = 0; from < mail.size();) {
+        size_t to = from;
+        for (int64_t strips = 0; to < mail.size() && strips < kSideBySide; ++to) strips += (ps[first + to].n + 15) / 16;
+        for (int64_t r = 0, more = 1; more; ++r) {
+            more = 0;
+            for (size_t i = from; i < to; ++i) {
+                const Prob &p = ps[first + i];
+                const int64_t h = kChainRows / p.es(), r0 = r * h;
+                if (r0 >= p.m) continue;
+                more = 1;
+                PanelParams<double> q{};
+                q.A = p.A + p.es() * (r0 + r0 * p.lda);
+                q.lda = p.lda;
+                q.B = p.B + p.es() * r0;
+                q.ldb = p.ldb;
+                q.n = p.n;
+                q.alpha_re = p.alpha.re;
+                q.alpha_im = p.alpha.im;
+                q.rows = (int)std::min(h, p.m - r0);
+                q.unit = p.unit;
+                q.left = (int)(r * (kChainRows / 16));
+                q.nblk = (int)((p.m * p.es() + 15) / 16);
+                q.mail = reinterpret_cast<double *>(mail[i] * sizeof(double));
+                q.tile0 = (int)std::min<int64_t>(l->tiles, 0x7fffffff);
+                l->tiles += (p.n + 15) / 16;
+                l->panels.push_back(q);
+            }
         }
+        from = to;
     }
     return end;
 }

@@ -214,6 +214,8 @@ int64_t panel_share(int64_t strips, int *per);
 template <typename T>
 hsma_status launch_panel_wide(bool cx, const PanelParams<T> &one, const PanelParams<T> *descs, int nd, int max_rows,
                               int64_t groups, hipStream_t s);
+hsma_status launch_chain_wide(bool cx, const PanelParams<double> *descs, int nd, int64_t tiles, unsigned *tickets,
+                              hipStream_t s);
 // Workgroups of 512 that one launch can have (2^32 threads).
 constexpr int64_t kMaxGroups = ((int64_t)1 << 32) / 512 - 1;
 // Rows of a panel of a solve with n columns, unless the caller says (blocked.cpp).

@@ -20,43 +20,6 @@ __global__ __launch_bounds__(256) void hsma_mail_empty(T *mail, int64_t n, unsig
     if (blockIdx.x == 0 && threadIdx.x == 0) *tickets = 0;
 }
 
-// A chain: workgroups take tickets, and ticket t of one solve is panel t /
-// strips, strip t % strips, so a workgroup waits only for workgroups that
-// started before it.  `one` describes panel 0 with the solve's row count in
-// `rows`; with descs each descriptor is one panel, listed so that a solve's
-// panels come in order.
-template <typename T, bool CX, bool AT>
-__global__ __launch_bounds__(64 * kWaves, 2) void hsma_chain(const PanelParams<T> one,
-                                                             const PanelParams<T> *__restrict__ descs, int nd,
-                                                             unsigned *__restrict__ tickets) {
-    typedef Solve<T, CX, kChainRows / (16 * kWaves), true, AT> S;
-    __shared__ typename S::Shared sh;
-    if (threadIdx.x == 0) {
-        sh.done = 0;
-        sh.ticket = (int)atomicAdd(tickets, 1u);
-    }
-    __syncthreads();
-    int tile = __builtin_amdgcn_readfirstlane(sh.ticket);
-    PanelParams<T> p = one;
-    if (descs) {
-        p = descs[find(descs, nd, tile)];
-        tile -= p.tile0;
-    } else {
-        constexpr int ES = CX ? 2 : 1, H = kChainRows / ES;
-        const int strips = (int)((p.n + 15) / 16);
-        const int r = tile / strips;
-        tile -= r * strips;
-        p.left = r * (kChainRows / 16);
-        p.A = one.A + ES * ((int64_t)r * H) * (1 + one.lda);
-        p.B = one.B + ES * (int64_t)r * H * (AT ? one.rs : 1);
-        if constexpr (AT)
-            if (p.keep) p.keep += ES * (int64_t)r * H;
-        p.rows = one.rows - r * H < H ? one.rows - r * H : H;
-    }
-    S s(sh);
-    s.run(p, tile);
-}
-
 template <typename T, bool CX>
 hsma_status launch(const PanelParams<T> &one, const PanelParams<T> *descs, int nd, int max_rows, int64_t groups, bool wide,
                    hipStream_t s) {
@@ -118,8 +81,8 @@ hsma_status launch_chain(bool cx, const PanelParams<T> &q, int64_t m, void *ws, 
     const dim3 grid((unsigned)(panels * strips)), block(64 * kWaves);
     auto go = [&](auto AT) {
         constexpr bool at = decltype(AT)::value;
-        if (cx) hipLaunchKernelGGL((hsma_chain<T, true, at>), grid, block, 0, s, p, nullptr, 0, tickets);
-        else hipLaunchKernelGGL((hsma_chain<T, false, at>), grid, block, 0, s, p, nullptr, 0, tickets);
+        if (cx) hipLaunchKernelGGL((hsma_chain<T, true, at, false>), grid, block, 0, s, p, nullptr, 0, tickets);
+        else hipLaunchKernelGGL((hsma_chain<T, false, at, false>), grid, block, 0, s, p, nullptr, 0, tickets);
     };
     if constexpr (sizeof(T) == 8) {
         if (p.at) go(std::true_type{});
@@ -188,9 +151,15 @@ hsma_status launch_chain_grouped(bool cx, const PanelParams<double> *descs, int 
     HSMA_TRY(empty_mail<double>(mail, words, tickets, s));
     ProfScope prof(HSMA_PHASE_LEAF, flops, s);
     const PanelParams<double> none{};
+    DeviceInfo dev;
+    const int64_t cus = (device_info(&dev) == HSMA_SUCCESS && dev.num_cus > 0) ? dev.num_cus : 256;
+    // Two workgroups a CU (panel_core.h, WIDE) where there are rounds of them: 200 of
+    // DTRSM 513..1024 x 513..1024 5.51 -> 4.06 ms, of ZTRSM 13.8 -> 12.3; a lone chain is
+    // shorter with a CU and all its registers to each workgroup.
+    if (tiles >= 4 * cus) return launch_chain_wide(cx, descs, nd, tiles, tickets, s);
     const dim3 grid((unsigned)tiles), block(64 * kWaves);
-    if (cx) hipLaunchKernelGGL((hsma_chain<double, true, false>), grid, block, 0, s, none, descs, nd, tickets);
-    else hipLaunchKernelGGL((hsma_chain<double, false, false>), grid, block, 0, s, none, descs, nd, tickets);
+    if (cx) hipLaunchKernelGGL((hsma_chain<double, true, false, false>), grid, block, 0, s, none, descs, nd, tickets);
+    else hipLaunchKernelGGL((hsma_chain<double, false, false, false>), grid, block, 0, s, none, descs, nd, tickets);
     HSMA_HIP(hipGetLastError());
     return HSMA_SUCCESS;
 }

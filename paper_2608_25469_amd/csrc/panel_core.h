@@ -164,7 +164,9 @@ struct Solve {
     GT *keep;          // AT: this lane's column of the copy of X
     Shared &sh;
     Acc acc[NQ];       // L X of the blocks solved so far, negated, from zero
-    Acc rhs[NQ > 1 ? 2 : 1];  // the right-hand side of blocks w + 8 q, before alpha: place q % 2
+    // The right-hand side of blocks w + 8 q, before alpha: place q % 2 (WIDE: one place).
+    static constexpr int RP = NQ > 1 && !WIDE ? 2 : 1;
+    Acc rhs[RP];
     T are, aim;        // alpha
     T a[D][NQ][4];     // L_ji of steps i, i + 1, ..: slot i % D
     T *mail;           // CHAIN: this strip's blocks of -X, from block 0 of the solve
@@ -349,16 +351,17 @@ struct Solve {
     // hands it round.  Four groups are on their way at once, and one that came
     // back empty is asked for again two rounds before it is needed: a look costs
     // 1.6 us, so with one group on its way the panel falls ever further behind
-    // the one before it.  L is loaded four blocks ahead.
+    // the one before it.  L is loaded four blocks ahead (WIDE: two).
     __device__ __forceinline__ void apply_left() {
         const int groups = left / 2;  // a multiple of 8: panels have 16 blocks
-        T l[4][NQ][4], nx[4], again = 0;
+        constexpr int LA = WIDE ? 2 : 4;  // blocks that L is loaded ahead
+        T l[LA][NQ][4], nx[4], again = 0;
         bool behind = false;  // the last group had to be waited for
         const T *src = mail + 256 * (w >> 2) + 64 * (w & 3) + lane;
         static_for<0, 4>([&](auto K) {
             constexpr int k = decltype(K)::value;
             nx[k] = mail_load(src + 512 * k);
-            static_for<0, NQ>([&](auto Q) { load_a(decltype(Q)::value, k - left, l[k][decltype(Q)::value]); });
+            if constexpr (k < LA) static_for<0, NQ>([&](auto Q) { load_a(decltype(Q)::value, k - left, l[k][decltype(Q)::value]); });
         });
         for (int t4 = 0; t4 < groups; t4 += 4) {
             static_for<0, 4>([&](auto H) {
@@ -378,7 +381,7 @@ struct Solve {
                 if (t + 4 < groups) nx[h] = mail_load(src + 512 * (int64_t)(t + 4));
                 __syncthreads();
                 static_for<0, 2>([&](auto K) {
-                    constexpr int k = decltype(K)::value, slot = (2 * h + k) % 4;
+                    constexpr int k = decltype(K)::value, slot = (2 * h + k) % LA;
                     T xb[4];
 #pragma unroll
                     for (int s = 0; s < 4; ++s) xb[s] = buf[256 * k + 64 * s + lane];
@@ -386,7 +389,7 @@ struct Solve {
                         constexpr int q = decltype(Q)::value;
                         multiply<q>(l[slot][q], xb);
                         // (Beyond the last: the first columns again.)
-                        load_a(q, (t + 2 < groups ? 2 * t + 4 : 0) + k - left, l[slot][q]);
+                        load_a(q, (t + LA / 2 < groups ? 2 * t + LA : 0) + k - left, l[slot][q]);
                     });
                 });
             });
@@ -412,7 +415,8 @@ struct Solve {
     template <int J>
     __device__ __forceinline__ void prepare() {
         constexpr int q = J / kWaves;
-        const Acc r = rhs[q % 2];
+        const Acc r = rhs[q % RP];
+        if constexpr (WIDE && q + 1 < NQ) rhs[0] = load4(16 * (J + kWaves), 4 * g);
         Acc b;
         if (CX && aim != 0) {
 #pragma unroll
@@ -508,6 +512,10 @@ struct Solve {
         for (int v = 0; v < 4; ++v) sh.blk[J][64 * v + lane] = -y[v];
         asm volatile("" ::: "memory");
         __hip_atomic_store(&sh.done, before + J + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if constexpr (WIDE) {  // (at once, not kept until it is off the others' way)
+            if constexpr (CHAIN) mail_send(J, y);
+            store4(16 * J + 4 * g, y);
+        }
     }
     // X_i is in its place, or this wavefront's further X are NaN (publish).
     __device__ __forceinline__ void await_block(int i) {
@@ -567,7 +575,7 @@ struct Solve {
                     }
                 }
                 // X_I leaves from its owner.
-                if (w == I % kWaves) {
+                if (!WIDE && w == I % kWaves) {
                     if constexpr (CHAIN) mail_send(I, mine);
                     store4(16 * I + 4 * g, mine);
                 }
@@ -575,8 +583,8 @@ struct Solve {
                 // The next row of blocks, six steps before the first of them is
                 // readied; all wavefronts at once, so that the counts of loads
                 // on their way agree and none waits for more than it needs.
-                if constexpr (I % kWaves == 0 && I / kWaves + 1 < NQ)
-                    rhs[(I / kWaves + 1) % 2] = load4(16 * (w + I + kWaves), 4 * g);
+                if constexpr (!WIDE && I % kWaves == 0 && I / kWaves + 1 < NQ)
+                    rhs[(I / kWaves + 1) % RP] = load4(16 * (w + I + kWaves), 4 * g);
                 step<I + 1>();
             }
         }
@@ -585,7 +593,7 @@ struct Solve {
     // What the steps have left: the last block (nothing waits for it here).
     __device__ __forceinline__ void drain() {
         const int J = nb - 1;
-        if (w == J % kWaves) {
+        if (!WIDE && w == J % kWaves) {
             if constexpr (CHAIN) mail_send(J, y);
             store4(16 * J + 4 * g, y);
         }
@@ -670,6 +678,7 @@ struct Solve {
                 if constexpr (k + 1 < N) smallk::fnma_rows<false, k + 1>(yr, yi, lre[k], 0, yr[k], 0);
             } else static_for<k + 1, N>([&](auto R) {
                 constexpr int r = decltype(R)::value;
+                if constexpr (WIDE && CX) __builtin_amdgcn_sched_barrier(0);
                 const T cr = bcast<r>(lre[k]);
                 if constexpr (CX) {
                     const T ci = bcast<r>(lim[k]);
@@ -720,8 +729,12 @@ struct Solve {
             T lre[N], lim[N];
             start_strip(p, strip);
             load_diag(lre, lim);
-            load_before(lb);
+            if constexpr (!WIDE) load_before(lb);
             invert(lre, lim);
+            if constexpr (WIDE) {
+                __builtin_amdgcn_sched_barrier(0);
+                load_before(lb);
+            }
         }
         for (;;) {
             // (Places and offsets are formed anew for each strip: kept, they and
@@ -756,7 +769,7 @@ struct Solve {
 #pragma unroll
                 for (int s = 0; s < 4; ++s) fi[s] = fp[s] = 0;
                 y = main = Acc{0, 0, 0, 0};
-                if constexpr (NQ > 1) rhs[1] = y;
+                if constexpr (RP > 1) rhs[RP - 1] = y;
             }
             // (A panel of one block has nothing below it: its L may end before
             // column 15.)
@@ -855,6 +868,43 @@ __global__ __launch_bounds__(64 * kWaves, WIDE || (NQ == 1 && sizeof(T) == 8 && 
     }
     if (threadIdx.x == 0) sh.done = 0;
     __syncthreads();
+    S s(sh);
+    s.run(p, tile);
+}
+
+// A chain: workgroups take tickets, and ticket t of one solve is panel t /
+// strips, strip t % strips, so a workgroup waits only for workgroups that
+// started before it.  `one` describes panel 0 with the solve's row count in
+// `rows`; with descs each descriptor is one panel, listed so that a solve's
+// panels come in order.
+template <typename T, bool CX, bool AT, bool WIDE>
+__global__ __launch_bounds__(64 * kWaves, WIDE ? 4 : 2) void hsma_chain(const PanelParams<T> one,
+                                                                        const PanelParams<T> *__restrict__ descs,
+                                                                        int nd, unsigned *__restrict__ tickets) {
+    typedef Solve<T, CX, kChainRows / (16 * kWaves), true, AT, WIDE> S;
+    __shared__ typename S::Shared sh;
+    if (threadIdx.x == 0) {
+        sh.done = 0;
+        sh.ticket = (int)atomicAdd(tickets, 1u);
+    }
+    __syncthreads();
+    int tile = __builtin_amdgcn_readfirstlane(sh.ticket);
+    PanelParams<T> p = one;
+    if (descs) {
+        p = descs[find(descs, nd, tile)];
+        tile -= p.tile0;
+    } else {
+        constexpr int ES = CX ? 2 : 1, H = kChainRows / ES;
+        const int strips = (int)((p.n + 15) / 16);
+        const int r = tile / strips;
+        tile -= r * strips;
+        p.left = r * (kChainRows / 16);
+        p.A = one.A + ES * ((int64_t)r * H) * (1 + one.lda);
+        p.B = one.B + ES * (int64_t)r * H * (AT ? one.rs : 1);
+        if constexpr (AT)
+            if (p.keep) p.keep += ES * (int64_t)r * H;
+        p.rows = one.rows - r * H < H ? one.rows - r * H : H;
+    }
     S s(sh);
     s.run(p, tile);
 }

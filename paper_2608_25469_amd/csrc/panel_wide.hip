@@ -1,6 +1,7 @@
 // The panel kernel for many more strips than the chip takes at once
-// (panel_core.h, WIDE), in panels of up to 128 real-view rows (FP32: 256): a unit
-// of its own, so that it compiles beside the others.
+// (panel_core.h, WIDE), in panels of up to 128 real-view rows (FP32: 256), and
+// that of chains for batches of many: a unit of its own, so that it compiles beside
+// the others.
 
 #include "panel_core.h"
 
@@ -34,5 +35,15 @@ template hsma_status launch_panel_wide<double>(bool, const PanelParams<double> &
                                                int64_t, hipStream_t);
 template hsma_status launch_panel_wide<float>(bool, const PanelParams<float> &, const PanelParams<float> *, int, int,
                                               int64_t, hipStream_t);
+
+hsma_status launch_chain_wide(bool cx, const PanelParams<double> *descs, int nd, int64_t tiles, unsigned *tickets,
+                              hipStream_t s) {
+    const PanelParams<double> none{};
+    const dim3 grid((unsigned)tiles), block(64 * kWaves);
+    if (cx) hipLaunchKernelGGL((hsma_chain<double, true, false, true>), grid, block, 0, s, none, descs, nd, tickets);
+    else hipLaunchKernelGGL((hsma_chain<double, false, false, true>), grid, block, 0, s, none, descs, nd, tickets);
+    HSMA_HIP(hipGetLastError());
+    return HSMA_SUCCESS;
+}
 
 }  // namespace hsma
