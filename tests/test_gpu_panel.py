@@ -292,3 +292,28 @@ def test_more_columns_than_one_launch_of_strips():
     want = (1 - torch.arange(m, device="cuda") % 2).float()
     for c in range(0, n, 1 << 24):
         assert bool((B[:, c:c + (1 << 24)] == want[:, None]).all()), c
+
+
+@pytest.mark.parametrize("dt", list("dzsc"))
+def test_chains_that_overlap(dt):
+    """Chains enqueued in turn on two streams with no wait between them, so that
+    two run at once and workspace passes from stream to stream while in use: the
+    bits of each alone."""
+    g = torch.Generator(device="cuda").manual_seed(17)
+    cases = []
+    for m, n in ((1300, 40), (2049, 17), (700, 333), (3000, 100)):
+        L = _colmajor(torch.tril(_ints((m, m), dt, -2, 2, g), -1) / m + 1.5 * torch.eye(m, dtype=DT[dt], device="cuda"))
+        B = _colmajor(_ints((m, n), dt, -3, 3, g))
+        alone = B.clone()
+        hs.trsm(L, alone)
+        torch.cuda.synchronize()
+        cases.append((L, B, alone, [B.clone() for _ in range(6)]))
+    sides = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for rep in range(6):
+        for k, (L, _, _, X) in enumerate(cases):
+            hs.trsm(L, X[rep], stream=sides[(rep + k) % 2])
+    torch.cuda.synchronize()
+    for k, (_, _, alone, X) in enumerate(cases):
+        for rep, x in enumerate(X):
+            assert torch.equal(x, alone), (dt, k, rep)
