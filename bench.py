@@ -303,7 +303,7 @@ def run_single_problem(args, torch, hs, cfg):
         avg = up["ms"] / up["launches"]
         ach = (up["flops"] / up["launches"]) / (avg * 1e-3) / 1e12
         peak = FP32_PEAK_TFLOPS if f32 else FP64_PEAK_TFLOPS
-        roof = {"bound": "mfma", "kernel": "hsma_gemm32 (trailing-update role)" if f32 else
+        roof = {"bound": "mfma", "kernel": "hsma_gemm (trailing-update role, FP32)" if f32 else
                 "hsma_gemm (trailing-update role)", "achieved": round(ach, 3),
                 "peak": peak, "unit": "TFLOP/s", "frac": round(ach / peak, 4),
                 "traffic": measured_traffic("gemm_update_dtrsm16384_traffic", GEMM_SOURCES,
@@ -350,7 +350,8 @@ def run_single_problem(args, torch, hs, cfg):
         "pct_fp64_peak": round(100 * value / (FP64_PEAK_TFLOPS * 1e3), 2),
         "pct_of_own_peak": round(100 * value / (out_peak * 1e3), 2),
         "extra_config": {"m": m, "n": n, "complex": cx, "path": rep["path"],
-                         "block_size": rep["block_size"], "flops_per_step": fl},
+                         # as given to the library; 0: its own panels or chain
+                         "block_size": args.ib, "flops_per_step": fl},
         "phases": phases, "parity": parity, "roofline": roof, "rocblas": rocblas, "cpu_baseline": cpu,
     }
 

@@ -216,8 +216,9 @@ typedef enum {
 /* Options of hsma_trsm_ex.  Zero-initialise and set what you need. */
 typedef struct {
     int32_t block_size;   /* rows of a panel of the blocked path: 16, 32, 64,
-                             128 or 256; 0 = as many as one launch takes (512
-                             real or 256 complex) */
+                             128 or 256; 0 = 512 real or 256 complex rows, from
+                             65536 columns 128 and 64 (FP32: 256 and 128), or
+                             one chained launch */
     int32_t path;         /* 0 = automatic (m <= 64 small kernel, else blocked);
                              1 = force the small kernel (requires m <= 64);
                              2 = force the blocked path */
@@ -373,7 +374,8 @@ hsma_status hsma_batch_plan_destroy(hsma_batch_plan *plan);
  * and stops recording.  Process-wide; meant for benchmarks and profiling.
  */
 typedef enum {
-    HSMA_PHASE_DIAG_INV = 0,  /* diagonal-block inversion (base kernel + merges) */
+    HSMA_PHASE_DIAG_INV = 0,  /* always empty: panels invert their diagonal blocks
+                                 themselves (HSMA_PHASE_LEAF) */
     HSMA_PHASE_UPDATE = 1,    /* trailing updates B_bot -= L_bot,top X_top */
     HSMA_PHASE_LEAF = 2,      /* diagonal solves X_r = alpha inv(D_r) B_r */
     HSMA_PHASE_SMALL = 3,     /* small-regime solves (m <= 64) */

@@ -6,8 +6,9 @@ panel) and keep the fastest.  The results go to a JSON file (written after every
 measurement, so an interrupted sweep resumes) and are turned into the
 compiled-in table ``csrc/tuning_gfx950.h``; at run time the library picks the
 entry of the nearest tested scale (``hsma_lookup_block_size``).  A solve that
-is given no block size reports that entry and sizes its footprint by it; its
-panels are as tall as the kernel takes.
+is given no block size reports that entry, and ``hsma_trsm_noalloc`` takes the
+sizes whose workspace of inverted blocks of that edge would fit its array; the
+solve itself has panels as tall as the kernel takes.
 
   python -m paper_2608_25469_amd.autotune sweep  --out results.json   (GPU)
   python -m paper_2608_25469_amd.autotune header --json results.json  (CPU)

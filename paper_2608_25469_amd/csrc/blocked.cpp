@@ -28,13 +28,15 @@ namespace hsma {
 
 // Whether a solve runs as one chain launch (panel.hip) instead of the recursion:
 // where few columns leave the recursion's launches mostly empty.  Measured, us,
-// chain / recursion in panels of 256 rows: DTRSM 1024 x 256 74 / 90, 1024 x
-// 1024 80 / 100, 4096 x 256 276 / 448, 4096 x 1024 571 / 617, 8192 x 256 756 /
-// 1114; ZTRSM 1024 x 256 129 / 195, 2048 x 1024 527 / 602, 8192 x 256 2022 /
-// 2833; STRSM 4096 x 256 174 / 378.  Beyond the rule the recursion in its own
-// panels of 512 rows is ahead or level: an earlier chain took 180 at 1024 x 4096
-// (130), 1992 at 8192 x 1024 (1747), ZTRSM 1800 at 4096 x 1024 (1751).  Up to
-// 512 real-view rows one panel is as fast (37 against 41) and needs no mail.
+// chain / recursion in panels of 512 real-view rows: DTRSM 513 x 256 48 / 64, 1000
+// x 256 73 / 83, 1000 x 1024 77 / 88, 2000 x 256 140 / 189, 2000 x 1024 189 / 220,
+// 4000 x 256 275 / 427, 4000 x 1024 567 / 585, 8000 x 256 774 / 1068, 1500 x 1024
+// 158 / 151; ZTRSM 300 x 256 49 / 57, 1000 x 300 130 / 200, 2000 x 1024 508 / 605,
+// 4000 x 256 624 / 1038, 8000 x 256 1983 / 2804; STRSM 1000 x 256 51 / 61, 4000 x
+// 256 174 / 326, 8000 x 256 437 / 742.  Beyond the rule an earlier chain was behind
+// or level: DTRSM 1024 x 4096 180 (130), 8192 x 1024 1992 (1747), ZTRSM 4096 x 1024
+// 1800 (1751).  Up to 512 real-view rows one panel is as fast (37 against 41) and
+// needs no mail.
 bool chain_rule(bool cx, int elem, int64_t m, int64_t n) {
     const int64_t mr = m * (cx ? 2 : 1), mail = mr * ((n + 15) / 16 * 16) * elem;
     if (mr <= kPanelRows || n > 1024 || mail > (int64_t)HSMA_NOALLOC_SCRATCH_BYTES / 2) return false;

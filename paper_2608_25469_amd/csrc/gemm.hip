@@ -75,10 +75,10 @@ hsma_status launch_mixed(const GemmParams &p, hipStream_t s) {
     const int64_t cus = (device_info(&dev) == HSMA_SUCCESS && dev.num_cus > 0) ? dev.num_cus : 256;
     auto tiles = [&](int bm, int bn) { return (int64_t)((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn); };
     if (p.M >= 128 && tiles(128, 128) >= 2 * cus)
-        return launch_tiles<double, float, false, false, 128, 128, 16, 2, 2, 2, 2, 256>(p, HSMA_PHASE_UPDATE, s);
+        return launch_tiles<double, float, false, false, 128, 128, 16, 2, 2, 2, 256>(p, HSMA_PHASE_UPDATE, s);
     if (p.M >= 64 && tiles(64, 64) >= cus)
-        return launch_tiles<double, float, false, false, 64, 64, 16, 2, 2, 3, 2, 256>(p, HSMA_PHASE_UPDATE, s);
-    return launch_tiles<double, float, false, false, 32, 32, 64, 2, 2, 3, 2, 256>(p, HSMA_PHASE_UPDATE, s);
+        return launch_tiles<double, float, false, false, 64, 64, 16, 2, 2, 3, 256>(p, HSMA_PHASE_UPDATE, s);
+    return launch_tiles<double, float, false, false, 32, 32, 64, 2, 2, 3, 256>(p, HSMA_PHASE_UPDATE, s);
 }
 
 // Grouped launch: descriptor d owns tiles [d.tile0, d.tile0 + tiles_m
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(256, OCC) void hsma_gemm_grouped(const GemmParams *
     const GemmParams p = descs[lo];
     const int local = t - p.tile0;
     if (local < 0 || local >= p.tiles_m * p.tiles_n) return;
-    gemm_tile<double, double, CX, false, BM, BN, BK, WM, WN, 2, BK>(
+    gemm_tile<double, double, CX, false, BM, BN, BK, WM, WN, BK>(
         p, (const HSMA_GLOBAL double *)p.A, (const HSMA_GLOBAL double *)p.B, (HSMA_GLOBAL double *)p.C,
         local % p.tiles_m, local / p.tiles_m);
 }
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(256, OCC) void hsma_gemm_grouped(const GemmParams *
 template <bool CX, int BM, int BN, int BK, int WM, int WN>
 hsma_status grouped_t(const GemmParams *descs, int nd, int64_t tiles, int phase, double flops,
                       hipStream_t s) {
-    constexpr int OCC = gemmk::occupancy(gemmk::ring_bytes<double, CX>(BM, BN, BK, 2), most_wg(BM, BN));
+    constexpr int OCC = gemmk::occupancy(gemmk::ring_bytes<double, CX>(BM, BN, BK), most_wg(BM, BN));
     ProfScope prof(phase, flops, s);
     hipLaunchKernelGGL((hsma_gemm_grouped<CX, BM, BN, BK, WM, WN, OCC>), dim3((unsigned)tiles), dim3(256), 0,
                        s, descs, nd);
@@ -124,11 +124,7 @@ hsma_status grouped_shape(int bm, int bn, const GemmParams *descs, int nd, int64
 
 }  // namespace
 
-int gemm_grouped_tile(int max_m, int max_n, int *bm, int *bn) {
-    (void)max_m;
-    *bm = *bn = max_n <= 32 ? 32 : max_n <= 256 ? 64 : 128;
-    return 1;
-}
+void gemm_grouped_tile(int max_n, int *bm, int *bn) { *bm = *bn = max_n <= 32 ? 32 : max_n <= 256 ? 64 : 128; }
 
 hsma_status launch_gemm_grouped(bool cplx_, int bm, int bn, const GemmParams *descs,
                                 int nd, int64_t total_tiles, double flops, hipStream_t s) {

@@ -9,9 +9,9 @@
 //
 // Tiling: a 256-thread workgroup (4 wavefronts) owns a BM x BN tile of C,
 // each wavefront a (BM/WM) x (BN/WN) sub-tile held as 16x16 accumulator
-// blocks.  K advances BK at a time through a ring of NS LDS stages, filled by
-// direct global-to-LDS loads (16 bytes a lane) NS - 1 slices ahead, one
-// barrier per slice.
+// blocks.  K advances BK at a time through a ring of two LDS stages, filled by
+// direct global-to-LDS loads (16 bytes a lane) a slice ahead, one barrier per
+// slice.
 //
 // What bounds it: the matrix cores.  On the DTRSM 16384 top update (M = K =
 // 8192, N = 16384) staging through registers, with a bounds test around each
@@ -105,8 +105,8 @@ struct Mma<float> {
 };
 
 template <typename TG, bool CX>
-constexpr int ring_bytes(int bm, int bn, int bk, int ns) {
-    return ns * ((CX ? bk / 2 : bk) * bm + bn * bk) * (int)sizeof(TG);
+constexpr int ring_bytes(int bm, int bn, int bk) {
+    return 2 * ((CX ? bk / 2 : bk) * bm + bn * bk) * (int)sizeof(TG);
 }
 // Workgroups per CU the ring allows (160 KB of LDS per CU, at most `most`);
 // the launch bound then caps registers so that many stay resident.
@@ -117,24 +117,10 @@ constexpr int occupancy(int bytes, int most) {
 
 typedef __attribute__((address_space(3))) void lds_void;
 
-// 16 bytes per lane from src to LDS at dst + 16 lane (dst the same in every
-// lane).  WAIT: by the compiler's builtin, which makes every later read of LDS
-// wait for the load, whatever stage it reads; otherwise by an instruction that
-// only `arrive` in gemm_tile waits for.
-template <bool WAIT>
-__device__ __forceinline__ void load_to_lds(const void *src, lds_void *dst) {
-    if constexpr (WAIT) {
-        __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0);
-    } else {
-        const unsigned at = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)dst);
-        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(at) : "m0");
-    }
-}
-
 // One BM x BN tile (tm, tn).  TG is the data type in memory and LDS, TM the
 // type on the matrix cores; GD is TG, or HSMA_GLOBAL TG where pointers come
 // from a descriptor table.  TRI: A is lower triangular (p.tri_a, p.k_lower).
-template <typename TG, typename TM, bool CX, bool TRI, int BM, int BN, int BK, int WM, int WN, int NS,
+template <typename TG, typename TM, bool CX, bool TRI, int BM, int BN, int BK, int WM, int WN,
           int KCHUNK, typename P, typename GD>
 __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
                                           const GD *__restrict__ Bg, GD *__restrict__ Cg, int tm,
@@ -147,18 +133,14 @@ __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
     constexpr int KA = CX ? BK / 2 : BK;     // stored columns of A per slice
     constexpr int PA = BM / V, PB = BK / V;  // pieces per column of A, of B
     constexpr bool SWZ_A = sizeof(TG) == 4 && !CX && BM >= 64;
-    // Where in a slice the next fill is issued: before the first read of LDS
-    // (-1), or at k-step FILL_AT; and whether the reads of LDS after it wait
-    // for it (TURNS).  With 128 x 128 tiles they do: two workgroups share a CU
-    // and fall into turns, one filling while the other multiplies, and a fill
-    // before the first read is best where the products are plain (72.3
-    // against 67.8 TF/s in FP64 at 8192^3, FP32 140 against 132), in mid-slice
-    // where fragments need work (complex 71.4 against 69.0, mixed 106 against
-    // 101).  Not waiting costs the large tiles 4 % (the fills of both
-    // workgroups then compete with their reads) and gains small ones, often
-    // alone on their CU, a fifth (32 x 32, K = 8192: 117 against 145 us).
-    constexpr bool TURNS = BM * BN >= 128 * 128;
-    constexpr int FILL_AT = (CX || MIXED || !TURNS) ? BK / 8 - 1 : -1;
+    // Where in a slice the next fill is issued: before the first read of LDS (-1)
+    // or at k-step FILL_AT.  Every read of LDS after it waits for it.  With 128 x
+    // 128 tiles two workgroups share a CU and fall into turns, one filling while
+    // the other multiplies, and a fill before the first read is best where the
+    // products are plain (72.3 against 67.8 TF/s in FP64 at 8192^3, FP32 140
+    // against 132), in mid-slice where fragments need work (complex 71.4 against
+    // 69.0, mixed 106 against 101) and for smaller tiles.
+    constexpr int FILL_AT = (CX || MIXED || BM * BN < 128 * 128) ? BK / 8 - 1 : -1;
     static_assert(!TRI || !SWZ_A, "the triangle is masked by LDS position");
     static_assert(WM * WN == 4, "four wavefronts");
     static_assert(TMR % 16 == 0 && TNC % 16 == 0, "16x16 blocks");
@@ -169,8 +151,8 @@ __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
     typedef typename Mma<TM>::Acc Acc;
     typedef typename Mma<TG>::Acc AccG;
 
-    __shared__ __attribute__((aligned(16))) TG As[NS][KA * BM];
-    __shared__ __attribute__((aligned(16))) TG Bs[NS][BN * BK];
+    __shared__ __attribute__((aligned(16))) TG As[2][KA * BM];
+    __shared__ __attribute__((aligned(16))) TG Bs[2][BN * BK];
 
     const int m0 = tm * BM, n0 = tn * BN;
     const int M = p.M, N = p.N;
@@ -268,15 +250,9 @@ __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
 #pragma unroll
         for (int it = 0; it < B_IT; ++it) pb[it] += BK;
     };
-    // Every wavefront's fills but those of the last NS - 2 slices have landed
-    // (LDS stores too), and every wavefront is done reading the stage that
-    // the next fill overwrites.  A wavefront that issues fewer loads per
-    // slice than A_IT + B_IT waits for its share.
-    auto arrive = [&](bool all) {
-        constexpr int L = (NS - 2) * (A_IT + B_IT);
-        if (NS == 2 || all || !(a_on && b_on)) asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(L) : "memory");
-    };
+    // Every wavefront's fill has landed (LDS stores too), and every wavefront is
+    // done reading the stage that the next fill overwrites.
+    auto arrive = [&] { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
     Acc acc[FM][FN];
     AccG accg[MIXED ? FM : 1][MIXED ? FN : 1];
@@ -289,10 +265,8 @@ __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
         }
 
     const int nk = (K + BK - 1) / BK;
-#pragma unroll
-    for (int q = 0; q < NS - 1; ++q)
-        if (q < nk) fill(q * BK, q);
-    arrive(nk < NS);
+    if (nk > 0) fill(0, 0);
+    arrive();
     const int lr = lane & 15, lk = lane >> 4;
     const int row_a = Mma<TM>::a_row(lr);
     // This lane's A element within a 16-row block (the component swap of a
@@ -307,8 +281,8 @@ __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
         bk[s] = (wn0 + lr) * BK + V * (((4 * s + lk) / V) ^ swz_b(lr)) + (4 * s + lk) % V;
     int buf = 0;
     for (int kt = 0; kt < nk; ++kt) {
-        const bool ahead = kt + NS - 1 < nk;
-        if (FILL_AT < 0 && ahead) fill((kt + NS - 1) * BK, buf == 0 ? NS - 1 : buf - 1);
+        const bool ahead = kt + 1 < nk;
+        if (FILL_AT < 0 && ahead) fill((kt + 1) * BK, buf ^ 1);
         const TG *as = As[buf];
         const TG *bs = Bs[buf];
         if constexpr (TRI) {
@@ -334,7 +308,7 @@ __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
             }
 #pragma unroll
             for (int j = 0; j < FN; ++j) fb[j] = (TM)bs[bk[s] + 16 * j * BK];
-            if (FILL_AT == s && ahead) fill((kt + NS - 1) * BK, buf == 0 ? NS - 1 : buf - 1);
+            if (FILL_AT == s && ahead) fill((kt + 1) * BK, buf ^ 1);
 #pragma unroll
             for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -352,8 +326,8 @@ __device__ __forceinline__ void gemm_tile(const P &p, const GD *__restrict__ Ag,
                     }
             }
         }
-        arrive(!ahead);
-        buf = buf + 1 == NS ? 0 : buf + 1;
+        arrive();
+        buf ^= 1;
     }
 
     // ---- epilogue: C = beta*C + alpha*acc, four rows of a column at a time ----
@@ -456,19 +430,19 @@ __device__ __forceinline__ bool tile_of(int bid, int nb, int tiles_m, int tiles_
     return true;
 }
 
-template <typename TG, typename TM, bool CX, bool TRI, int BM, int BN, int BK, int WM, int WN, int NS,
+template <typename TG, typename TM, bool CX, bool TRI, int BM, int BN, int BK, int WM, int WN,
           int KCHUNK, int OCC, typename P>
 __global__ __launch_bounds__(256, OCC) void hsma_gemm(const P p) {
     int tm, tn;
     if (!tile_of(blockIdx.x, gridDim.x, p.tiles_m, p.tiles_n, p.k_lower || p.c_lower, tm, tn)) return;
-    gemm_tile<TG, TM, CX, TRI, BM, BN, BK, WM, WN, NS, KCHUNK>(p, p.A, p.B, p.C, tm, tn);
+    gemm_tile<TG, TM, CX, TRI, BM, BN, BK, WM, WN, KCHUNK>(p, p.A, p.B, p.C, tm, tn);
 }
 
 // Launch of one product with tiles of BM x BN.
 template <typename TG, typename TM, bool CX, bool TRI, int BM, int BN, int BK, int WM, int WN, int MOST = 3,
-          int NS = 2, int KCHUNK = BK, typename P>
+          int KCHUNK = BK, typename P>
 hsma_status launch_tiles(P p, int phase, hipStream_t s) {
-    constexpr int OCC = occupancy(ring_bytes<TG, CX>(BM, BN, BK, NS), MOST);
+    constexpr int OCC = occupancy(ring_bytes<TG, CX>(BM, BN, BK), MOST);
     p.tiles_m = (p.M + BM - 1) / BM;
     p.tiles_n = (p.N + BN - 1) / BN;
     const int64_t T = (int64_t)p.tiles_m * p.tiles_n;
@@ -476,7 +450,7 @@ hsma_status launch_tiles(P p, int phase, hipStream_t s) {
     if (grid > 0x7fffffff) return HSMA_INVALID_SIZE;
     // A lower-triangular C computes about half of the product.
     ProfScope prof(phase, (p.c_lower ? 1.0 : 2.0) * p.M * (double)p.N * p.K, s);
-    hipLaunchKernelGGL((hsma_gemm<TG, TM, CX, TRI, BM, BN, BK, WM, WN, NS, KCHUNK, OCC, P>),
+    hipLaunchKernelGGL((hsma_gemm<TG, TM, CX, TRI, BM, BN, BK, WM, WN, KCHUNK, OCC, P>),
                        dim3((unsigned)grid), dim3(256), 0, s, p);
     HSMA_HIP(hipGetLastError());
     return HSMA_SUCCESS;

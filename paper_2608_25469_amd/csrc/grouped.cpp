@@ -249,7 +249,7 @@ hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_
             Launch l;
             l.cx = cxi;
             l.panel = k % 2 == 0;
-            int max_m = 0, max_n = 0;
+            int max_n = 0;
             std::vector<int64_t> strips;
             for (size_t pi = 0; pi < ps.size(); ++pi) {
                 const Prob &p = ps[pi];
@@ -263,7 +263,6 @@ hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_
                     l.panels.push_back(q);
                 } else {
                     l.gemms.push_back(op_update(p, o));
-                    max_m = std::max(max_m, l.gemms.back().M);
                     max_n = std::max(max_n, l.gemms.back().N);
                 }
             }
@@ -277,7 +276,7 @@ hsma_status grouped_blocked(const hsma_problem *probs, int64_t count, hipStream_
                     l.tiles += panel_share((q.n + 15) / 16, &q.per);
                 }
             } else {
-                if (!gemm_grouped_tile(max_m, max_n, &l.bm, &l.bn)) return HSMA_NOT_SUPPORTED;
+                gemm_grouped_tile(max_n, &l.bm, &l.bn);
                 for (GemmParams &g : l.gemms) {
                     g.tiles_m = (g.M + l.bm - 1) / l.bm;
                     g.tiles_n = (g.N + l.bn - 1) / l.bn;

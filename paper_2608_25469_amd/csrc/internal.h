@@ -150,9 +150,10 @@ struct GemmParamsT {
 };
 typedef GemmParamsT<double> GemmParams;
 
-// Tile shape a grouped launch of updates uses when its largest product has
-// max_m real-view rows and max_n columns; 0 if unsupported.
-int gemm_grouped_tile(int max_m, int max_n, int *bm, int *bn);
+// Tile shape of a grouped launch of updates whose widest product has max_n columns
+// (not tuned: the widest product's columns, up to four tiles of the next smaller
+// shape).
+void gemm_grouped_tile(int max_n, int *bm, int *bn);
 // Launch over nd descriptors already in device memory (tile0 / tiles_m /
 // tiles_n filled for the shape gemm_grouped_tile returned); total_tiles is
 // the grid size.  flops is for the phase profiler.

@@ -9,10 +9,10 @@
 // is looked up once per device with hipGetSymbolAddress (the array's name is a
 // host-side stand-in in host code, never a device address) and passed to the
 // same kernels hsma_trsm launches, in the same schedule, so the results are
-// bit-for-bit those of hsma_trsm.  A chain clears its flags before it starts
-// and reads no mail before its flag is set, so nothing depends on what an
-// earlier call left there.  Calls that overlap in time on one GPU share the
-// array and race.
+// bit-for-bit those of hsma_trsm.  A chain fills its mail with a word that no
+// arithmetic returns before it starts and takes a place for arrived when it holds
+// anything else, so nothing depends on what an earlier call left there.  Calls that
+// overlap in time on one GPU share the array and race.
 //
 // The sizes it takes are those whose I_B-block workspace would fit the array.
 
@@ -80,7 +80,6 @@ extern "C" hsma_status hsma_trsm_noalloc(hsma_diag diag, int64_t m, int64_t n, c
     const double *Ad = static_cast<const double *>(A);
     if (azero) return launch_zero(m, n, cx ? 2 : 1, Bd, ldb, s);
     if (m <= 64) return launch_small_solve(cx, diag == HSMA_UNIT, (int)m, n, al, Ad, lda, Bd, ldb, s);
-    if (blocked_bytes<double>(cx, m, n, 0, false) > kScratchBytes) return HSMA_WORKSPACE_TOO_SMALL;
     void *ws = nullptr;
     HSMA_TRY(scratch_address(&ws));
     return blocked_trsm(cx, diag == HSMA_UNIT, m, n, al, Ad, lda, Bd, ldb, 0, ws, s, false);

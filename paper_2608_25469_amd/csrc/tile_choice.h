@@ -3,9 +3,10 @@
 //
 // A workgroup stages its A and B tiles through an LDS ring of two slices; the
 // ring's size sets how many workgroups a CU holds (160 KB of LDS, at most
-// three; lower_tile_shape counts 16-deep slices).  For a lower-triangular C only the tiles on or
-// below the diagonal run, and each runs the whole K, so a launch takes about
-// ceil(non-empty tiles / resident slots) rounds of one tile's time;
+// three).  For a lower-triangular C only the tiles on or below the diagonal run, and
+// each runs the whole K, so a launch takes about ceil(non-empty tiles / resident
+// slots) rounds of one tile's time (slots counted as for 16-deep slices, three a CU
+// for the small shapes; their 32- and 64-deep ones hold two);
 // lower_tile_shape picks the shape with the fewest rounds times tile area,
 // weighted by the shape's relative throughput (narrower tiles reuse less of
 // what they stage).
