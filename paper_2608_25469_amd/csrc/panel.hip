@@ -29,7 +29,9 @@ hsma_status launch(const PanelParams<T> &one, const PanelParams<T> *descs, int n
     const dim3 grid((unsigned)groups), block(64 * kWaves);
     auto go = [&](auto AT) {
         constexpr bool at = decltype(AT)::value;
-        if (mr <= 128) hipLaunchKernelGGL((hsma_panel<T, CX, 1, at, false>), grid, block, 0, s, one, descs, nd);
+        // (Strides are for m > 64: complex ones have more than 128 real-view rows.)
+        constexpr int least = CX && at ? 2 : 1;
+        if (mr <= 128) hipLaunchKernelGGL((hsma_panel<T, CX, least, at, false>), grid, block, 0, s, one, descs, nd);
         else if (mr <= 256) hipLaunchKernelGGL((hsma_panel<T, CX, 2, at, false>), grid, block, 0, s, one, descs, nd);
         else hipLaunchKernelGGL((hsma_panel<T, CX, 4, at, false>), grid, block, 0, s, one, descs, nd);
     };

@@ -13,7 +13,8 @@ template <typename T>
 hsma_status launch_panel_wide(bool cx, const PanelParams<T> &one, const PanelParams<T> *descs, int nd, int max_rows,
                               int64_t groups, hipStream_t s) {
     const int mr = max_rows * (cx ? 2 : 1);
-    if (mr > wide_rows(sizeof(T)) || (one.at && sizeof(T) == 4)) return HSMA_NOT_SUPPORTED;
+    // (Strides are for m > 64, so complex ones never have 128 real-view rows.)
+    if (mr > wide_rows(sizeof(T)) || (one.at && (cx || sizeof(T) == 4))) return HSMA_NOT_SUPPORTED;
     const dim3 grid((unsigned)groups), block(64 * kWaves);
     auto go = [&](auto CX, auto AT) {
         constexpr bool z = decltype(CX)::value, at = decltype(AT)::value;
@@ -23,7 +24,7 @@ hsma_status launch_panel_wide(bool cx, const PanelParams<T> &one, const PanelPar
     constexpr std::true_type yes{};
     constexpr std::false_type no{};
     if constexpr (sizeof(T) == 8) {
-        if (one.at) cx ? go(yes, yes) : go(no, yes);
+        if (one.at) go(no, yes);
         else cx ? go(yes, no) : go(no, no);
     } else {
         cx ? go(yes, no) : go(no, no);
