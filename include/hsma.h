@@ -217,7 +217,7 @@ typedef enum {
 typedef struct {
     int32_t block_size;   /* rows of a panel of the blocked path: 16, 32, 64,
                              128 or 256; 0 = 512 real or 256 complex rows, from
-                             65536 columns 128 and 64 (FP32: 256 and 128), or
+                             32768 columns 128 and 64 (FP32: 256 and 128), or
                              one chained launch */
     int32_t path;         /* 0 = automatic (m <= 64 small kernel, else blocked);
                              1 = force the small kernel (requires m <= 64);

@@ -46,10 +46,11 @@ bool chain_rule(bool cx, int elem, int64_t m, int64_t n) {
 // Panels of 512 real-view rows are the shortest way through the rows.  Through many
 // columns it is panels of 128 rows (FP32: 256), which have a kernel that takes them
 // two workgroups a CU and shares its start, with products between them.  Tall /
-// short panels, us: DTRSM 300 x 65536 425 / 295, 512 x 65536 564 / 548, 512 x 16384
-// 142 / 190, 300 x 300000 2025 / 1440; ZTRSM 129 x 65536 397 / 280, 256 x 65536 580 /
-// 613; STRSM 300 x 65536 289 / 233, 300 x 300000 1320 / 792.
-constexpr int64_t kWideColumns = 65536;
+// short panels, us: DTRSM 300 x 24576 161 / 129, 512 x 24576 212 / 229, 512 x 32768
+// 279 / 286, 700 x 32768 497 / 512, 300 x 49152 318 / 219, 512 x 49152 415 / 389;
+// ZTRSM 65 x 32768 92 / 85, 256 x 32768 311 / 314, 150 x 49152 335 / 234; STRSM 512 x
+// 32768 194 / 170; CTRSM 256 x 32768 203 / 165.
+constexpr int64_t kWideColumns = 32768;
 int panel_span(bool cx, int elem, int64_t n) {
     return (n >= kWideColumns ? wide_rows(elem) : kPanelRows) / (cx ? 2 : 1);
 }

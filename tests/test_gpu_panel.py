@@ -246,12 +246,12 @@ def test_error_of_a_solve(dt, m, n):
         assert (got[m // 2] == 0).all() and np.isfinite(got).all(), (dt, m, n)
 
 
-@pytest.mark.parametrize("n", [16400, 65541])
+@pytest.mark.parametrize("n", [16400, 32768, 65541])
 @pytest.mark.parametrize("dt,m", [("d", 65), ("d", 128), ("d", 129), ("d", 300), ("z", 40), ("z", 64), ("z", 150),
                                   ("s", 65), ("s", 256), ("s", 300), ("c", 64), ("c", 65), ("c", 200)])
 def test_many_columns(dt, m, n):
     """Panels of many strips (several a workgroup, panels of another height from
-    65536 columns): the bits of the same panels on a thousand columns."""
+    32768 columns): the bits of the same panels on a thousand columns."""
     span = {"d": 128, "z": 64, "s": 256, "c": 128}[dt]
     g = torch.Generator(device="cuda").manual_seed(m)
     Ls = torch.tril(_ints((m, m), dt, -3, 3, g), -1) / m + 1.5 * torch.eye(m, dtype=DT[dt], device="cuda")
@@ -263,7 +263,7 @@ def test_many_columns(dt, m, n):
     hs.trsm(L, X, 0.5, path=2, unit=m == 129)
     for c in (0, n // 2, n - 1000):
         want = _colmajor(B[:, c:c + 1000])
-        hs.trsm(L, want, 0.5, path=2, unit=m == 129, block_size=span if n >= 65536 and m > span else 0)
+        hs.trsm(L, want, 0.5, path=2, unit=m == 129, block_size=span if n >= 32768 and m > span else 0)
         torch.cuda.synchronize()
         assert torch.equal(X[:, c:c + 1000], want), (dt, m, n, c)
 
